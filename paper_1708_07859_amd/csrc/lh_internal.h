@@ -89,26 +89,35 @@ struct DBuf {  // owning device buffer, freed on the stream it was made on
   }
 };
 
-// A 64-byte pinned host buffer per host thread, kept until the process
-// ends: a scalar read back into pinned memory skips the staging of a
-// pageable copy (about 40 us per read on the sync-heavy paths).
-inline void* pinned_scratch() {
+// A small pinned host buffer per host thread, kept until the process ends.
+// Kernels store the few words that the host waits for straight into it
+// (a store and a wait cost 12 us, a copy of a device scalar into pinned
+// memory 15 us, into pageable memory 22 us).  A thread's next use overwrites
+// it: read the words right after the wait.
+constexpr size_t PINNED_BYTES = 4096;
+inline void*& pinned_slot() {
   thread_local void* p = nullptr;
-  if (!p) LH_HIP(hipHostMalloc(&p, 64, hipHostMallocPortable));
   return p;
 }
+inline void* pinned_scratch() {
+  void*& p = pinned_slot();
+  if (!p) LH_HIP(hipHostMalloc(&p, PINNED_BYTES, hipHostMallocPortable));
+  return p;
+}
+// The same, or null when an arena forbids allocating it now.
+inline void* pinned_scratch_or_null() { return arena_active() ? pinned_slot() : pinned_scratch(); }
 
 template <class T>
 T read_scalar(const T* dptr, hipStream_t s) {
-  static_assert(sizeof(T) <= 64, "read_scalar: at most 64 bytes");
-  if (arena_active()) {
+  static_assert(sizeof(T) <= PINNED_BYTES, "read_scalar: at most PINNED_BYTES");
+  T* h = static_cast<T*>(pinned_scratch_or_null());
+  if (!h) {
     // no host allocation either: read into this frame
     T v;
     LH_HIP(hipMemcpyAsync(&v, dptr, sizeof(T), hipMemcpyDeviceToHost, s));
     LH_HIP(hipStreamSynchronize(s));
     return v;
   }
-  T* h = static_cast<T*>(pinned_scratch());
   LH_HIP(hipMemcpyAsync(h, dptr, sizeof(T), hipMemcpyDeviceToHost, s));
   LH_HIP(hipStreamSynchronize(s));
   return *h;
