@@ -158,13 +158,21 @@ void gather_f64(const double* src, const uint32_t* idx, double* dst, uint64_t n,
 void radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* tkeys, uint32_t* tvals,
                       uint64_t n, uint32_t bits, hipStream_t s, uint32_t lo_bit = 0);
 
+// What travels with a sort's rows: nothing (bytes 0), the input row of each
+// sorted position (bytes 4, in null), or one column of 4 or 8 bytes (in; it
+// may not alias out).
+struct SortValue {
+  const void* in = nullptr;
+  void* out = nullptr;
+  uint32_t bytes = 0;
+};
+
 // Sort rows lexicographically by cols[0], cols[1], ... when their bits add
-// up to at most 64: one packed key per row, radix-sorted, then unpacked into
-// the sorted columns (ncols buffers of n).  perm (n entries, may be null)
-// receives the input row of each sorted position.  Rows already sorted by
+// up to at most 96: one packed key per row, radix-sorted, then unpacked into
+// the sorted columns (ncols buffers of n).  Rows already sorted by
 // the last sorted_tail columns are sorted by the others only (stably).  Returns false, doing
-// nothing, when the keys do not fit one word.
-bool sort_packed(const uint32_t* const* cols, const uint32_t* bits, uint32_t ncols, uint64_t n, uint32_t* perm,
+// nothing, when the keys do not fit.
+bool sort_packed(const uint32_t* const* cols, const uint32_t* bits, uint32_t ncols, uint64_t n, const SortValue& val,
                  uint32_t* const* sorted, hipStream_t s, uint32_t sorted_tail = 0);
 
 // Permutation that sorts rows lexicographically by cols[0], cols[1], ...

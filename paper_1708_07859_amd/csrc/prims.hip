@@ -2,6 +2,7 @@
 #include <algorithm>
 #include <climits>
 #include <cstring>
+#include <type_traits>
 
 #include "device_common.h"
 #include "lh_internal.h"
@@ -222,27 +223,45 @@ unsigned grid_for(uint64_t n) {
 }
 
 // ---------------------------------------------------------------------------
-// LSD radix sort, 8-bit digits.  Per pass: tile histograms (digit-major, so
-// an exclusive scan yields every tile's first slot per digit), then a
-// stable scatter that ranks equal digits inside a wave with eight ballots
-// and across the block's waves through LDS.  A sort of key columns reads
-// the columns in its first pass (packing each row's key on the fly) and
-// writes the sorted columns in its last (unpacking them), so no pass of
-// its own packs or unpacks.
+// LSD radix sort, 8-bit digits, one kernel per pass.  Memory bounds a pass:
+// every key is read once and written once, in runs of equal digits.  One
+// kernel first counts the digits of all passes in a single read of the
+// input; a pass then needs, for its tile's first slot of each digit, only
+// the counts of the tiles before it, which it adds up from what they publish
+// (decoupled look-back) while its own keys are ranked.  A sort of key
+// columns reads the columns in its first pass (packing each row's key on the
+// fly) and writes the sorted columns in its last (unpacking them).  Keys of
+// 65 to 96 bits are two words; a value (the row permutation, or the one
+// column that must follow) travels along.  Sorts of one tile run all passes
+// in one launch, in LDS.
+// Tiles of 4096 keys by 512 threads: runs of 16 keys (128 bytes) per digit
+// on average, and 33 KB of LDS leaves four tiles (32 waves) on a CU; tiles
+// of 8192 keys measured the same on 64 M keys and 30% slower on 1 M.
+// 64 M 44-bit keys, six passes: 0.36 ms of counting and 0.37 ms per pass
+// (2.8 TB/s), 2.56 ms in all; a count, a scan of seven kernels and a scatter
+// per pass took 3.7 ms.  A whole trie build of 20 M rows of 66
+// bits with an annotation: 5.2 ms, 7.4 ms when the row permutation was
+// sorted by two packed words and the columns gathered through it.
 // ---------------------------------------------------------------------------
-constexpr int RS_NT = 256;
+constexpr int RS_NT = 512;
 constexpr int RS_ITEMS = 8;
 constexpr int RS_TILE = RS_NT * RS_ITEMS;
 constexpr int RS_NW = RS_NT / WAVE;
+constexpr int RS_MAXP = 12;    // passes: 96 bits
+constexpr int RH_COPIES = 2;   // histogram copies per block (lanes spread over them)
+constexpr uint32_t RS_GROUP = 32;  // tiles per group of the look-back
+constexpr int RS_LOOK = 8;     // tiles looked back at per round
+constexpr int RS_GLOOK = 4;    // groups looked back at per round
 
-// Key columns packed into one word: column c at bit shift[c].
+// Key columns packed into one key: column c at bit shift[c] of 64, or of 96
+// (wide: the low 32 bits in a word of their own).
 struct PackArgs {
   const uint32_t* col[LH_MAX_KEYS];
   uint32_t shift[LH_MAX_KEYS];
   uint32_t ncols;
 };
 
-// One word unpacked into key columns: bits[c] bits at shift[c].
+// One key unpacked into key columns: bits[c] bits at shift[c].
 struct UnpackCols {
   uint32_t* col[LH_MAX_KEYS];
   uint32_t shift[LH_MAX_KEYS];
@@ -250,173 +269,432 @@ struct UnpackCols {
   uint32_t ncols;
 };
 
-__device__ __forceinline__ uint64_t pack_row(const PackArgs& a, uint64_t r) {
+template <bool WIDE>
+__device__ __forceinline__ uint64_t pack_row(const PackArgs& a, uint64_t r, uint32_t& x) {
   uint64_t k = 0;
+  x = 0;
 #pragma unroll
   for (uint32_t c = 0; c < LH_MAX_KEYS; c++)
-    if (c < a.ncols) k |= (uint64_t)a.col[c][r] << a.shift[c];
+    if (c < a.ncols) {
+      const uint64_t v = a.col[c][r];
+      const uint32_t sh = a.shift[c];
+      if constexpr (!WIDE) {
+        k |= v << sh;
+      } else if (sh >= 32) {
+        k |= v << (sh - 32);
+      } else {
+        x |= (uint32_t)(v << sh);
+        k |= v >> (32 - sh);
+      }
+    }
   return k;
 }
 
-__device__ __forceinline__ void unpack_row(const UnpackCols& a, uint64_t r, uint64_t k) {
+template <bool WIDE>
+__device__ __forceinline__ void unpack_row(const UnpackCols& a, uint64_t r, uint64_t k, uint32_t x) {
 #pragma unroll
   for (uint32_t c = 0; c < LH_MAX_KEYS; c++)
-    if (c < a.ncols) a.col[c][r] = a.bits[c] ? (uint32_t)((k >> a.shift[c]) & ((1ull << a.bits[c]) - 1)) : 0u;
+    if (c < a.ncols) {
+      const uint32_t sh = a.shift[c];
+      uint64_t v;
+      if constexpr (!WIDE) v = k >> sh;
+      else v = sh >= 32 ? k >> (sh - 32) : (((uint64_t)(uint32_t)k << 32) | x) >> sh;
+      // (a column of no bits has shift up to the key's width: its value is 0)
+      a.col[c][r] = a.bits[c] ? (uint32_t)(v & ((1ull << a.bits[c]) - 1)) : 0u;
+    }
 }
 
-// FROM_COLS: the keys are packed from the columns of `pa` (else read from
-// `keys`).
-template <bool FROM_COLS>
-__global__ __launch_bounds__(RS_NT) void k_rs_hist(const uint64_t* keys, PackArgs pa, uint64_t n, uint32_t shift,
-                                                   uint32_t* hist, uint32_t ntiles) {
-  __shared__ uint32_t h[256];
-  h[threadIdx.x] = 0;
+// Eight bits of a key at a wave-uniform shift: one funnel shift of the two
+// words that can hold them (a 64-bit shift by a register is several times
+// dearer, and a pass takes each element's digit three times).
+template <bool WIDE>
+__device__ __forceinline__ uint32_t digit_at(uint64_t k, uint32_t x, uint32_t shift) {
+  const uint32_t k0 = (uint32_t)k, k1 = (uint32_t)(k >> 32);
+  uint32_t lo, hi;
+  if constexpr (WIDE) {
+    lo = shift < 32 ? x : shift < 64 ? k0 : k1;
+    hi = shift < 32 ? k0 : shift < 64 ? k1 : 0u;
+  } else {
+    lo = shift < 32 ? k0 : k1;
+    hi = shift < 32 ? k1 : 0u;
+  }
+  return __builtin_amdgcn_alignbit(hi, lo, shift & 31u) & 255u;
+}
+
+// Digit counts of every pass, in one read of the keys: hist[p * 256 + d],
+// cleared before.  Lanes spread over copies of the LDS counters, and a wave
+// whose lanes all hold one digit (hub vertices, high digits) adds once.
+template <bool FROM_COLS, bool WIDE>
+__global__ __launch_bounds__(RS_NT) void k_rs_hist(const uint64_t* keys, const uint32_t* xkeys, PackArgs pa, uint64_t n,
+                                                   uint32_t lo_bit, uint32_t passes, uint32_t* hist) {
+  __shared__ uint32_t h[RS_MAXP * 256 * RH_COPIES];
+  const uint32_t nh = passes * 256 * RH_COPIES;
+  for (uint32_t i = threadIdx.x; i < nh; i += RS_NT) h[i] = 0;
   __syncthreads();
-  uint64_t base = (uint64_t)blockIdx.x * RS_TILE;
-  if (!FROM_COLS && !((uintptr_t)keys & 15u)) {
-    // packed keys, two per 16-byte load (the order of a histogram's keys
-    // does not matter)
-    const uint64_t ntile = min<uint64_t>(RS_TILE, n - base);
-    const ulonglong2* k2 = reinterpret_cast<const ulonglong2*>(keys + base);
+  const uint32_t copy = lane_id() & (RH_COPIES - 1);
+  const uint64_t stride = (uint64_t)gridDim.x * RS_NT * 4;
+  for (uint64_t i0 = (uint64_t)blockIdx.x * RS_NT * 4 + threadIdx.x; i0 - threadIdx.x < n; i0 += stride) {
+    uint64_t k[4];
+    uint32_t x[4];
 #pragma unroll
-    for (int i = 0; i < RS_ITEMS / 2; i++) {
-      const uint64_t j = (uint64_t)i * RS_NT + threadIdx.x;  // pair index in the tile
-      if (2 * j + 1 < ntile) {
-        const ulonglong2 v = k2[j];
-        atomicAdd(&h[(uint32_t)(v.x >> shift) & 255u], 1u);
-        atomicAdd(&h[(uint32_t)(v.y >> shift) & 255u], 1u);
-      } else if (2 * j < ntile) {
-        atomicAdd(&h[(uint32_t)(keys[base + 2 * j] >> shift) & 255u], 1u);
+    for (int j = 0; j < 4; j++) {
+      const uint64_t i = i0 + (uint64_t)j * RS_NT;
+      k[j] = 0;
+      x[j] = 0;
+      if (i < n) {
+        if constexpr (FROM_COLS) k[j] = pack_row<WIDE>(pa, i, x[j]);
+        else {
+          k[j] = keys[i];
+          if constexpr (WIDE) x[j] = xkeys[i];
+        }
       }
     }
-  } else {
 #pragma unroll
-    for (int i = 0; i < RS_ITEMS; i++) {
-      uint64_t idx = base + (uint64_t)i * RS_NT + threadIdx.x;
-      if (idx < n) {
-        const uint64_t k = FROM_COLS ? pack_row(pa, idx) : keys[idx];
-        atomicAdd(&h[(uint32_t)(k >> shift) & 255u], 1u);
+    for (int j = 0; j < 4; j++) {
+      const bool in = i0 + (uint64_t)j * RS_NT < n;
+      const uint64_t live = ballot(in);
+      if (!live) continue;
+#pragma unroll
+      for (uint32_t p = 0; p < (WIDE ? 12u : 8u); p++) {
+        if (p >= passes) break;
+        const uint32_t d = digit_at<WIDE>(k[j], x[j], lo_bit + 8 * p);
+        const uint32_t d0 = __builtin_amdgcn_readfirstlane(d);
+        if (ballot(in && d != d0) == 0) {  // (lane 0 is in whenever any lane is)
+          if (lane_id() == 0) atomicAdd(&h[(p * 256 + d0) * RH_COPIES], (uint32_t)__popcll(live));
+        } else if (in) {
+          atomicAdd(&h[(p * 256 + d) * RH_COPIES + copy], 1u);
+        }
       }
     }
   }
   __syncthreads();
-  hist[(uint64_t)threadIdx.x * ntiles + blockIdx.x] = h[threadIdx.x];
+  for (uint32_t i = threadIdx.x; i < passes * 256; i += RS_NT) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int j = 0; j < RH_COPIES; j++) c += h[i * RH_COPIES + j];
+    if (c) atomicAdd(&hist[i], c);
+  }
 }
 
-// Stable scatter of one tile.  Wave w holds the tile's elements
-// [w * RS_ITEMS * 64, (w + 1) * RS_ITEMS * 64), item i of lane l at offset
-// i * 64 + l, so a wave's items in order are the input order.  A wave ranks
-// its items one after another against digit counters of its own (eight
-// ballots find a lane's equal-digit peers; no barrier between items, the
-// wave's LDS operations run in order), then one prefix over the waves per
-// digit places every element in LDS in digit order, and the tile is written
-// out in that order, so each digit's run of the tile goes to consecutive
-// global slots (coalesced writes).
-// HAS_V: a 32-bit value travels with each key (else keys only); a null
-// `vin` gives every element its input position as value.
-// FROM_COLS: keys packed from the columns of `pa` (else read from `kin`).
-// TO_COLS: sorted keys unpacked into the columns of `ua` (else to `kout`).
-template <bool HAS_V, bool FROM_COLS, bool TO_COLS>
-__global__ __launch_bounds__(RS_NT) void k_rs_scatter(const uint64_t* kin, PackArgs pa, const uint32_t* vin,
-                                                      uint64_t* kout, UnpackCols ua, uint32_t* vout, uint64_t n,
-                                                      uint32_t shift, const uint32_t* offs, const uint32_t* hist,
-                                                      uint32_t ntiles) {
-  __shared__ uint64_t sk[RS_TILE];
-  __shared__ uint32_t sv[HAS_V ? RS_TILE : 1];
-  __shared__ uint32_t lstart[256];       // first slot of each digit in the tile
-  __shared__ uint32_t wcnt[RS_NW][256];  // each wave's digit counts, then its first slot per digit
+struct RsArgs {
+  PackArgs pa;             // first pass of a sort of columns
+  UnpackCols ua;           // its last
+  const uint64_t* kin;
+  const uint32_t* xin;     // wide: the keys' low words
+  const void* vin;         // null: every element's value is its input position
+  uint64_t* kout;
+  uint32_t* xout;
+  void* vout;
+  uint64_t n;
+  uint32_t shift;          // of the pass's digit
+  uint32_t tag;            // of the pass, in the status words (from 1)
+  uint32_t passes;         // one tile: passes run here
+  const uint32_t* hist;    // digit counts of the pass
+  uint32_t* status;        // per tile and digit: tag << 16 | the tile's count
+  uint64_t* gsum;          // per group and digit, of this pass: tiles added so far << 40 | their count
+  uint64_t* gpref;         // per group and digit: tag << 34 | count of all tiles before the group
+  uint32_t* ticket;        // tiles handed out so far
+};
+
+// One pass over one tile (ONE: every pass of a sort of a single tile).
+// Wave w holds the tile's elements [w * RS_ITEMS * 64, (w + 1) * RS_ITEMS *
+// 64), item i of lane l at offset i * 64 + l, so a wave's items in order are
+// the input order.  A wave ranks its items one after another against digit
+// counters of its own (eight ballots find a lane's equal-digit peers; no
+// barrier between items, the wave's LDS operations run in order), one prefix
+// over the waves per digit places every element in LDS in digit order, and
+// the tile is written out in that order, each digit's run to consecutive
+// slots.  The key, its low word and its value go through the same LDS one
+// after another.
+// Look-back: a tile publishes its digit counts and adds them to its group's;
+// it adds up the tiles before it in its group, and the group's first tile
+// adds up the groups before (until one whose own prefix is known) and
+// publishes that for the others.  Walking back tile by tile instead cost as
+// much as the rest of the pass: the reads of other XCDs' words, not their
+// latency, were the limit (twice the words per round made it slower).
+// Tiles are handed out by a ticket, so all that a tile waits for comes from
+// tiles that have started, and each publishes its counts before it waits
+// itself: every wait ends.  A word holds a count and the pass (or the number
+// of tiles) that makes it valid, and is written and read whole, so no other
+// memory has to be ordered with it.
+template <int VB, bool FROM_COLS, bool TO_COLS, bool WIDE, bool ONE>
+__global__ __launch_bounds__(RS_NT, WIDE || ONE ? 4 : 8) void k_rs_pass(RsArgs a) {
+  __shared__ __align__(16) unsigned char s_raw[RS_TILE * 8];
+  __shared__ uint32_t s_lstart[256];  // first slot of each digit in the tile
+  __shared__ uint32_t s_gbase[256];   // global slot of tile slot 0, per digit (modulo 2^32)
   __shared__ uint32_t s_red[RS_NW];
+  __shared__ uint32_t s_tile;
+  uint64_t* sk = reinterpret_cast<uint64_t*>(s_raw);
+  uint32_t* s32 = reinterpret_cast<uint32_t*>(s_raw);
+  uint32_t (*wcnt)[256] = reinterpret_cast<uint32_t(*)[256]>(s_raw);  // per wave, before the keys are staged
   const int tid = threadIdx.x, w = tid / WAVE, lane = tid & (WAVE - 1);
-  const uint64_t base = (uint64_t)blockIdx.x * RS_TILE;
-  const uint32_t ntile = (uint32_t)min<uint64_t>(RS_TILE, n - base);
+  uint32_t tile = 0;
+  if constexpr (!ONE) {
+    if (tid == 0) s_tile = atomicAdd(a.ticket, 1u);
+    __syncthreads();
+    tile = s_tile;
+  }
+  const uint64_t base = (uint64_t)tile * RS_TILE;
+  const uint32_t ntile = (uint32_t)min<uint64_t>(RS_TILE, a.n - base);
   const uint32_t wbase = (uint32_t)w * RS_ITEMS * WAVE;
-  // all of the wave's loads are issued first
   uint64_t kk[RS_ITEMS];
-  uint32_t vv[RS_ITEMS];
+  uint32_t xx[WIDE ? RS_ITEMS : 1];
+  uint32_t vv[VB == 4 ? RS_ITEMS : 1];
+  uint64_t vd[VB == 8 ? RS_ITEMS : 1];
 #pragma unroll
   for (int i = 0; i < RS_ITEMS; i++) {
     const uint32_t li = wbase + (uint32_t)i * WAVE + lane;
-    if constexpr (FROM_COLS) kk[i] = li < ntile ? pack_row(pa, base + li) : 0;
-    else kk[i] = li < ntile ? kin[base + li] : 0;
-    vv[i] = 0;
-    if constexpr (HAS_V) vv[i] = li < ntile ? (vin ? vin[base + li] : (uint32_t)(base + li)) : 0u;
+    kk[i] = 0;
+    uint32_t x = 0;
+    if (li < ntile) {
+      if constexpr (FROM_COLS) kk[i] = pack_row<WIDE>(a.pa, base + li, x);
+      else {
+        kk[i] = a.kin[base + li];
+        if constexpr (WIDE) x = a.xin[base + li];
+      }
+    }
+    if constexpr (WIDE) xx[i] = x;
   }
-  {
-    const uint32_t c = hist[(uint64_t)tid * ntiles + blockIdx.x];
+  auto load_values = [&]() {
+#pragma unroll
+    for (int i = 0; i < RS_ITEMS; i++) {
+      const uint32_t li = wbase + (uint32_t)i * WAVE + lane;
+      if constexpr (VB == 4) {
+        vv[i] = (uint32_t)(base + li);
+        if (a.vin && li < ntile) vv[i] = static_cast<const uint32_t*>(a.vin)[base + li];
+      } else if constexpr (VB == 8) {
+        vd[i] = li < ntile ? static_cast<const uint64_t*>(a.vin)[base + li] : 0ull;
+      }
+    }
+  };
+  if constexpr (ONE) load_values();
+  uint32_t lp[RS_ITEMS], pos[RS_ITEMS];
+  for (uint32_t pass = 0; pass < (ONE ? a.passes : 1u); pass++) {
+    const uint32_t shift = a.shift + 8 * pass;
+#pragma unroll
+    for (int j = 0; j < RS_NW; j++)
+      if (tid < 256) wcnt[j][tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < RS_ITEMS; i++) {
+      const bool valid = wbase + (uint32_t)i * WAVE + lane < ntile;
+      const uint32_t d = digit_at<WIDE>(kk[i], WIDE ? xx[WIDE ? i : 0] : 0u, shift);
+      // lanes of the same digit: those whose bit b agrees, for all b
+      const uint64_t live = ballot(valid);
+      uint32_t plo = (uint32_t)live, phi = (uint32_t)(live >> 32);
+#pragma unroll
+      for (int b = 0; b < 8; b++) {
+        const uint32_t bit = (uint32_t)((int32_t)(d << (31 - b)) >> 31);  // all ones or zero
+        const uint64_t m = ballot(bit != 0);
+        plo &= ~((uint32_t)m ^ bit);
+        phi &= ~((uint32_t)(m >> 32) ^ bit);
+      }
+      const uint64_t peers = ((uint64_t)phi << 32) | plo;
+      const uint32_t below = lanes_below(peers);
+      const uint32_t pre = valid ? wcnt[w][d] : 0u;
+      lp[i] = pre + below;
+      // the lowest peer moves the wave's count on, after every peer has read it
+      if (valid && below == 0) wcnt[w][d] = pre + (uint32_t)__popcll(peers);
+    }
+    __syncthreads();
+    uint32_t c = 0;
+    if (tid < 256) {
+#pragma unroll
+      for (int j = 0; j < RS_NW; j++) c += wcnt[j][tid];
+      if constexpr (!ONE) {
+        __hip_atomic_store(&a.status[(uint64_t)tile * 256 + tid], (a.tag << 16) | c, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        (void)__hip_atomic_fetch_add(&a.gsum[(uint64_t)(tile / RS_GROUP) * 256 + tid], (1ull << 40) | c,
+                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
     uint32_t tot;
-    lstart[tid] = block_excl_scan<uint32_t, RS_NT>(c, s_red, tot);
-  }
+    const uint32_t lstart = block_excl_scan<uint32_t, RS_NT>(c, s_red, tot);
+    uint32_t gstart = 0;  // first slot of digit tid in the output
+    if constexpr (!ONE) gstart = block_excl_scan<uint32_t, RS_NT>(tid < 256 ? a.hist[tid] : 0u, s_red, tot);
+    if (tid < 256) {
+      s_lstart[tid] = lstart;
+      uint32_t slot = lstart;
 #pragma unroll
-  for (int j = 0; j < RS_NW; j++) wcnt[j][tid] = 0;
-  __syncthreads();
-  uint32_t rank[RS_ITEMS];
-#pragma unroll
-  for (int i = 0; i < RS_ITEMS; i++) {
-    const bool valid = wbase + (uint32_t)i * WAVE + lane < ntile;
-    const uint32_t d = (uint32_t)(kk[i] >> shift) & 255u;
-    uint64_t peers = ballot(valid);
-#pragma unroll
-    for (int b = 0; b < 8; b++) {
-      const bool bit = (d >> b) & 1u;
-      const uint64_t m = ballot(valid && bit);
-      peers &= bit ? m : ~m;
+      for (int j = 0; j < RS_NW; j++) {
+        const uint32_t t = wcnt[j][tid];
+        wcnt[j][tid] = slot;
+        slot += t;
+      }
     }
-    const uint32_t below = lanes_below(peers);
-    const uint32_t pre = valid ? wcnt[w][d] : 0u;
-    rank[i] = pre + below;
-    // the lowest peer moves the wave's count on, after every peer has read it
-    if (valid && below == 0) wcnt[w][d] = pre + (uint32_t)__popcll(peers);
-  }
-  __syncthreads();
-  {
-    // digit tid: the first slot of each wave's run of it
-    uint32_t slot = lstart[tid];
+    __syncthreads();
 #pragma unroll
-    for (int j = 0; j < RS_NW; j++) {
-      const uint32_t c = wcnt[j][tid];
-      wcnt[j][tid] = slot;
-      slot += c;
-    }
-  }
-  __syncthreads();
+    for (int i = 0; i < RS_ITEMS; i++)
+      lp[i] += wcnt[w][digit_at<WIDE>(kk[i], WIDE ? xx[WIDE ? i : 0] : 0u, shift)];
+    __syncthreads();
 #pragma unroll
-  for (int i = 0; i < RS_ITEMS; i++) {
-    if (wbase + (uint32_t)i * WAVE + lane < ntile) {
-      const uint32_t lp = wcnt[w][(uint32_t)(kk[i] >> shift) & 255u] + rank[i];
-      sk[lp] = kk[i];
-      if constexpr (HAS_V) sv[lp] = vv[i];
+    for (int i = 0; i < RS_ITEMS; i++)
+      if (wbase + (uint32_t)i * WAVE + lane < ntile) sk[lp[i]] = kk[i];
+    if constexpr (!ONE) {
+      load_values();
+      if (tid < 256) {
+        const uint32_t g = tile / RS_GROUP;
+        uint32_t before = 0;  // elements of the digit in the tiles before
+        if (tile % RS_GROUP == 0) {
+          for (int64_t j = (int64_t)g - 1; j >= 0;) {
+            uint64_t gs[RS_GLOOK], gp[RS_GLOOK];
+#pragma unroll
+            for (int q = 0; q < RS_GLOOK; q++) {
+              const uint64_t at = (uint64_t)max<int64_t>(0, j - q) * 256 + tid;
+              gs[q] = __hip_atomic_load(&a.gsum[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              gp[q] = __hip_atomic_load(&a.gpref[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            bool wait = false;
+#pragma unroll
+            for (int q = 0; q < RS_GLOOK; q++) {
+              if (wait || j < 0) continue;
+              if ((gs[q] >> 40) != RS_GROUP) {
+                wait = true;
+                continue;
+              }
+              before += (uint32_t)gs[q];
+              if ((gp[q] >> 34) == a.tag) {
+                before += (uint32_t)gp[q];
+                j = -1;
+              } else {
+                j--;
+              }
+            }
+            if (wait) __builtin_amdgcn_s_sleep(1);
+          }
+          __hip_atomic_store(&a.gpref[(uint64_t)g * 256 + tid], ((uint64_t)a.tag << 34) | before, __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+          for (uint32_t t = g * RS_GROUP; t < tile;) {
+            uint32_t st[RS_LOOK];
+#pragma unroll
+            for (int j = 0; j < RS_LOOK; j++)
+              st[j] = __hip_atomic_load(&a.status[(uint64_t)min(t + j, tile) * 256 + tid], __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT);
+            bool wait = false;
+#pragma unroll
+            for (int j = 0; j < RS_LOOK; j++) {
+              if (wait || t >= tile) continue;
+              if ((st[j] >> 16) != a.tag) {
+                wait = true;
+              } else {
+                before += st[j] & 0xffffu;
+                t++;
+              }
+            }
+            if (wait) __builtin_amdgcn_s_sleep(1);
+          }
+          for (;;) {
+            const uint64_t gp = __hip_atomic_load(&a.gpref[(uint64_t)g * 256 + tid], __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT);
+            if ((gp >> 34) == a.tag) {
+              before += (uint32_t)gp;
+              break;
+            }
+            __builtin_amdgcn_s_sleep(2);
+          }
+        }
+        s_gbase[tid] = gstart + before - lstart;
+      }
     }
+    __syncthreads();
+    // slot t of the tile: its key, and where it goes
+#pragma unroll
+    for (int i = 0; i < RS_ITEMS; i++) {
+      const uint32_t t = (uint32_t)i * RS_NT + tid;
+      pos[i] = t;
+      if constexpr (ONE) {
+        // back into the wave's items for the next pass
+        const uint32_t li = wbase + (uint32_t)i * WAVE + lane;
+        kk[i] = li < ntile ? sk[li] : 0ull;
+        pos[i] = li;
+      } else if constexpr (!WIDE) {
+        if (t < ntile) {
+          const uint64_t k = sk[t];
+          pos[i] = s_gbase[digit_at<false>(k, 0u, shift)] + t;
+          if constexpr (TO_COLS) unpack_row<false>(a.ua, pos[i], k, 0u);
+          else a.kout[pos[i]] = k;
+        }
+      } else {
+        kk[i] = t < ntile ? sk[t] : 0ull;
+      }
+    }
+    if constexpr (WIDE) {
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < RS_ITEMS; i++)
+        if (wbase + (uint32_t)i * WAVE + lane < ntile) s32[lp[i]] = xx[i];
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < RS_ITEMS; i++) {
+        const uint32_t t = pos[i];
+        const uint32_t x = t < ntile ? s32[t] : 0u;
+        if constexpr (ONE) xx[i] = x;
+        else if (t < ntile) {
+          pos[i] = s_gbase[digit_at<true>(kk[i], x, shift)] + t;
+          if constexpr (TO_COLS) unpack_row<true>(a.ua, pos[i], kk[i], x);
+          else {
+            a.kout[pos[i]] = kk[i];
+            a.xout[pos[i]] = x;
+          }
+        }
+      }
+    }
+    if constexpr (VB == 4) {
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < RS_ITEMS; i++)
+        if (wbase + (uint32_t)i * WAVE + lane < ntile) s32[lp[i]] = vv[i];
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < RS_ITEMS; i++) {
+        const uint32_t t = ONE ? pos[i] : (uint32_t)i * RS_NT + tid;
+        if constexpr (ONE) vv[i] = t < ntile ? s32[t] : 0u;
+        else if (t < ntile) static_cast<uint32_t*>(a.vout)[pos[i]] = s32[t];
+      }
+    } else if constexpr (VB == 8) {
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < RS_ITEMS; i++)
+        if (wbase + (uint32_t)i * WAVE + lane < ntile) sk[lp[i]] = vd[i];
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < RS_ITEMS; i++) {
+        const uint32_t t = ONE ? pos[i] : (uint32_t)i * RS_NT + tid;
+        if constexpr (ONE) vd[i] = t < ntile ? sk[t] : 0ull;
+        else if (t < ntile) static_cast<uint64_t*>(a.vout)[pos[i]] = sk[t];
+      }
+    }
+    if constexpr (ONE) __syncthreads();
   }
-  __syncthreads();
-  for (uint32_t t = tid; t < ntile; t += RS_NT) {
-    const uint64_t k = sk[t];
-    const uint32_t d = (uint32_t)(k >> shift) & 255u;
-    const uint32_t pos = offs[(uint64_t)d * ntiles + blockIdx.x] + (t - lstart[d]);
-    if constexpr (TO_COLS) unpack_row(ua, pos, k);
-    else kout[pos] = k;
-    if constexpr (HAS_V) vout[pos] = sv[t];
+  if constexpr (ONE) {
+#pragma unroll
+    for (int i = 0; i < RS_ITEMS; i++) {
+      const uint32_t li = wbase + (uint32_t)i * WAVE + lane;
+      if (li >= ntile) continue;
+      if constexpr (TO_COLS) unpack_row<WIDE>(a.ua, li, kk[i], WIDE ? xx[WIDE ? i : 0] : 0u);
+      else a.kout[li] = kk[i];
+      if constexpr (VB == 4) static_cast<uint32_t*>(a.vout)[li] = vv[i];
+      if constexpr (VB == 8) static_cast<uint64_t*>(a.vout)[li] = vd[i];
+    }
   }
 }
 
-template <bool HAS_V>
-void launch_rs_scatter(bool from_cols, bool to_cols, unsigned grid, hipStream_t s, const uint64_t* kin,
-                       const PackArgs& pa, const uint32_t* vin, uint64_t* kout, const UnpackCols& ua, uint32_t* vout,
-                       uint64_t n, uint32_t shift, const uint32_t* offs, const uint32_t* hist, uint32_t ntiles) {
-  if (from_cols && to_cols)
-    k_rs_scatter<HAS_V, true, true><<<grid, RS_NT, 0, s>>>(kin, pa, vin, kout, ua, vout, n, shift, offs, hist, ntiles);
-  else if (from_cols)
-    k_rs_scatter<HAS_V, true, false><<<grid, RS_NT, 0, s>>>(kin, pa, vin, kout, ua, vout, n, shift, offs, hist, ntiles);
-  else if (to_cols)
-    k_rs_scatter<HAS_V, false, true><<<grid, RS_NT, 0, s>>>(kin, pa, vin, kout, ua, vout, n, shift, offs, hist, ntiles);
-  else
-    k_rs_scatter<HAS_V, false, false><<<grid, RS_NT, 0, s>>>(kin, pa, vin, kout, ua, vout, n, shift, offs, hist,
-                                                             ntiles);
+template <int VB, bool WIDE>
+void launch_rs_pass(bool from_cols, bool to_cols, unsigned grid, hipStream_t s, const RsArgs& a) {
+  if (from_cols && to_cols) k_rs_pass<VB, true, true, WIDE, false><<<grid, RS_NT, 0, s>>>(a);
+  else if (from_cols) k_rs_pass<VB, true, false, WIDE, false><<<grid, RS_NT, 0, s>>>(a);
+  else if (to_cols) k_rs_pass<VB, false, true, WIDE, false><<<grid, RS_NT, 0, s>>>(a);
+  else k_rs_pass<VB, false, false, WIDE, false><<<grid, RS_NT, 0, s>>>(a);
   LH_HIP(hipGetLastError());
 }
 
 __global__ void k_pack(PackArgs a, const uint32_t* perm, uint64_t* out, uint64_t n) {
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-    out[i] = pack_row(a, perm ? perm[i] : (uint32_t)i);
+{
+    uint32_t x;
+    out[i] = pack_row<false>(a, perm ? perm[i] : (uint32_t)i, x);
+  }
 }
 
 __device__ __forceinline__ int32_t lowest_bit_exp(double v) {
@@ -641,7 +919,7 @@ void column_freq(const uint32_t* col, uint64_t n, uint32_t range, uint64_t& dist
   const uint32_t bits = range ? 32 - __builtin_clz(range) : 0;
   DBuf<uint32_t> sorted(n, s);
   uint32_t* out = sorted.p;
-  if (!sort_packed(&col, &bits, 1, n, nullptr, &out, s)) fail(LH_ERR_DEVICE, "column statistics: sort failed");
+  if (!sort_packed(&col, &bits, 1, n, SortValue{}, &out, s)) fail(LH_ERR_DEVICE, "column statistics: sort failed");
   sorted_run_stats(sorted.p, n, distinct, freq_max, s);
 }
 
@@ -688,46 +966,102 @@ void gather_f64(const double* src, const uint32_t* idx, double* dst, uint64_t n,
 
 namespace {
 
-// The passes of one radix sort over bits [lo_bit, lo_bit + 8 * passes) of
-// the keys.  The first pass reads `pa`'s columns when from_cols (else
-// kin) and, when vals are wanted, `vin` (null: input positions).  Pass p
-// writes kbuf[(p + phase) & 1] and vbuf[(p + phase) & 1], except that
-// the last writes `ua`'s columns instead of keys when to_cols.
-void radix_passes(const uint64_t* kin, const PackArgs& pa, bool from_cols, const uint32_t* vin, bool vals,
-                  uint64_t* const kbuf[2], const UnpackCols& ua, bool to_cols, uint32_t* const vbuf[2],
-                  uint32_t phase, uint64_t n, uint32_t lo_bit, uint32_t passes, hipStream_t s) {
-  const uint32_t ntiles = (uint32_t)((n + RS_TILE - 1) / RS_TILE);
-  const uint64_t hn = (uint64_t)ntiles * 256;
-  DBuf<uint32_t> hist(hn, s), offs(hn + 1, s);
-  const uint64_t in_bytes = from_cols ? 4ull * pa.ncols : 8ull, out_bytes = to_cols ? 4ull * ua.ncols : 8ull;
-  const uint64_t* ki = kin;
-  const uint32_t* vi = vin;
+// One radix sort.  Passes cover bits [lo_bit, lo_bit + 8 * passes) of the
+// keys.  The first pass reads io.pa's columns when from_cols (else kin, xin)
+// and the last writes io.ua's columns when to_cols (else the keys).  Pass p
+// writes buffers (p + phase) & 1.  Values (vb bytes each, 0: none) start in
+// vin (null: the input positions, vb = 4).
+struct RadixIO {
+  PackArgs pa{};
+  UnpackCols ua{};
+  bool from_cols = false, to_cols = false, wide = false;
+  const uint64_t* kin = nullptr;
+  uint64_t* kbuf[2] = {nullptr, nullptr};
+  uint32_t* xbuf[2] = {nullptr, nullptr};
+  int vb = 0;
+  const void* vin = nullptr;
+  void* vbuf[2] = {nullptr, nullptr};
+  uint32_t phase = 0;
+};
+
+template <int VB, bool WIDE>
+void launch_one_tile(const RadixIO& io, const RsArgs& a, hipStream_t s) {
+  if (io.from_cols) k_rs_pass<VB, true, true, WIDE, true><<<1, RS_NT, 0, s>>>(a);
+  else k_rs_pass<VB, false, false, WIDE, true><<<1, RS_NT, 0, s>>>(a);
+  LH_HIP(hipGetLastError());
+}
+
+template <class F>
+void by_value_and_width(const RadixIO& io, F&& f) {
+  using std::integral_constant;
+  if (io.wide) {
+    if (io.vb == 0) f(integral_constant<int, 0>{}, std::true_type{});
+    else if (io.vb == 4) f(integral_constant<int, 4>{}, std::true_type{});
+    else f(integral_constant<int, 8>{}, std::true_type{});
+  } else {
+    if (io.vb == 0) f(integral_constant<int, 0>{}, std::false_type{});
+    else if (io.vb == 4) f(integral_constant<int, 4>{}, std::false_type{});
+    else f(integral_constant<int, 8>{}, std::false_type{});
+  }
+}
+
+void radix_passes(const RadixIO& io, uint64_t n, uint32_t lo_bit, uint32_t passes, hipStream_t s) {
+  RsArgs a{};
+  a.pa = io.pa;
+  a.ua = io.ua;
+  a.n = n;
+  a.kin = io.kin;
+  a.vin = io.vin;
+  const uint64_t ntiles = (n + RS_TILE - 1) / RS_TILE;
+  const uint64_t kb = io.wide ? 12 : 8;
+  const uint64_t in_bytes = io.from_cols ? 4ull * io.pa.ncols : kb, out_bytes = io.to_cols ? 4ull * io.ua.ncols : kb;
+  if (ntiles == 1 && io.from_cols == io.to_cols) {
+    // one tile: every pass in one launch, the last pass's buffers written
+    a.shift = lo_bit;
+    a.passes = passes;
+    a.kout = io.kbuf[(passes - 1 + io.phase) & 1];
+    a.vout = io.vbuf[(passes - 1 + io.phase) & 1];
+    ProfScope ps("sort_scatter", s, n, (in_bytes + out_bytes + (io.vb ? 2 * io.vb : 0)) * n);
+    by_value_and_width(io, [&](auto vb, auto wide) { launch_one_tile<vb.value, wide.value>(io, a, s); });
+    return;
+  }
+  // digit counts of all passes, the tickets and the look-back's words (the
+  // tiles' counts and the groups' prefixes are tagged by pass), cleared once
+  const uint64_t ngroups = (ntiles + RS_GROUP - 1) / RS_GROUP;
+  const uint64_t head = (uint64_t)RS_MAXP * 256 + RS_MAXP + 4;  // 32-bit words before the 64-bit ones (even)
+  DBuf<uint32_t> ws(head + ngroups * 512 * (passes + 1) + ntiles * 256, s);
+  LH_HIP(hipMemsetAsync(ws.p, 0, ws.n * sizeof(uint32_t), s));
+  {
+    // elements: the pass's algorithmic bytes (its keys read)
+    ProfScope ps("sort_hist", s, n, in_bytes * n);
+    const unsigned grid = (unsigned)std::min<uint64_t>(ntiles, 1024);
+    if (io.from_cols && io.wide) k_rs_hist<true, true><<<grid, RS_NT, 0, s>>>(nullptr, nullptr, io.pa, n, lo_bit, passes, ws.p);
+    else if (io.from_cols) k_rs_hist<true, false><<<grid, RS_NT, 0, s>>>(nullptr, nullptr, io.pa, n, lo_bit, passes, ws.p);
+    else k_rs_hist<false, false><<<grid, RS_NT, 0, s>>>(io.kin, nullptr, io.pa, n, lo_bit, passes, ws.p);
+  }
+  LH_HIP(hipGetLastError());
+  a.gpref = reinterpret_cast<uint64_t*>(ws.p + head);
+  a.status = ws.p + head + ngroups * 512 * (passes + 1);
   for (uint32_t p = 0; p < passes; p++) {
-    const uint32_t shift = lo_bit + p * 8;
-    const bool first = p == 0, last = p + 1 == passes;
-    const bool fc = first && from_cols, tc = last && to_cols;
-    {
-      // elements: the pass's algorithmic bytes (its keys read)
-      ProfScope ps("sort_hist", s, n, (fc ? in_bytes : 8) * n);
-      if (fc) k_rs_hist<true><<<ntiles, RS_NT, 0, s>>>(nullptr, pa, n, shift, hist.p, ntiles);
-      else k_rs_hist<false><<<ntiles, RS_NT, 0, s>>>(ki, pa, n, shift, hist.p, ntiles);
-    }
-    LH_HIP(hipGetLastError());
-    scan_u32_dev(hist.p, offs.p, hn, s);
-    uint64_t* ko = tc ? nullptr : kbuf[(p + phase) & 1];
-    uint32_t* vo = vals ? vbuf[(p + phase) & 1] : nullptr;
-    {
-      // elements: the pass's algorithmic bytes (keys, and values when they
-      // travel, read once and written once; values made from positions
-      // are written only)
-      const uint64_t vb = vals ? (vi ? 8 : 4) : 0;
-      ProfScope ps("sort_scatter", s, n, ((fc ? in_bytes : 8) + (tc ? out_bytes : 8) + vb) * n);
-      if (vals) launch_rs_scatter<true>(fc, tc, ntiles, s, ki, pa, vi, ko, ua, vo, n, shift, offs.p, hist.p, ntiles);
-      else launch_rs_scatter<false>(fc, tc, ntiles, s, ki, pa, nullptr, ko, ua, nullptr, n, shift, offs.p, hist.p,
-                                    ntiles);
-    }
-    ki = ko;
-    vi = vo;
+    const bool fc = p == 0 && io.from_cols, tc = p + 1 == passes && io.to_cols;
+    const uint32_t to = (p + io.phase) & 1;
+    a.shift = lo_bit + p * 8;
+    a.tag = p + 1;
+    a.hist = ws.p + p * 256;
+    a.ticket = ws.p + RS_MAXP * 256 + p;
+    a.gsum = a.gpref + ngroups * 256 * (p + 1);
+    a.kout = io.kbuf[to];
+    a.xout = io.xbuf[to];
+    a.vout = io.vbuf[to];
+    // elements: the pass's algorithmic bytes (keys, and values when they
+    // travel, read once and written once; values made from positions are
+    // written only)
+    const uint64_t vbytes = io.vb ? (a.vin ? 2 : 1) * io.vb : 0;
+    ProfScope ps("sort_scatter", s, n, ((fc ? in_bytes : kb) + (tc ? out_bytes : kb) + vbytes) * n);
+    by_value_and_width(io, [&](auto vb, auto wide) { launch_rs_pass<vb.value, wide.value>(fc, tc, (unsigned)ntiles, s, a); });
+    a.kin = a.kout;
+    a.xin = a.xout;
+    a.vin = a.vout;
   }
 }
 
@@ -741,10 +1075,16 @@ void radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* tkeys, uint32_t*
   const uint32_t passes = (bits - lo_bit + 7) / 8;
   // pass p writes buffer (p + 1) & 1: the first writes the temporaries,
   // the last the caller's buffers when the count is even
-  uint64_t* const kbuf[2] = {keys, tkeys};
-  uint32_t* const vbuf[2] = {vals, tvals};
-  radix_passes(keys, PackArgs{}, false, vals, vals != nullptr, kbuf, UnpackCols{}, false, vbuf, 1, n, lo_bit, passes,
-               s);
+  RadixIO io;
+  io.kin = keys;
+  io.kbuf[0] = keys;
+  io.kbuf[1] = tkeys;
+  io.vb = vals ? 4 : 0;
+  io.vin = vals;
+  io.vbuf[0] = vals;
+  io.vbuf[1] = tvals;
+  io.phase = 1;
+  radix_passes(io, n, lo_bit, passes, s);
   if (passes & 1) {
     LH_HIP(hipMemcpyAsync(keys, tkeys, n * sizeof(uint64_t), hipMemcpyDeviceToDevice, s));
     if (vals) LH_HIP(hipMemcpyAsync(vals, tvals, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
@@ -782,22 +1122,23 @@ void lex_sort_perm(const uint32_t* const* cols, const uint32_t* bits, uint32_t n
   }
 }
 
-bool sort_packed(const uint32_t* const* cols, const uint32_t* bits, uint32_t ncols, uint64_t n, uint32_t* perm,
+bool sort_packed(const uint32_t* const* cols, const uint32_t* bits, uint32_t ncols, uint64_t n, const SortValue& val,
                  uint32_t* const* sorted, hipStream_t s, uint32_t sorted_tail) {
   uint32_t tot = 0;
   for (uint32_t c = 0; c < ncols; c++) tot += bits[c];
-  if (tot > 64 || ncols > LH_MAX_KEYS) return false;
+  if (tot > 96 || ncols > LH_MAX_KEYS) return false;
   if (!n) return true;
   if (n >= (1ull << 32)) fail(LH_ERR_OVERFLOW, "radix sort: more than 2^32 - 1 keys");
-  PackArgs a{};
-  UnpackCols u{};
-  a.ncols = u.ncols = ncols;
+  RadixIO io;
+  io.wide = tot > 64;
+  io.pa.ncols = io.ua.ncols = ncols;
   uint32_t sh = 0;
   for (int c = (int)ncols - 1; c >= 0; c--) {  // the last column lowest
-    a.col[c] = cols[c];
-    a.shift[c] = u.shift[c] = sh;
-    u.bits[c] = bits[c];
-    u.col[c] = sorted[c];
+    io.pa.col[c] = cols[c];
+    // (a leading column of no bits holds zeros: any shift below the width)
+    io.pa.shift[c] = io.ua.shift[c] = bits[c] ? sh : 0;
+    io.ua.bits[c] = bits[c];
+    io.ua.col[c] = sorted[c];
     sh += bits[c];
   }
   uint32_t tail_bits = 0;
@@ -808,20 +1149,28 @@ bool sort_packed(const uint32_t* const* cols, const uint32_t* bits, uint32_t nco
     // columns are copies
     for (uint32_t c = 0; c < ncols; c++)
       LH_HIP(hipMemcpyAsync(sorted[c], cols[c], n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
-    if (perm) iota_u32(perm, n, s);
+    if (val.bytes && val.in) LH_HIP(hipMemcpyAsync(val.out, val.in, n * val.bytes, hipMemcpyDeviceToDevice, s));
+    else if (val.bytes) iota_u32(static_cast<uint32_t*>(val.out), n, s);
     return true;
   }
   // the first pass packs the columns, the last unpacks into `sorted`; the
-  // permutation starts as the input positions and ends in perm
+  // values end in val.out
   DBuf<uint64_t> k(passes > 1 ? n : 0, s), tk(passes > 2 ? n : 0, s);
-  DBuf<uint32_t> tv(perm && passes > 1 ? n : 0, s);
-  uint64_t* const kbuf[2] = {k.p, tk.p};
-  uint32_t* const vbuf[2] = {perm, tv.p};
-  // pass p writes buffer (p + phase) & 1: the last writes vbuf[0] = perm,
-  // the first writes kbuf[0] = k
-  const uint32_t phase = (passes - 1) & 1;
-  uint64_t* const kb[2] = {kbuf[phase], kbuf[phase ^ 1]};
-  radix_passes(nullptr, a, true, nullptr, perm != nullptr, kb, u, true, vbuf, phase, n, tail_bits, passes, s);
+  DBuf<uint32_t> x(passes > 1 && io.wide ? n : 0, s), tx(passes > 2 && io.wide ? n : 0, s);
+  DBuf<uint64_t> tv(val.bytes && passes > 1 ? (n * val.bytes + 7) / 8 : 0, s);
+  // pass p writes buffer (p + phase) & 1: the last writes vbuf[0] =
+  // val.out, the first writes k
+  io.phase = (passes - 1) & 1;
+  io.from_cols = io.to_cols = true;
+  io.kbuf[io.phase] = k.p;
+  io.kbuf[io.phase ^ 1] = tk.p;
+  io.xbuf[io.phase] = x.p;
+  io.xbuf[io.phase ^ 1] = tx.p;
+  io.vb = (int)val.bytes;
+  io.vin = val.in;
+  io.vbuf[0] = val.out;
+  io.vbuf[1] = tv.p;
+  radix_passes(io, n, tail_bits, passes, s);
   return true;
 }
 
