@@ -198,8 +198,10 @@ __device__ __forceinline__ void atomic_add_digit(int64_t* slots, uint32_t q, uin
 // Add a normalized register accumulator (or any slots whose lower values
 // are non-negative) to a shared-form accumulator.
 __device__ __forceinline__ void atomic_add_acc(int64_t* slots, const RegAcc& t, uint32_t D) {
-  for (uint32_t q = 0; q < D; q++)
-    if (t.s[q]) atomic_add_digit(slots, q, D, t.s[q]);
+  // constant slot indices keep the accumulator in registers
+#pragma unroll
+  for (int q = 0; q < EXACT_MAXD; q++)
+    if (q < (int)D && t.s[q]) atomic_add_digit(slots, (uint32_t)q, D, t.s[q]);
 }
 
 // Add mult * v straight into a shared-form accumulator: at most five

@@ -27,7 +27,17 @@ namespace {
 constexpr int J_NT = 256;          // 4 waves per block, one work unit per wave
 constexpr int J_NW = J_NT / WAVE;
 constexpr int U_IT = 4;            // elements per lane per unit
-constexpr int U_EL = WAVE * U_IT;  // driver elements per unit
+constexpr int U_EL = WAVE * U_IT;  // driver elements per unit of a whole wave
+// Short sets: units of SUB_LANES lanes, eight rows to a wave.  A wave per row
+// left 246 of its 256 element slots idle on rows of ten (SpGEMM, SpMV,
+// small graphs), and every row paid a whole wave's reduction.  Taken when
+// the smallest participating level's sets hold at most SUB_AVG elements on
+// average; longer rows cost only more units.
+// SpMV of 250,000 power-law rows (4 M entries): the leaf 1.56 -> 0.24 ms,
+// with sums stored by a row's only unit and carried over a hub row's units;
+// Q5 shape at 24 M rows: its three SUM leaves 1.6 -> 0.33 ms.
+constexpr int SUB_LANES = 8;
+constexpr uint64_t SUB_AVG = 24;
 // Two-set leaves: rows whose two sets hold TOP_MIN elements or more
 // together form the top bucket, the largest intersections.  They run as a
 // launch of their own.  Units of TOP_IT elements per lane (twice the loads
@@ -185,6 +195,7 @@ struct LeafArgs {
   uint32_t D;
   // streamed groups (outputs are a prefix of the order)
   const uint32_t* gid;    // group of each frontier row (null: one group)
+  uint32_t own_group;     // every frontier row is a group of its own
   uint64_t* gcount;
   int64_t* gacc;          // n_groups x EXACT_MAXD slots
   // materialized tuples
@@ -228,7 +239,8 @@ struct ElemArgs {
   const uint64_t* U;      // exclusive scan of per-row work units, nrows + 1 entries
   const uint32_t* urow;   // row of each unit
   uint64_t total_units;
-  uint64_t nvblk;         // virtual blocks of J_NW units
+  uint64_t nvblk;         // virtual blocks of J_NW waves of units
+  uint32_t lanes;         // lanes per unit (WAVE or SUB_LANES)
   uint32_t need_pos_mask; // participants whose position is needed
   // fill
   uint32_t n_atoms;
@@ -283,8 +295,8 @@ constexpr uint8_t DRV_MERGE = 0xfe;
 // leaf2: the row's two sets feed the two-set leaf (word-AND and merge
 // allowed; top-bucket rows get units of TOP_EL elements, counted into
 // n_units[0]; merged rows units of MERGE_TILE, counted into n_units[1]).
-__global__ void k_work(WorkArgs a, uint64_t nrows, uint32_t* work, uint8_t* drv, uint32_t* units, uint32_t leaf2,
-                       unsigned long long* n_units) {
+__global__ void k_work(WorkArgs a, uint64_t nrows, uint32_t* work, uint8_t* drv, uint32_t* units, uint32_t unit_el,
+                       uint32_t leaf2, unsigned long long* n_units) {
   __shared__ uint64_t s_red[256 / WAVE];
   uint64_t top_units = 0, merge_units = 0;
   for (uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; r < nrows; r += (uint64_t)gridDim.x * blockDim.x) {
@@ -329,7 +341,7 @@ __global__ void k_work(WorkArgs a, uint64_t nrows, uint32_t* work, uint8_t* drv,
     }
     if (empty) best = 0;
     uint8_t dv = (uint8_t)bi;
-    uint32_t chunk = U_EL;
+    uint32_t chunk = unit_el;
     if (leaf2 && a.np == 2 && !empty && probe[0] > 1.0f && probe[1] > 1.0f) {
       // two sorted sets of similar, large size whose values are dense
       // enough for the merge tiles' LDS bitmaps: merged
@@ -386,16 +398,19 @@ __global__ void k_work(WorkArgs a, uint64_t nrows, uint32_t* work, uint8_t* drv,
 }
 
 // Rows of a leaf hit: for each atom, the range of rows of its leaf node.
+// NA bounds the query's atoms, so that the per-atom arrays of the common
+// two-atom queries stay small in registers.
+template <int NA>
 struct HitRows {
-  uint32_t rb[MAXA], re[MAXA];
+  uint32_t rb[NA], re[NA];
   uint64_t mult;  // product of run lengths of the non-expanding atoms
 };
 
-template <int NP>
-__device__ __forceinline__ void leaf_rows(const LeafArgs& L, uint64_t r, const uint32_t* ppos, HitRows& h) {
+template <int NP, int NA>
+__device__ __forceinline__ void leaf_rows(const LeafArgs& L, uint64_t r, const uint32_t* ppos, HitRows<NA>& h) {
   h.mult = 1;
 #pragma unroll
-  for (int e = 0; e < MAXA; e++) {
+  for (int e = 0; e < NA; e++) {
     if (e >= (int)L.n_atoms) break;
     const LeafAtom& A = L.at[e];
     uint32_t lp = 0;
@@ -420,11 +435,12 @@ __device__ __forceinline__ void leaf_rows(const LeafArgs& L, uint64_t r, const u
 // Product term of one row combination: (hi, lo) with hi + lo exact.  The
 // factors are taken in atom order; all but the last are multiplied with
 // rounding, the last multiplication is exact (a two-product).
+template <int NA>
 __device__ __forceinline__ void term_of(const LeafArgs& L, const uint32_t* cur, double& hi, double& lo) {
   double p = 1.0, last = 1.0;
   int nf = 0;
 #pragma unroll
-  for (int e = 0; e < MAXA; e++) {
+  for (int e = 0; e < NA; e++) {
     if (e >= (int)L.n_atoms) break;
     if (!L.at[e].anno) continue;
     double v = L.at[e].anno[cur[e]];
@@ -446,10 +462,11 @@ __device__ __forceinline__ void term_of(const LeafArgs& L, const uint32_t* cur, 
 
 // Number of row combinations of the expanding atoms (UINT64_MAX when it
 // does not fit 64 bits).
-__device__ __forceinline__ uint64_t combos(const LeafArgs& L, const HitRows& h) {
+template <int NA>
+__device__ __forceinline__ uint64_t combos(const LeafArgs& L, const HitRows<NA>& h) {
   uint64_t c = 1;
 #pragma unroll
-  for (int e = 0; e < MAXA; e++) {
+  for (int e = 0; e < NA; e++) {
     if (e >= (int)L.n_atoms) break;
     if (L.at[e].expand) c = sat_mul_u64(c, (uint64_t)(h.re[e] - h.rb[e]));
   }
@@ -463,10 +480,11 @@ __device__ __forceinline__ void atomic_add_count(uint64_t* c, uint64_t v, uint32
 }
 
 // Advance the odometer over expanding atoms; false when exhausted.
-__device__ __forceinline__ bool next_combo(const LeafArgs& L, const HitRows& h, uint32_t* cur) {
+template <int NA>
+__device__ __forceinline__ bool next_combo(const LeafArgs& L, const HitRows<NA>& h, uint32_t* cur) {
   bool carry = true;
 #pragma unroll
-  for (int e = MAXA - 1; e >= 0; e--) {
+  for (int e = NA - 1; e >= 0; e--) {
     if (!carry) break;
     if (e >= (int)L.n_atoms || !L.at[e].expand) continue;
     if (++cur[e] < h.re[e]) {
@@ -478,10 +496,83 @@ __device__ __forceinline__ bool next_combo(const LeafArgs& L, const HitRows& h, 
   return !carry;
 }
 
+// v of the lane that a DPP control names (a register move, no LDS trip).
+template <int CTRL, class T>
+__device__ __forceinline__ T dpp64(T v) {
+  static_assert(sizeof(T) == 8, "dpp64");
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)((uint64_t)v >> 32), CTRL, 0xf, 0xf, true);
+  return (T)(((uint64_t)hi << 32) | lo);
+}
+
+// Sum over the LPR consecutive lanes of a unit; every lane gets it.
+template <int LPR, class T>
+__device__ __forceinline__ T unit_sum(T v) {
+  if constexpr (LPR == 8) {
+    v += dpp64<0xB1>(v);    // quad_perm [1,0,3,2]
+    v += dpp64<0x4E>(v);    // quad_perm [2,3,0,1]: every lane holds its quad's sum
+    v += dpp64<0x141>(v);   // row_half_mirror: the other quad's
+    return v;
+  } else {
+#pragma unroll
+    for (int d = LPR / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, WAVE);
+    return v;
+  }
+}
+
+// A unit's carried count and sum into its group's slots: stored when `only`
+// (the group is this unit's row's, which has no other unit; normalized
+// digits are a valid shared-form value), else added; `whole`: by the wave,
+// whose units all end the same group.  Clears what was carried.
+template <int LPR>
+__device__ __forceinline__ void flush_group(uint64_t& run_cnt, RegAcc& run_acc, uint64_t* count, int64_t* slots,
+                                            bool sum, uint32_t D, bool only, bool whole, uint32_t* err, uint32_t& bad) {
+  // lane counts below 2^58 cannot wrap the sum over the lanes
+  if (run_cnt >= (1ull << 58)) bad |= ERR_COUNT_OVERFLOW;
+  const uint64_t cnt = whole ? wave_sum(run_cnt) : unit_sum<LPR>(run_cnt);
+  const bool writer = whole ? lane_id() == 0 : lane_id() % LPR == 0;
+  if (writer && only) *count = cnt;
+  else if (writer && cnt) atomic_add_count(count, cnt, err);
+  if (sum) {
+    run_acc.normalize(D);
+    int64_t c = 0;
+#pragma unroll
+    for (int i = 0; i < EXACT_MAXD; i++) {
+      if (i >= (int)D) break;
+      // normalized lane digits: the sum over the lanes stays below 2^38
+      int64_t v = c + (whole ? wave_sum(run_acc.s[i]) : unit_sum<LPR>(run_acc.s[i]));
+      if (i + 1 < (int)D) {
+        c = v >> 32;
+        v -= c << 32;
+      }
+      if (writer && only) slots[i] = v;
+      else if (writer && v) atomic_add_digit(slots, (uint32_t)i, D, v);
+    }
+  }
+  run_cnt = 0;
+  run_acc.clear();
+}
+
+// End the carried group (run_g) of the lanes that ask for it.  A wave whose
+// units all end one group adds once: thousands of units of a hub row would
+// otherwise queue at one accumulator.  Every lane of the wave calls this.
+template <int LPR>
+__device__ __forceinline__ void end_groups(bool mine, uint64_t run_g, uint64_t& run_cnt, RegAcc& run_acc,
+                                           uint64_t* gcount, int64_t* gacc, bool sum, uint32_t D, uint32_t* err,
+                                           uint32_t& bad) {
+  if (!__any(mine)) return;
+  const bool whole = __all(mine && run_g == (uint64_t)__shfl((unsigned long long)run_g, 0, WAVE));
+  if (whole || mine)
+    flush_group<LPR>(run_cnt, run_acc, gcount + run_g, gacc + run_g * EXACT_MAXD, sum, D, false, whole, err, bad);
+}
+
 // NP bounds the participants at the attribute (a.np <= NP): the per-set
-// arrays stay in registers at the size the plan needs.
-template <int MODE, int NP>
+// arrays stay in registers at the size the plan needs.  LPR lanes work on a
+// unit of LPR * U_IT driver elements.
+template <int MODE, int NP, int LPR, int NA>
 __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
+  constexpr int UPW = WAVE / LPR;               // units per wave
+  constexpr uint32_t UNIT_EL = LPR * U_IT;
   __shared__ uint64_t s_wcnt[J_NW];
   __shared__ uint64_t s_red[J_NW];
   __shared__ unsigned long long s_cnt;
@@ -494,6 +585,7 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
   const int tid = threadIdx.x;
   const int w = tid / WAVE;
   const int lane = lane_id();
+  const int ul = lane % LPR;                    // lane within the unit
   const LeafArgs& L = a.leaf;
   constexpr bool NEED_POS = !(MODE == M_COUNT || MODE == M_LEAF_COUNT);
   constexpr bool LEAF_AGG = (MODE == M_LEAF_A || MODE == M_LEAF_COUNT);
@@ -510,22 +602,28 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
     s_cnt = 0;
     for (int i = 0; i < EXACT_MAXD; i++) s_acc[i] = 0;
   }
-  // one-group aggregation is carried across the block's virtual blocks
+  // M_LEAF_A: counts and sums are carried in registers from unit to unit
+  // while the group stays the same (one_group: to the end)
   uint64_t run_cnt = 0;
   RegAcc run_acc;
   run_acc.clear();
+  uint64_t run_g = UINT64_MAX;
   uint32_t bad = 0;
+  // carried units are taken from one contiguous range per block
+  const uint64_t vper = MODE == M_LEAF_A ? (a.nvblk + gridDim.x - 1) / gridDim.x : 1;
+  const uint64_t vstep = MODE == M_LEAF_A ? 1 : gridDim.x;
+  const uint64_t vend = MODE == M_LEAF_A ? min<uint64_t>(a.nvblk, (blockIdx.x + 1) * vper) : a.nvblk;
 
   // The grid is capped (a dispatch holds < 2^32 work-items); each block
-  // walks virtual blocks of J_NW units.
-  for (uint64_t vb = blockIdx.x; vb < a.nvblk; vb += gridDim.x) {
-    const uint64_t u = vb * J_NW + w;
-    const bool wave_valid = u < a.total_units;
+  // walks virtual blocks of J_NW waves of units.
+  for (uint64_t vb = blockIdx.x * vper; vb < vend; vb += vstep) {
+    const uint64_t u = (vb * J_NW + w) * UPW + lane / LPR;
+    const bool unit_valid = u < a.total_units;
 
-    // the wave's row and chunk (uniform across the wave)
+    // the unit's row and chunk (uniform across its lanes)
     uint64_t r = 0;
     uint32_t chunk = 0, work = 0, d = 0;
-    if (wave_valid) {
+    if (unit_valid) {
       r = a.urow[u];
       chunk = (uint32_t)(u - a.U[r]);
       work = (uint32_t)(a.W[r + 1] - a.W[r]);
@@ -539,7 +637,7 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
     for (int p = 0; p < NP; p++) {
       b[p] = e[p] = 0;
       sidx[p] = 0;
-      if (p < (int)a.np && wave_valid) dset_range(a.set[p], r, b[p], e[p], sidx[p]);
+      if (p < (int)a.np && unit_valid) dset_range(a.set[p], r, b[p], e[p], sidx[p]);
       if (p == (int)d) {
         bd = b[p];
         dkeys = a.set[p].keys;
@@ -551,8 +649,8 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
     uint32_t ppos[U_IT][NEED_POS ? NP : 1];
 #pragma unroll
     for (int it = 0; it < U_IT; it++) {
-      const uint32_t i = chunk * U_EL + it * WAVE + lane;
-      const bool valid = wave_valid && i < work;
+      const uint32_t i = chunk * UNIT_EL + it * LPR + ul;
+      const bool valid = unit_valid && i < work;
       hit[it] = valid;
       x[it] = valid ? dkeys[bd + i] : 0u;
       if constexpr (NEED_POS) {
@@ -582,8 +680,8 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
       if (one_group) {
         run_cnt += c;
       } else {
-        c = wave_sum(c);
-        if (wave_valid && lane == 0 && c) atomicAdd((unsigned long long*)&L.gcount[L.gid[r]], (unsigned long long)c);
+        c = unit_sum<LPR>(c);
+        if (unit_valid && ul == 0 && c) atomicAdd((unsigned long long*)&L.gcount[L.gid[r]], (unsigned long long)c);
       }
     } else if (MODE == M_COUNT) {
       uint64_t c = 0;
@@ -600,13 +698,21 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
       __syncthreads();
       uint64_t off = a.blk_off[vb];
       for (int j = 0; j < w; j++) off += s_wcnt[j];
+      // the wave's units one after another: hits of the units below first
+      const int u0 = lane - ul;
+      const uint64_t below = (1ull << u0) - 1;
+      const uint64_t mine = (LPR == WAVE ? ~0ull : (1ull << (LPR & 63)) - 1) << u0;
+      if constexpr (LPR < WAVE) {
+#pragma unroll
+        for (int it = 0; it < U_IT; it++) off += (uint64_t)__popcll(ballot(hit[it]) & below);
+      }
 #pragma unroll
       for (int it = 0; it < U_IT; it++) {
-        const uint64_t bal = ballot(hit[it]);
+        const uint64_t bal = ballot(hit[it]) & mine;
         if (hit[it]) {
           const uint64_t o = off + lanes_below(bal);
 #pragma unroll
-          for (int at = 0; at < MAXA; at++) {
+          for (int at = 0; at < NA; at++) {
             if (at >= (int)a.n_atoms) break;
             uint32_t* po = a.pos_out[at];
             if (!po) continue;
@@ -633,51 +739,39 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
       }
       __syncthreads();
     } else if (MODE == M_LEAF_A) {
+      const uint64_t g = !one_group && unit_valid ? (uint64_t)L.gid[r] : UINT64_MAX;
+      // (uniform over a unit's lanes; a unit without a row ends nothing)
+      if (!one_group) {
+        end_groups<LPR>(unit_valid && run_g != UINT64_MAX && run_g != g, run_g, run_cnt, run_acc, L.gcount, L.gacc,
+                        L.sum, L.D, L.err, bad);
+        if (unit_valid) run_g = g;
+      }
       uint64_t cnt = 0;
-      RegAcc acc;
-      acc.clear();
 #pragma unroll
       for (int it = 0; it < U_IT; it++) {
         if (!hit[it]) continue;
-        HitRows h;
-        leaf_rows<NP>(L, r, ppos[it], h);
+        HitRows<NA> h;
+        leaf_rows<NP, NA>(L, r, ppos[it], h);
         const uint64_t nc = combos(L, h);
         cnt = sat_add_u64(cnt, sat_mul_u64(h.mult, nc));
         if (L.sum && nc) {
-          uint32_t cur[MAXA];
+          uint32_t cur[NA];
 #pragma unroll
-          for (int at = 0; at < MAXA; at++) cur[at] = h.rb[at];
+          for (int at = 0; at < NA; at++) cur[at] = h.rb[at];
           do {
             double hi, lo;
-            term_of(L, cur, hi, lo);
-            bool ok = acc.add(hi, L.lsb, L.D, h.mult);
-            ok = acc.add(lo, L.lsb, L.D, h.mult) && ok;
+            term_of<NA>(L, cur, hi, lo);
+            bool ok = run_acc.add(hi, L.lsb, L.D, h.mult);
+            ok = run_acc.add(lo, L.lsb, L.D, h.mult) && ok;
             if (!ok) bad |= 1u;
           } while (next_combo(L, h, cur));
         }
       }
       if (cnt == UINT64_MAX) bad |= ERR_COUNT_OVERFLOW;
-      if (L.sum) acc.normalize(L.D);
-      if (one_group) {
-        run_cnt = sat_add_u64(run_cnt, cnt);
-#pragma unroll
-        for (int i = 0; i < EXACT_MAXD; i++) run_acc.s[i] += acc.s[i];
-        if (L.sum) run_acc.normalize(L.D);
-      } else {
-        // the wave's unit belongs to one row, hence to one group; lane
-        // counts below 2^58 cannot wrap the wave's sum
-        if (__any(cnt >= (1ull << 58))) bad |= ERR_COUNT_OVERFLOW;
-        cnt = wave_sum(cnt);
-        if (wave_valid) {
-          const uint64_t g = L.gid[r];
-          if (lane == 0 && cnt) atomic_add_count(&L.gcount[g], cnt, L.err);
-          if (L.sum)
-            for (uint32_t i = 0; i < L.D; i++) {
-              // normalized lane digits: the wave's sum stays below 2^38
-              const int64_t v = wave_sum(acc.s[i]);
-              if (lane == 0 && v) atomic_add_digit(L.gacc + g * EXACT_MAXD, i, L.D, v);
-            }
-        }
+      run_cnt = sat_add_u64(run_cnt, cnt);
+      if (!one_group && unit_valid && L.own_group && work <= UNIT_EL) {
+        flush_group<LPR>(run_cnt, run_acc, L.gcount + g, L.gacc + g * EXACT_MAXD, L.sum, L.D, true, false, L.err, bad);
+        run_g = UINT64_MAX;
       }
     } else if (MODE == M_LEAF_B_COUNT) {
       // rows to materialize; a block's count saturates at UINT32_MAX, which
@@ -686,8 +780,8 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
 #pragma unroll
       for (int it = 0; it < U_IT; it++) {
         if (!hit[it]) continue;
-        HitRows h;
-        leaf_rows<NP>(L, r, ppos[it], h);
+        HitRows<NA> h;
+        leaf_rows<NP, NA>(L, r, ppos[it], h);
         c = sat_add_u64(c, combos(L, h));
       }
       c = min(c, (uint64_t)UINT32_MAX);
@@ -700,8 +794,8 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
       for (int it = 0; it < U_IT; it++) {
         m[it] = 0;
         if (hit[it]) {
-          HitRows h;
-          leaf_rows<NP>(L, r, ppos[it], h);
+          HitRows<NA> h;
+          leaf_rows<NP, NA>(L, r, ppos[it], h);
           m[it] = combos(L, h);
         }
         wtot += wave_sum(m[it]);
@@ -715,11 +809,11 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
         const uint64_t incl = wave_incl_scan(m[it]);
         const uint64_t tot = __shfl(incl, WAVE - 1, WAVE);
         if (m[it]) {
-          HitRows h;
-          leaf_rows<NP>(L, r, ppos[it], h);
-          uint32_t cur[MAXA];
+          HitRows<NA> h;
+          leaf_rows<NP, NA>(L, r, ppos[it], h);
+          uint32_t cur[NA];
 #pragma unroll
-          for (int at = 0; at < MAXA; at++) cur[at] = h.rb[at];
+          for (int at = 0; at < NA; at++) cur[at] = h.rb[at];
           uint64_t o = off + incl - m[it];
           do {
             for (uint32_t c = 0; c < L.n_cols; c++) {
@@ -731,7 +825,7 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
                 v = 0;
                 const int32_t ga = L.gm_atom[c];
 #pragma unroll
-                for (int at = 0; at < MAXA; at++)
+                for (int at = 0; at < NA; at++)
                   if (at == ga) v = L.gm_col[c][cur[at]];
               }
               L.col_out[c][o] = v;
@@ -739,7 +833,7 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
             L.mult_out[o] = h.mult;
             if (L.sum) {
               double hi, lo;
-              term_of(L, cur, hi, lo);
+              term_of<NA>(L, cur, hi, lo);
               L.hi_out[o] = hi;
               L.lo_out[o] = lo;
             }
@@ -757,12 +851,12 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
 #pragma unroll
       for (int it = 0; it < U_IT; it++) {
         if (!hit[it] || table_full) continue;
-        HitRows h;
-        leaf_rows<NP>(L, r, ppos[it], h);
+        HitRows<NA> h;
+        leaf_rows<NP, NA>(L, r, ppos[it], h);
         if (!combos(L, h)) continue;
-        uint32_t cur[MAXA];
+        uint32_t cur[NA];
 #pragma unroll
-        for (int at = 0; at < MAXA; at++) cur[at] = h.rb[at];
+        for (int at = 0; at < NA; at++) cur[at] = h.rb[at];
         do {
           auto val = [&](uint32_t c) -> uint32_t {
             const int32_t src = L.col_src[c];
@@ -771,7 +865,7 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
             uint32_t v = 0;
             const int32_t ga = L.gm_atom[c];
 #pragma unroll
-            for (int at = 0; at < MAXA; at++)
+            for (int at = 0; at < NA; at++)
               if (at == ga) v = L.gm_col[c][cur[at]];
             return v;
           };
@@ -848,7 +942,7 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
             else atomic_add_count(&L.gcount[slot], h.mult, L.err);
             if (L.sum) {
               double hi, lo;
-              term_of(L, cur, hi, lo);
+              term_of<NA>(L, cur, hi, lo);
               int64_t* dig = (GAGG && L.glds) ? (int64_t*)&s_gdig[slot * EXACT_MAXD] : L.gacc + slot * L.D;
               bool fits = atomic_add_term(dig, hi, L.lsb, L.D, h.mult);
               fits = atomic_add_term(dig, lo, L.lsb, L.D, h.mult) && fits;
@@ -877,6 +971,8 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
       }
     }
   }
+  if (MODE == M_LEAF_A && !one_group)
+    end_groups<LPR>(run_g != UINT64_MAX, run_g, run_cnt, run_acc, L.gcount, L.gacc, L.sum, L.D, L.err, bad);
   if (LEAF_AGG) {
     if (bad) atomicOr(L.err, bad);
     if (one_group) {
@@ -885,10 +981,13 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
       if (__any(run_cnt >= (1ull << 58))) atomicOr(L.err, ERR_COUNT_OVERFLOW);
       const uint64_t c = wave_sum(run_cnt);
       if (lane == 0 && c) atomic_add_count((uint64_t*)&s_cnt, c, L.err);
+      if (MODE == M_LEAF_A && L.sum) run_acc.normalize(L.D);
       if (MODE == M_LEAF_A && L.sum)
-        for (uint32_t i = 0; i < L.D; i++) {
+#pragma unroll
+        for (int i = 0; i < EXACT_MAXD; i++) {
+          if (i >= (int)L.D) break;
           const int64_t v = wave_sum(run_acc.s[i]);
-          if (lane == 0 && v) atomic_add_digit((int64_t*)s_acc, i, L.D, v);
+          if (lane == 0 && v) atomic_add_digit((int64_t*)s_acc, (uint32_t)i, L.D, v);
         }
       __syncthreads();
       if (tid == 0) {
@@ -905,9 +1004,20 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
 
 template <int MODE>
 void launch_elem(const ElemArgs& a, unsigned grid, hipStream_t s) {
-  if (a.np <= 2) k_elem<MODE, 2><<<grid, J_NT, 0, s>>>(a);
-  else if (a.np <= 4) k_elem<MODE, 4><<<grid, J_NT, 0, s>>>(a);
-  else k_elem<MODE, MAXP><<<grid, J_NT, 0, s>>>(a);
+  const bool sub = a.lanes == SUB_LANES;
+  if (a.n_atoms <= 2) {  // (then np <= 2)
+    if (sub) k_elem<MODE, 2, SUB_LANES, 2><<<grid, J_NT, 0, s>>>(a);
+    else k_elem<MODE, 2, WAVE, 2><<<grid, J_NT, 0, s>>>(a);
+  } else if (sub) {
+    if (a.np <= 2) k_elem<MODE, 2, SUB_LANES, MAXA><<<grid, J_NT, 0, s>>>(a);
+    else k_elem<MODE, 4, SUB_LANES, MAXA><<<grid, J_NT, 0, s>>>(a);
+  } else if (a.np <= 2) {
+    k_elem<MODE, 2, WAVE, MAXA><<<grid, J_NT, 0, s>>>(a);
+  } else if (a.np <= 4) {
+    k_elem<MODE, 4, WAVE, MAXA><<<grid, J_NT, 0, s>>>(a);
+  } else {
+    k_elem<MODE, MAXP, WAVE, MAXA><<<grid, J_NT, 0, s>>>(a);
+  }
 }
 
 // Row of every work unit.  A thread writes up to UROW_SMALL units of its
@@ -1739,7 +1849,9 @@ __global__ void k_seg_accumulate(SegAccArgs a, uint64_t n) {
 }
 
 // A dispatch counts work-items in 32 bits: cap the grid and let blocks
-// stride over virtual blocks.
+// stride over virtual blocks.  Blocks that carry sums take contiguous
+// ranges, long enough that a hub row's units meet in few of them.
+constexpr uint64_t CARRY_BLOCKS = 2048;
 unsigned elem_grid(uint64_t nvblk) { return (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(nvblk, 32768)); }
 // The merge launch: as many blocks as fit on the device at once; each loops
 // over a contiguous range of tiles, loading the next while counting one.
@@ -1795,7 +1907,7 @@ DSet make_dset(const lh_plan_t* p, const Participant& pt, const Frontier& F) {
 }
 
 // Per-row work (smallest participating set), its exclusive scan, and the
-// cut of every row into work units of U_EL elements.
+// cut of every row into work units.
 struct DepthWork {
   DBuf<uint64_t> W, U;
   DBuf<uint64_t> n_top;     // two-set leaves: units of the top bucket, then of merged rows (device)
@@ -1814,6 +1926,13 @@ void depth_work(const lh_plan_t* p, uint32_t d, const Frontier& F, ElemArgs& a, 
     wa.set[i] = make_dset(p, parts[i], F);
     a.set[i] = wa.set[i];
   }
+  // average size of the smallest participating level's sets
+  uint64_t avg = UINT64_MAX;
+  for (const Participant& pt : parts) {
+    const Level& L = p->atoms[pt.atom].trie->lv[pt.level];
+    avg = std::min(avg, L.n / std::max<uint64_t>(1, L.n_sets));
+  }
+  a.lanes = !leaf2 && wa.np <= 4 && avg <= SUB_AVG ? SUB_LANES : WAVE;
   DBuf<uint32_t> work(F.n, s), units(F.n, s);
   dw.drv.alloc(F.n, s);
   dw.W.alloc(F.n + 1, s);
@@ -1824,7 +1943,7 @@ void depth_work(const lh_plan_t* p, uint32_t d, const Frontier& F, ElemArgs& a, 
       dw.n_top.alloc(2, s);
       fill_u64(dw.n_top.p, 0, 2, s);
     }
-    k_work<<<grid_for(F.n), 256, 0, s>>>(wa, F.n, work.p, dw.drv.p, units.p, leaf2 ? 1u : 0u,
+    k_work<<<grid_for(F.n), 256, 0, s>>>(wa, F.n, work.p, dw.drv.p, units.p, a.lanes * U_IT, leaf2 ? 1u : 0u,
                                          leaf2 ? (unsigned long long*)dw.n_top.p : nullptr);
   }
   LH_HIP(hipGetLastError());
@@ -1841,7 +1960,8 @@ void depth_work(const lh_plan_t* p, uint32_t d, const Frontier& F, ElemArgs& a, 
     k_unit_rows_big<<<1024, 256, 0, s>>>(dw.U.p, big.p, nbig.p, dw.urow.p);
     LH_HIP(hipGetLastError());
   }
-  dw.nblk = (dw.units + J_NW - 1) / J_NW;
+  const uint64_t per_block = (uint64_t)J_NW * (WAVE / a.lanes);
+  dw.nblk = (dw.units + per_block - 1) / per_block;
   a.nvblk = dw.nblk;
   a.W = dw.W.p;
   a.drv = dw.drv.p;
@@ -1873,6 +1993,7 @@ void step(const lh_plan_t* p, uint32_t d, Frontier& F, hipStream_t s) {
   DBuf<uint32_t> bcnt(nblk, s);
   a.blk_cnt = bcnt.p;
   a.need_pos_mask = 0;
+  a.n_atoms = (uint32_t)p->atoms.size();
   {
     static const char* names[MAXV] = {"join_count_d0", "join_count_d1", "join_count_d2", "join_count_d3",
                                       "join_count_d4", "join_count_d5", "join_count_d6", "join_count_d7",
@@ -2342,6 +2463,7 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
     LH_HIP(hipMemsetAsync(gcount.p, 0, gcount.n * sizeof(uint64_t), s));
     if (is_sum) LH_HIP(hipMemsetAsync(gacc.p, 0, gacc.n * sizeof(int64_t), s));
     L.gid = no > 0 ? F.gid.p : nullptr;
+    L.own_group = no > 0 && no == leaf ? 1u : 0u;
     L.gcount = gcount.p;
     L.gacc = gacc.p;
     if (total) {
@@ -2426,7 +2548,7 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
       } else {
         ProfScope ps("leaf_aggregate", s, F.n, total);
         if (all_set) launch_elem<M_LEAF_COUNT>(a, elem_grid(nblk), s);
-        else launch_elem<M_LEAF_A>(a, elem_grid(nblk), s);
+        else launch_elem<M_LEAF_A>(a, (unsigned)std::min<uint64_t>(nblk, CARRY_BLOCKS), s);
       }
       LH_HIP(hipGetLastError());
     }
