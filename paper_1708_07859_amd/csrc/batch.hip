@@ -183,7 +183,7 @@ constexpr int DSTRIDE = EXACT_MAXD + 1;
 // A row with fewer products than this keeps its LDS accumulators in signed
 // slots: a product adds two terms, each at most one word below 2^32 to any
 // slot, so no slot can leave int64 (2 * 2^30 * 2^32 = 2^63).
-constexpr uint64_t BOUNDED_PRODUCTS = 1ull << 30;
+constexpr uint64_t BOUNDED_PRODUCTS = SIGNED_TERMS;
 
 // Exact sum held in the LDS slots (digits) of one accumulator: add v.
 // bounded (the row has fewer than BOUNDED_PRODUCTS products): signed slots,
@@ -191,24 +191,7 @@ constexpr uint64_t BOUNDED_PRODUCTS = 1ull << 30;
 // shared slot form, which carries every wrap, so any number of terms is
 // exact.  A row uses one form for all of its accumulators.
 __device__ __forceinline__ bool lds_add_term(long long* slots, double v, int32_t lsb, uint32_t D, bool bounded) {
-  if (!bounded) return atomic_add_term((int64_t*)slots, v, lsb, D, 1);
-  if (v == 0.0) return true;
-  int32_t k0;
-  uint32_t p[5];
-  bool neg;
-  if (!term_words(v, lsb, 1, k0, p, neg)) return false;
-  bool ok = true;
-#pragma unroll
-  for (int j = 0; j < 5; j++) {
-    if (!p[j]) continue;
-    if (k0 + j >= (int32_t)D) {
-      ok = false;
-      continue;
-    }
-    const int64_t w = neg ? -(int64_t)p[j] : (int64_t)p[j];
-    atomicAdd((unsigned long long*)&slots[k0 + j], (unsigned long long)w);
-  }
-  return ok;
+  return bounded ? signed_add_term((int64_t*)slots, v, lsb, D, 1) : atomic_add_term((int64_t*)slots, v, lsb, D, 1);
 }
 
 // The correctly rounded value of an LDS accumulator in the form lds_add_term
@@ -218,9 +201,7 @@ __device__ __forceinline__ double lds_round(const long long* slots, uint32_t D, 
                                             uint32_t* err) {
   if (!bounded) return exact_round((const int64_t*)slots, D, lsb, err);
   RegAcc r;
-#pragma unroll
-  for (int i = 0; i < EXACT_MAXD; i++) r.s[i] = i < (int)D ? (int64_t)slots[i] : 0;
-  r.normalize(D);
+  r.load_signed((const int64_t*)slots, D);
   return exact_round(r.s, D, lsb, err);
 }
 

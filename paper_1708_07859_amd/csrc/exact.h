@@ -12,7 +12,7 @@
 // at most five 32-bit words, so every addition into a slot is below 2^32
 // in magnitude whatever the multiplicity.
 //
-// Two slot forms exist:
+// Three slot forms exist:
 //  - register accumulators (RegAcc) add signed words into int64 slots and
 //    carry every 2^24 additions, so no slot leaves int64;
 //  - shared accumulators (global or LDS, updated with atomics) keep every
@@ -23,9 +23,13 @@
 //    wraps counted this way are exactly those of the serial history, and
 //    the value is kept exactly for any number of additions.  The top slot
 //    is signed; the plan sizes D so that it stays far inside int64.
-// Both forms are read with the same carry rule (lower slots unsigned, top
+//  - signed slots (global or LDS) take plain int64 atomic adds that nobody
+//    waits for, where fewer than SIGNED_TERMS products can reach a slot: a
+//    product adds two exact terms, each at most one word below 2^32 to any
+//    slot, so no slot leaves int64 (2 * 2^30 * 2^32 = 2^63).
+// The first two are read with the same carry rule (lower slots unsigned, top
 // slot signed), since a normalized register accumulator is also a valid
-// shared-form value.
+// shared-form value; signed slots are carried into digits first.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -171,6 +175,12 @@ struct RegAcc {
     }
     pending = 0;
   }
+  // Take the value of signed slots, normalized.
+  __device__ __forceinline__ void load_signed(const int64_t* slot, uint32_t D) {
+#pragma unroll
+    for (int i = 0; i < EXACT_MAXD; i++) s[i] = i < (int)D ? slot[i] : 0;
+    normalize(D);
+  }
   __device__ __forceinline__ bool zero() const {
     int64_t o = 0;
 #pragma unroll
@@ -221,6 +231,29 @@ __device__ __forceinline__ bool atomic_add_term(int64_t* slots, double v, int32_
       continue;
     }
     atomic_add_digit(slots, (uint32_t)(k0 + j), D, neg ? -(int64_t)p[j] : (int64_t)p[j]);
+  }
+  return ok;
+}
+
+// Add mult * v into signed slots: at most five atomics whose results nobody
+// waits for.  Returns false if v does not fit the window.
+constexpr uint64_t SIGNED_TERMS = 1ull << 30;
+__device__ __forceinline__ bool signed_add_term(int64_t* slots, double v, int32_t lsb, uint32_t D, uint64_t mult) {
+  if (v == 0.0) return true;
+  int32_t k0;
+  uint32_t p[5];
+  bool neg;
+  if (!term_words(v, lsb, mult, k0, p, neg)) return false;
+  bool ok = true;
+#pragma unroll
+  for (int j = 0; j < 5; j++) {
+    if (!p[j]) continue;
+    if (k0 + j >= (int32_t)D) {
+      ok = false;
+      continue;
+    }
+    const int64_t w = neg ? -(int64_t)p[j] : (int64_t)p[j];
+    atomicAdd((unsigned long long*)&slots[k0 + j], (unsigned long long)w);
   }
   return ok;
 }

@@ -33,7 +33,7 @@ constexpr int U_EL = WAVE * U_IT;  // driver elements per unit of a whole wave
 // small graphs), and every row paid a whole wave's reduction.  Taken when
 // the smallest participating level's sets hold at most SUB_AVG elements on
 // average; longer rows cost only more units.
-// SpMV of 250,000 power-law rows (4 M entries): the leaf 1.56 -> 0.24 ms,
+// SpMV of 250,000 power-law rows (4 M entries): the leaf 1.56 -> 0.23 ms,
 // with sums stored by a row's only unit and carried over a hub row's units;
 // Q5 shape at 24 M rows: its three SUM leaves 1.6 -> 0.33 ms.
 constexpr int SUB_LANES = 8;
@@ -149,6 +149,14 @@ __device__ __forceinline__ uint32_t sampled_lower_bound(const uint32_t* keys, co
   return keys[pos] < x ? pos + 1 : pos;
 }
 
+__device__ __forceinline__ void wave_lds_sync() {
+  // LDS operations of one wave complete in order; this keeps the compiler
+  // from moving them across the point where lanes read what others wrote
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Membership of x in set [b, e) (descriptor sidx); its position if asked.
 __device__ __forceinline__ bool dset_find(const DSet& st, uint32_t b, uint32_t e, uint64_t sidx, uint32_t x,
                                           bool need_pos, uint32_t& pos) {
@@ -213,6 +221,10 @@ struct LeafArgs {
   // (col_out = its key columns, gtag = slot states); counts in gcount and
   // exact digits in gacc at stride D
   uint32_t gmode;
+  uint32_t gstride;       // words per slot of gacc: the count, then the digits
+  uint32_t gsigned;       // digits are signed slots (few enough tuples), and
+  uint32_t gplain;        // counts cannot overflow: no add's result is waited for
+  uint32_t gpack;         // a tuple's count and digits leave as one request (gstride 2, 4 or 8)
   uint32_t* gtag;
   uint64_t gmask;
   uint64_t radix[MAXV + MAXA];
@@ -579,8 +591,12 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
   __shared__ long long s_acc[EXACT_MAXD];
 
   constexpr bool GAGG = MODE == M_LEAF_B_AGG;
-  __shared__ unsigned long long s_gcnt[GAGG ? GLDS_MAX : 1];
-  __shared__ long long s_gdig[GAGG ? GLDS_MAX * EXACT_MAXD : 1];
+  // few groups: the block's counts and digits; else (gpack) a row of a count
+  // and digits per lane
+  __shared__ unsigned long long s_group[GAGG ? GLDS_MAX * (1 + EXACT_MAXD) : 1];
+  unsigned long long* const s_gcnt = s_group;
+  long long* const s_gdig = (long long*)(s_group + (GAGG ? GLDS_MAX : 0));
+  static_assert(GLDS_MAX == J_NT, "a row per thread takes what the groups take");
 
   const int tid = threadIdx.x;
   const int w = tid / WAVE;
@@ -850,14 +866,20 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
           (__hip_atomic_load(L.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ERR_TABLE_FULL);
 #pragma unroll
       for (int it = 0; it < U_IT; it++) {
-        if (!hit[it] || table_full) continue;
         HitRows<NA> h;
-        leaf_rows<NP, NA>(L, r, ppos[it], h);
-        if (!combos(L, h)) continue;
         uint32_t cur[NA];
+        bool more = hit[it] && !table_full;
+        if (more) {
+          leaf_rows<NP, NA>(L, r, ppos[it], h);
+          more = combos(L, h) != 0;
 #pragma unroll
-        for (int at = 0; at < NA; at++) cur[at] = h.rb[at];
-        do {
+          for (int at = 0; at < NA; at++) cur[at] = h.rb[at];
+        }
+        // the wave's tuples, one per lane and round
+        while (__any(more)) {
+          uint64_t slot = 0;
+          bool ok = more;
+          if (more) {
           auto val = [&](uint32_t c) -> uint32_t {
             const int32_t src = L.col_src[c];
             if (src >= 0) return a.outv_in[src][r];
@@ -869,8 +891,6 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
               if (at == ga) v = L.gm_col[c][cur[at]];
             return v;
           };
-          uint64_t slot = 0;
-          bool ok = true;
           if (L.gmode == 1) {
             for (uint32_t c = 0; c < L.n_cols; c++) slot = slot * L.radix[c] + val(c);
           } else if (L.gkey64) {
@@ -896,10 +916,7 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
               }
               slot = (slot + 1) & L.gmask;
             }
-            if (!ok) {
-              atomicOr(L.err, ERR_TABLE_FULL);
-              break;
-            }
+            if (!ok) atomicOr(L.err, ERR_TABLE_FULL);
           } else {
             uint64_t hs = 0x9e3779b97f4a7c15ull;
             for (uint32_t c = 0; c < L.n_cols; c++) hs = key_mix(hs, val(c));
@@ -932,24 +949,60 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
               // claimed by another upsert that is writing its key: read again
               if (++spins > SLOT_SPIN_MAX) break;
             }
-            if (!ok) {
-              atomicOr(L.err, spins > SLOT_SPIN_MAX ? ERR_SLOT_SPIN : ERR_TABLE_FULL);
-              break;  // this lane's remaining tuples wait for the rerun
-            }
+            if (!ok) atomicOr(L.err, spins > SLOT_SPIN_MAX ? ERR_SLOT_SPIN : ERR_TABLE_FULL);
           }
-          if (ok) {
-            if (GAGG && L.glds) atomic_add_count((uint64_t*)&s_gcnt[slot], h.mult, L.err);
-            else atomic_add_count(&L.gcount[slot], h.mult, L.err);
+          if (!ok) more = false;  // this lane's remaining tuples wait for the rerun
+          }
+          if (L.gpack) {
+            // A tuple's slot lies in one 64-byte line.  The lanes leave their
+            // count and digits in LDS and eight lanes add one tuple's words,
+            // so a tuple is one request: added word by word, 64 lines per
+            // instruction, the requests (44 G/s) were all the time.
+            unsigned long long* row = s_group + tid * (1 + EXACT_MAXD);
+            if (ok) {
+              row[0] = h.mult;
+#pragma unroll
+              for (int q = 1; q < 8; q++) row[q] = 0;
+              double hi, lo;
+              term_of<NA>(L, cur, hi, lo);
+              bool fits = signed_add_term((int64_t*)row + 1, hi, L.lsb, L.D, h.mult);
+              fits = signed_add_term((int64_t*)row + 1, lo, L.lsb, L.D, h.mult) && fits;
+              if (!fits) bad |= 1u;
+            }
+            const uint64_t active = ballot(ok);
+            wave_lds_sync();
+#pragma unroll
+            for (int q = 0; q < 8; q++) {
+              const int from = q * 8 + (lane >> 3);
+              const uint64_t at = __shfl((unsigned long long)slot, from, WAVE);
+              const unsigned long long v = s_group[(w * WAVE + from) * (1 + EXACT_MAXD) + (lane & 7)];
+              // (words past the slot's stride are 0)
+              if ((active >> from & 1ull) && v) atomicAdd((unsigned long long*)L.gacc + at * L.gstride + (lane & 7), v);
+            }
+            wave_lds_sync();
+          } else if (ok) {
+            const bool lds = GAGG && L.glds;
+            int64_t* sl = L.gacc + slot * L.gstride;
+            uint64_t* count = lds ? (uint64_t*)&s_gcnt[slot] : (uint64_t*)sl;
+            if (L.gplain) atomicAdd((unsigned long long*)count, (unsigned long long)h.mult);
+            else atomic_add_count(count, h.mult, L.err);
             if (L.sum) {
               double hi, lo;
               term_of<NA>(L, cur, hi, lo);
-              int64_t* dig = (GAGG && L.glds) ? (int64_t*)&s_gdig[slot * EXACT_MAXD] : L.gacc + slot * L.D;
-              bool fits = atomic_add_term(dig, hi, L.lsb, L.D, h.mult);
-              fits = atomic_add_term(dig, lo, L.lsb, L.D, h.mult) && fits;
+              int64_t* dig = lds ? (int64_t*)&s_gdig[slot * EXACT_MAXD] : sl + 1;
+              bool fits;
+              if (L.gsigned) {
+                fits = signed_add_term(dig, hi, L.lsb, L.D, h.mult);
+                fits = signed_add_term(dig, lo, L.lsb, L.D, h.mult) && fits;
+              } else {
+                fits = atomic_add_term(dig, hi, L.lsb, L.D, h.mult);
+                fits = atomic_add_term(dig, lo, L.lsb, L.D, h.mult) && fits;
+              }
               if (!fits) bad |= 1u;
             }
           }
-        } while (next_combo(L, h, cur));
+          if (more) more = next_combo(L, h, cur);
+        }
       }
     }
   }
@@ -962,11 +1015,21 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
       for (uint32_t i = tid; i < L.gspace; i += J_NT) {
         const unsigned long long c = s_gcnt[i];
         if (!c) continue;
-        atomic_add_count(&L.gcount[i], c, L.err);
+        int64_t* sl = L.gacc + (uint64_t)i * L.gstride;
+        atomic_add_count((uint64_t*)sl, c, L.err);
         if (L.sum) {
+          // (a block adds digits below 2^32, so signed slots stay in int64)
           RegAcc t;
-          t.load_shared((const int64_t*)&s_gdig[i * EXACT_MAXD], L.D);
-          atomic_add_acc(L.gacc + i * L.D, t, L.D);
+          if (L.gsigned) {
+            t.load_signed((const int64_t*)&s_gdig[i * EXACT_MAXD], L.D);
+#pragma unroll
+            for (int q = 0; q < EXACT_MAXD; q++)
+              if (q < (int)L.D && t.s[q])
+                atomicAdd((unsigned long long*)&sl[1 + q], (unsigned long long)t.s[q]);
+          } else {
+            t.load_shared((const int64_t*)&s_gdig[i * EXACT_MAXD], L.D);
+            atomic_add_acc(sl + 1, t, L.D);
+          }
         }
       }
     }
@@ -1281,14 +1344,6 @@ __device__ __forceinline__ void wave_stage(uint32_t* dst, const uint32_t* src, u
       if (i < m) dst[i] = t[j];
     }
   }
-}
-
-__device__ __forceinline__ void wave_lds_sync() {
-  // LDS operations of one wave complete in order; this keeps the compiler
-  // from moving them across the point where lanes read what others wrote
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Probe path of a unit: the unit's driver keys against the probed set's
@@ -1700,36 +1755,93 @@ __global__ void k_tag_flags(const uint32_t* tag, uint64_t n, uint32_t* flags) {
     flags[i] = tag[i] == SLOT_READY ? 1u : 0u;
 }
 
-__global__ void k_key64_flags(const uint64_t* key, uint64_t n, uint32_t* flags) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-    flags[i] = key[i] != KEY64_EMPTY ? 1u : 0u;
-}
-
-struct UnpackArgs {
+// Entries of a GROUP BY array in use: a dense array's slots with a count, a
+// hash table's words with a key.
+struct DenseUsed {
+  const int64_t* acc;
+  uint32_t stride;
+  __device__ __forceinline__ bool operator()(uint64_t i) const { return acc[i * stride] != 0; }
+};
+struct HashUsed {
   const uint64_t* key;
-  const uint32_t* sid;
-  uint32_t n_cols;
-  uint32_t shift[MAXV + MAXA];
-  uint32_t bits[MAXV + MAXA];
-  uint32_t* out[MAXV + MAXA];
+  __device__ __forceinline__ bool operator()(uint64_t i) const { return key[i] != KEY64_EMPTY; }
 };
 
-__global__ void k_unpack_keys(UnpackArgs a, uint64_t n) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-    const uint64_t k = a.key[a.sid[i]];
-    for (uint32_t c = 0; c < a.n_cols; c++)
-      a.out[c][i] = a.bits[c] ? (uint32_t)((k >> a.shift[c]) & ((1ull << a.bits[c]) - 1)) : 0u;
+constexpr int GU_NT = 256, GU_ITEMS = 8, GU_TILE = GU_NT * GU_ITEMS;
+
+template <class U>
+__global__ __launch_bounds__(GU_NT) void k_used_counts(U used, uint64_t n, uint32_t* cnt) {
+  __shared__ uint32_t s_red[GU_NT / WAVE];
+  const uint64_t base = (uint64_t)blockIdx.x * GU_TILE;
+  uint32_t c = 0;
+#pragma unroll
+  for (int j = 0; j < GU_ITEMS; j++) {
+    const uint64_t i = base + (uint64_t)j * GU_NT + threadIdx.x;
+    c += i < n && used(i);
   }
+  const uint32_t t = block_sum<uint32_t, GU_NT>(c, s_red);
+  if (threadIdx.x == 0) cnt[blockIdx.x] = t;
+}
+
+// Output positions of a tile's entries in use, in index order: at[j] for
+// entry j * GU_NT + threadIdx.x of the tile (mask bit j: in use).
+template <class U>
+__device__ __forceinline__ uint32_t used_ranks(const U& used, uint64_t n, const uint64_t* off, uint64_t* at) {
+  __shared__ uint32_t s_cnt[GU_ITEMS][GU_NT / WAVE];
+  const uint64_t base = (uint64_t)blockIdx.x * GU_TILE;
+  const int w = threadIdx.x / WAVE;
+  uint32_t mask = 0, below[GU_ITEMS];
+#pragma unroll
+  for (int j = 0; j < GU_ITEMS; j++) {
+    const uint64_t i = base + (uint64_t)j * GU_NT + threadIdx.x;
+    const bool u = i < n && used(i);
+    const uint64_t b = ballot(u);
+    below[j] = lanes_below(b);
+    if (u) mask |= 1u << j;
+    if (lane_id() == 0) s_cnt[j][w] = (uint32_t)__popcll(b);
+  }
+  __syncthreads();
+  uint64_t o = off[blockIdx.x];
+#pragma unroll
+  for (int j = 0; j < GU_ITEMS; j++) {
+    uint32_t pre = 0;
+#pragma unroll
+    for (int v = 0; v < GU_NT / WAVE; v++) {
+      const uint32_t c = s_cnt[j][v];
+      if (v < w) pre += c;
+    }
+    at[j] = o + pre + below[j];
+#pragma unroll
+    for (int v = 0; v < GU_NT / WAVE; v++) o += s_cnt[j][v];
+  }
+  return mask;
+}
+
+// The keys in use of a hash table and their slots.
+__global__ __launch_bounds__(GU_NT) void k_compact_keys(const uint64_t* key, uint64_t n, const uint64_t* off,
+                                                        uint64_t* out_key, uint32_t* out_slot) {
+  uint64_t at[GU_ITEMS];
+  const uint32_t mask = used_ranks(HashUsed{key}, n, off, at);
+#pragma unroll
+  for (int j = 0; j < GU_ITEMS; j++)
+    if (mask >> j & 1u) {
+      const uint64_t i = (uint64_t)blockIdx.x * GU_TILE + (uint64_t)j * GU_NT + threadIdx.x;
+      out_key[at[j]] = key[i];
+      out_slot[at[j]] = (uint32_t)i;
+    }
 }
 
 struct GroupFin {
-  const uint64_t* cnt;
-  const int64_t* acc;       // stride D
-  const uint64_t* off;      // dense: exclusive scan of the non-empty flags
-  const uint32_t* sid;      // hash: table slot of each group
-  const uint32_t* perm;     // hash: groups in key order
+  const int64_t* acc;       // per slot: the count, then D digits
+  uint32_t stride, sgn;     // words per slot; signed digits
+  const uint64_t* off;      // dense: output rows before each tile
+  const uint64_t* key;      // hash: packed keys in order, or null:
+  const uint32_t* sid;      //   table slot of each key / of each group
+  const uint32_t* perm;     //   groups in key order
   uint32_t n_cols;
-  const uint32_t* key_in[MAXV + MAXA];  // hash: keys of each group (sid order)
+  const uint32_t* key_in[MAXV + MAXA];  // hash, unpacked keys: of each group (sid order)
+  uint32_t shift[MAXV + MAXA];          // hash, packed keys: where each column lies
+  uint32_t bits[MAXV + MAXA];
   uint64_t radix[MAXV + MAXA];          // dense: mixed radix of the index
   uint32_t* key_out[MAXV + MAXA];
   uint64_t* count_out;
@@ -1739,35 +1851,68 @@ struct GroupFin {
   int32_t lsb;
   uint32_t D;
   uint32_t* err;
+  uint64_t* n_join;         // all counts together (cleared before)
 };
+
+// One output row's count and sum; returns the count.
+__device__ __forceinline__ uint64_t finish_group(const GroupFin& f, uint64_t slot, uint64_t o) {
+  const int64_t* sl = f.acc + slot * f.stride;
+  const uint64_t c = (uint64_t)sl[0];
+  f.count_out[o] = c;
+  if (f.sum) {
+    RegAcc r;
+    if (f.sgn) r.load_signed(sl + 1, f.D);
+    else r.load_shared(sl + 1, f.D);
+    f.sum_out[o] = exact_round(r.s, f.D, f.lsb, f.err);
+    if (f.parts) exact_parts(r.s, f.D, f.lsb, f.parts + o * EXACT_PARTS, f.err);
+  }
+  return c;
+}
+
+__device__ __forceinline__ void add_join_tuples(const GroupFin& f, uint64_t c) {
+  __shared__ uint64_t s_red[GU_NT / WAVE];
+  const uint64_t t = block_sum<uint64_t, GU_NT>(c, s_red);
+  if (threadIdx.x == 0 && t) atomicAdd((unsigned long long*)f.n_join, (unsigned long long)t);
+}
 
 // Dense GROUP BY: a non-empty index becomes the next output row; its keys
 // are the digits of the index, so rows come out in key order.
-__global__ void k_dense_finalize(GroupFin f, uint64_t n) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-    if (f.off[i + 1] == f.off[i]) continue;
-    const uint64_t o = f.off[i];
+__global__ __launch_bounds__(GU_NT) void k_dense_finalize(GroupFin f, uint64_t n) {
+  uint64_t at[GU_ITEMS];
+  const uint32_t mask = used_ranks(DenseUsed{f.acc, f.stride}, n, f.off, at);
+  uint64_t sum = 0;
+#pragma unroll
+  for (int j = 0; j < GU_ITEMS; j++) {
+    if (!(mask >> j & 1u)) continue;
+    const uint64_t i = (uint64_t)blockIdx.x * GU_TILE + (uint64_t)j * GU_NT + threadIdx.x;
     uint64_t idx = i;
     for (int c = (int)f.n_cols - 1; c >= 0; c--) {
-      f.key_out[c][o] = (uint32_t)(idx % f.radix[c]);
+      f.key_out[c][at[j]] = (uint32_t)(idx % f.radix[c]);
       idx /= f.radix[c];
     }
-    f.count_out[o] = f.cnt[i];
-    if (f.sum) f.sum_out[o] = exact_round(f.acc + i * f.D, f.D, f.lsb, f.err);
-    if (f.parts) exact_parts(f.acc + i * f.D, f.D, f.lsb, f.parts + o * EXACT_PARTS, f.err);
+    sum += finish_group(f, i, at[j]);
   }
+  add_join_tuples(f, sum);
 }
 
 // Hash GROUP BY: output row i is the i-th group in key order.
-__global__ void k_hash_finalize(GroupFin f, uint64_t n) {
+__global__ __launch_bounds__(GU_NT) void k_hash_finalize(GroupFin f, uint64_t n) {
+  uint64_t sum = 0;
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) {
-    const uint32_t j = f.perm[i];
-    const uint64_t slot = f.sid[j];
-    for (uint32_t c = 0; c < f.n_cols; c++) f.key_out[c][i] = f.key_in[c][j];
-    f.count_out[i] = f.cnt[slot];
-    if (f.sum) f.sum_out[i] = exact_round(f.acc + slot * f.D, f.D, f.lsb, f.err);
-    if (f.parts) exact_parts(f.acc + slot * f.D, f.D, f.lsb, f.parts + i * EXACT_PARTS, f.err);
+    uint64_t slot;
+    if (f.key) {
+      const uint64_t k = f.key[i];
+      for (uint32_t c = 0; c < f.n_cols; c++)
+        f.key_out[c][i] = f.bits[c] ? (uint32_t)((k >> f.shift[c]) & ((1ull << f.bits[c]) - 1)) : 0u;
+      slot = f.sid[i];
+    } else {
+      const uint32_t j = f.perm[i];
+      for (uint32_t c = 0; c < f.n_cols; c++) f.key_out[c][i] = f.key_in[c][j];
+      slot = f.sid[j];
+    }
+    sum += finish_group(f, slot, i);
   }
+  add_join_tuples(f, sum);
 }
 
 struct FinA {
@@ -2067,35 +2212,48 @@ void step(const lh_plan_t* p, uint32_t d, Frontier& F, hipStream_t s) {
 // fit).
 bool group_in_place(const lh_plan_t* p, const Frontier& F, ElemArgs& a, uint64_t nblk, uint64_t total,
                     uint32_t no, uint32_t n_cols, bool is_sum, uint32_t D, DBuf<uint32_t>& err,
-                    lh_result_impl* res, hipStream_t s) {
+                    lh_result_impl* res, DBuf<uint64_t>& n_join_out, hipStream_t s) {
   uint32_t impl = p->group_impl;
   if (impl == LH_GROUP_SORT >> 4) return false;
   const uint32_t leaf = p->n_attrs - 1;
   LeafArgs& L = a.leaf;
-  // key space: the largest value of every output column
-  std::vector<uint32_t> bits(n_cols);
-  uint64_t space = 1;
+  // key space: the largest value of every output column (the leaf's is the
+  // trie's own, the others are read back together)
+  std::vector<uint32_t> bits(n_cols), top(n_cols, 0);
+  std::vector<const uint32_t*> mcol;
+  std::vector<uint64_t> mn;
+  std::vector<uint32_t> mof;
   for (uint32_t c = 0; c < n_cols; c++) {
-    uint32_t mx = 0;
     if (c < no) {
       const uint32_t attr = p->out_attrs[c];
       if (p->depth_of[attr] == leaf) {
         L.col_src[c] = -1;
         const Participant& P = p->parts[leaf][0];
-        const Level& lv = p->atoms[P.atom].trie->lv[P.level];
-        mx = lv.n ? reduce_max_u32(lv.keys.p, lv.n, s) : 0;
-      } else {
-        L.col_src[c] = (int32_t)c;
-        mx = F.n ? reduce_max_u32(F.outv[c].p, F.n, s) : 0;
+        const lh_trie* T = p->atoms[P.atom].trie;
+        top[c] = T->lv[P.level].n ? T->key_max[P.level] : 0;
+        continue;
       }
+      L.col_src[c] = (int32_t)c;
+      mcol.push_back(F.outv[c].p);
+      mn.push_back(F.n);
     } else {
       L.col_src[c] = -2;
       const lh_group_col& G = p->groups[c - no];
       const lh_trie* T = p->atoms[G.atom].trie;
-      mx = T->n_rows ? reduce_max_u32(T->meta[G.meta_col].p, T->n_rows, s) : 0;
+      mcol.push_back(T->meta[G.meta_col].p);
+      mn.push_back(T->n_rows);
     }
-    L.radix[c] = (uint64_t)mx + 1;
-    bits[c] = bitlen(mx);
+    mof.push_back(c);
+  }
+  if (!mcol.empty()) {
+    std::vector<uint32_t> m(mcol.size());
+    column_maxima(mcol.data(), mn.data(), (uint32_t)mcol.size(), m.data(), s);
+    for (size_t i = 0; i < mof.size(); i++) top[mof[i]] = m[i];
+  }
+  uint64_t space = 1;
+  for (uint32_t c = 0; c < n_cols; c++) {
+    L.radix[c] = (uint64_t)top[c] + 1;
+    bits[c] = bitlen(top[c]);
     space = (space > (1ull << 62) / L.radix[c]) ? (1ull << 62) : space * L.radix[c];
   }
   const uint64_t dense_bytes = 8 + (is_sum ? 8ull * D : 0);
@@ -2105,16 +2263,35 @@ bool group_in_place(const lh_plan_t* p, const Frontier& F, ElemArgs& a, uint64_t
   const uint64_t hash_bytes = 4 + 4ull * n_cols + 8 + (is_sum ? 8ull * D : 0);  // an upper bound
   uint64_t cap = 1024;
   if (impl == 2) {
-    const uint64_t want = 2 * std::min<uint64_t>(space, std::max<uint64_t>(total, 512));
+    // (a power of two: two thirds full at most, by the estimate)
+    const uint64_t keys = std::min<uint64_t>(space, std::max<uint64_t>(total, 512));
+    const uint64_t want = keys + keys / 2;
     while (cap < want) cap <<= 1;
     if (cap > (1ull << 31) || cap * hash_bytes > (16ull << 30)) return false;
   }
-  const uint64_t slots = impl == 3 ? space : cap;
   L.n_cols = n_cols;
   L.gmode = impl == 3 ? 1u : 2u;
   L.glds = (impl == 3 && space <= GLDS_MAX) ? 1u : 0u;
   L.gspace = (uint32_t)std::min<uint64_t>(space, GLDS_MAX);
-  DBuf<uint64_t> cnt;
+  // Tuples that can reach one slot: the leaf's elements times the longest
+  // runs of the atoms whose rows are walked.  Below SIGNED_TERMS the digits
+  // are signed slots, added to without waiting; counts too, when every
+  // tuple counts once.  Ten million tuples into 100,000 of a million dense
+  // slots: the pass took 1.43 ms with carrying adds and as much with plain
+  // ones (44 G adds/s), 0.49 ms with a tuple's words in one request.
+  uint64_t most = total;
+  bool once = true;
+  for (uint32_t e = 0; e < p->atoms.size(); e++) {
+    const PlanAtom& A = p->atoms[e];
+    const uint64_t run = A.bag ? A.trie->max_run : 1;
+    if (L.at[e].expand) most = run && most > UINT64_MAX / run ? UINT64_MAX : most * run;
+    else once = once && run <= 1;
+  }
+  L.gsigned = most < SIGNED_TERMS ? 1u : 0u;
+  L.gplain = L.gsigned && once ? 1u : 0u;
+  L.gpack = L.gplain && is_sum && D <= 7 && !L.glds && !arena_tight() ? 1u : 0u;
+  L.gstride = 1 + (is_sum ? D : 0u);
+  if (L.gpack) L.gstride = L.gstride <= 2 ? 2u : L.gstride <= 4 ? 4u : 8u;
   DBuf<int64_t> acc;
   DBuf<uint32_t> tag;
   std::vector<DBuf<uint32_t>> tkeys;
@@ -2134,11 +2311,8 @@ bool group_in_place(const lh_plan_t* p, const Frontier& F, ElemArgs& a, uint64_t
   }
   for (;;) {
     const uint64_t n = impl == 3 ? space : cap;
-    cnt.alloc(n, s);
-    acc.alloc(is_sum ? n * D : 0, s);
-    LH_HIP(hipMemsetAsync(cnt.p, 0, n * sizeof(uint64_t), s));
-    if (is_sum) LH_HIP(hipMemsetAsync(acc.p, 0, n * D * sizeof(int64_t), s));
-    L.gcount = cnt.p;
+    acc.alloc(n * L.gstride, s);
+    LH_HIP(hipMemsetAsync(acc.p, 0, n * L.gstride * sizeof(int64_t), s));
     L.gacc = acc.p;
     if (impl == 2 && packed) {
       key64.alloc(n, s);
@@ -2187,28 +2361,28 @@ bool group_in_place(const lh_plan_t* p, const Frontier& F, ElemArgs& a, uint64_t
     }
     break;
   }
-  (void)slots;
+  DBuf<uint64_t> n_join(1, s);
+  LH_HIP(hipMemsetAsync(n_join.p, 0, sizeof(uint64_t), s));
   GroupFin f{};
-  f.cnt = cnt.p;
   f.acc = acc.p;
+  f.stride = L.gstride;
+  f.sgn = L.gsigned;
   f.n_cols = n_cols;
   f.sum = is_sum ? 1u : 0u;
   f.lsb = L.lsb;
   f.D = D;
   f.err = err.p;
+  f.n_join = n_join.p;
   uint64_t n_groups = 0;
   lh_result& R = res->pub;
-  if (impl == 3) {
-    DBuf<uint32_t> flags(space, s);
-    DBuf<uint64_t> off(space + 1, s);
-    k_nonzero_flags<<<grid_for(space), 256, 0, s>>>(cnt.p, space, flags.p);
-    LH_HIP(hipGetLastError());
-    n_groups = scan_u32_to_u64(flags.p, off.p, space, s);
+  auto alloc_rows = [&]() {
     res->cols.resize(n_cols);
     for (uint32_t c = 0; c < n_cols; c++) {
       res->cols[c].alloc(n_groups, s);
       f.key_out[c] = res->cols[c].p;
       f.radix[c] = L.radix[c];
+      f.shift[c] = L.gshift[c];
+      f.bits[c] = bits[c];
     }
     res->counts.alloc(n_groups, s);
     if (is_sum) res->sums.alloc(n_groups, s);
@@ -2216,59 +2390,61 @@ bool group_in_place(const lh_plan_t* p, const Frontier& F, ElemArgs& a, uint64_t
     f.count_out = res->counts.p;
     f.sum_out = res->sums.p;
     f.parts = res->parts.p;
-    f.off = off.p;
-    if (n_groups) {
-      k_dense_finalize<<<grid_for(space), 256, 0, s>>>(f, space);
+  };
+  const uint64_t n_ent = impl == 3 ? space : cap;
+  const unsigned tiles = (unsigned)((n_ent + GU_TILE - 1) / GU_TILE);
+  if (impl == 3 || packed) {
+    DBuf<uint32_t> used(tiles, s);
+    DBuf<uint64_t> off(tiles + 1, s);
+    if (impl == 3) k_used_counts<<<tiles, GU_NT, 0, s>>>(DenseUsed{acc.p, L.gstride}, n_ent, used.p);
+    else k_used_counts<<<tiles, GU_NT, 0, s>>>(HashUsed{key64.p}, n_ent, used.p);
+    LH_HIP(hipGetLastError());
+    n_groups = scan_u32_to_u64(used.p, off.p, tiles, s);
+    alloc_rows();
+    if (n_groups && impl == 3) {
+      f.off = off.p;
+      k_dense_finalize<<<tiles, GU_NT, 0, s>>>(f, n_ent);
+      LH_HIP(hipGetLastError());
+    } else if (n_groups) {
+      // the keys in use and their slots, sorted by key
+      DBuf<uint64_t> k0(n_groups, s), k1(n_groups, s);
+      DBuf<uint32_t> v0(n_groups, s), v1(n_groups, s);
+      k_compact_keys<<<tiles, GU_NT, 0, s>>>(key64.p, n_ent, off.p, k0.p, v0.p);
+      LH_HIP(hipGetLastError());
+      uint64_t* const kb[2] = {k0.p, k1.p};
+      uint32_t* const vb[2] = {v0.p, v1.p};
+      const uint32_t at = radix_sort_between(kb, vb, n_groups, key_bits, s);
+      f.key = kb[at];
+      f.sid = vb[at];
+      k_hash_finalize<<<grid_for(n_groups), GU_NT, 0, s>>>(f, n_groups);
       LH_HIP(hipGetLastError());
     }
-    R.group_impl = 3;
   } else {
     DBuf<uint32_t> flags(cap, s), sid(cap, s);
-    if (packed) k_key64_flags<<<grid_for(cap), 256, 0, s>>>(key64.p, cap, flags.p);
-    else k_tag_flags<<<grid_for(cap), 256, 0, s>>>(tag.p, cap, flags.p);
+    k_tag_flags<<<grid_for(cap), 256, 0, s>>>(tag.p, cap, flags.p);
     LH_HIP(hipGetLastError());
     n_groups = select_flagged(flags.p, cap, sid.p, s);
     std::vector<DBuf<uint32_t>> gk(n_cols);
     std::vector<const uint32_t*> gp(n_cols);
-    UnpackArgs ua{};
-    ua.key = key64.p;
-    ua.sid = sid.p;
-    ua.n_cols = n_cols;
     for (uint32_t c = 0; c < n_cols; c++) {
       gk[c].alloc(n_groups, s);
-      if (n_groups && !packed) gather_u32(tkeys[c].p, sid.p, gk[c].p, n_groups, s);
+      if (n_groups) gather_u32(tkeys[c].p, sid.p, gk[c].p, n_groups, s);
       gp[c] = gk[c].p;
       f.key_in[c] = gk[c].p;
-      ua.shift[c] = L.gshift[c];
-      ua.bits[c] = bits[c];
-      ua.out[c] = gk[c].p;
-    }
-    if (n_groups && packed) {
-      k_unpack_keys<<<grid_for(n_groups), 256, 0, s>>>(ua, n_groups);
-      LH_HIP(hipGetLastError());
     }
     DBuf<uint32_t> perm(n_groups, s);
     if (n_groups) lex_sort_perm(gp.data(), bits.data(), n_cols, n_groups, perm.p, s);
-    res->cols.resize(n_cols);
-    for (uint32_t c = 0; c < n_cols; c++) {
-      res->cols[c].alloc(n_groups, s);
-      f.key_out[c] = res->cols[c].p;
-    }
-    res->counts.alloc(n_groups, s);
-    if (is_sum) res->sums.alloc(n_groups, s);
-    if (is_sum && p->want_parts) res->parts.alloc(n_groups * EXACT_PARTS, s);
-    f.count_out = res->counts.p;
-    f.sum_out = res->sums.p;
-    f.parts = res->parts.p;
+    alloc_rows();
     f.sid = sid.p;
     f.perm = perm.p;
     if (n_groups) {
-      k_hash_finalize<<<grid_for(n_groups), 256, 0, s>>>(f, n_groups);
+      k_hash_finalize<<<grid_for(n_groups), GU_NT, 0, s>>>(f, n_groups);
       LH_HIP(hipGetLastError());
     }
-    R.group_impl = 2;
   }
+  R.group_impl = impl;
   R.n_rows = n_groups;
+  n_join_out = std::move(n_join);
   return true;
 }
 
@@ -2455,6 +2631,7 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
   lh_result& R = res->pub;
   R.n_cols = n_cols;
   R.exact = is_sum ? 1u : 0u;
+  DBuf<uint64_t> n_join;  // join tuples (device), when the finalization added them up
 
   if (p->case_prefix) {
     // streamed groups: one accumulator per group of the output prefix
@@ -2592,7 +2769,7 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
       LH_HIP(hipGetLastError());
     }
     R.n_rows = n_out_rows;
-  } else if (!group_in_place(p, F, a, nblk, total, no, n_cols, is_sum, D, err, res.get(), s)) {
+  } else if (!group_in_place(p, F, a, nblk, total, no, n_cols, is_sum, D, err, res.get(), n_join, s)) {
     // materialize leaf tuples keyed by the output columns, sort, reduce
     R.group_impl = 1;
     uint64_t n_emit = 0;
@@ -2716,7 +2893,9 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
   R.counts = res->counts.p;
   R.sums = is_sum ? res->sums.p : nullptr;
   uint64_t nj = 0;
-  if (R.n_rows) {
+  if (n_join.p) {
+    nj = read_scalar(n_join.p, s);
+  } else if (R.n_rows) {
     DBuf<uint64_t> tmp(R.n_rows + 1, s);
     nj = scan_u64(res->counts.p, tmp.p, R.n_rows, s);
   }

@@ -46,6 +46,8 @@ struct Arena {
   size_t cap = 0;
   size_t used = 0;
   size_t peak = 0;
+  bool full = false;    // an allocation did not fit
+  bool tight = false;   // spend no memory for speed (arena_tight)
 };
 struct ArenaScope {
   Arena* prev;
@@ -54,6 +56,9 @@ struct ArenaScope {
 };
 void register_arena_range(void* base, size_t cap);
 bool arena_active();
+// An arena that the faster, larger forms of the temporaries did not fit: the
+// join runs again with the smallest.
+bool arena_tight();
 
 template <class T>
 struct DBuf {  // owning device buffer, freed on the stream it was made on
@@ -157,6 +162,13 @@ void gather_f64(const double* src, const uint32_t* idx, double* dst, uint64_t n,
 // vals (and tvals) may be null: keys only.
 void radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* tkeys, uint32_t* tvals,
                       uint64_t n, uint32_t bits, hipStream_t s, uint32_t lo_bit = 0);
+// The same on all of the keys' bits, the sorted pairs left where the last
+// pass wrote them: k[i], v[i] for the returned i (the input is k[0], v[0]).
+uint32_t radix_sort_between(uint64_t* const k[2], uint32_t* const v[2], uint64_t n, uint32_t bits, hipStream_t s);
+
+// The largest of each of up to MAX_COLS columns, read back together.
+constexpr uint32_t MAX_COLS = 24;
+void column_maxima(const uint32_t* const* cols, const uint64_t* n, uint32_t ncols, uint32_t* out, hipStream_t s);
 
 // What travels with a sort's rows: nothing (bytes 0), the input row of each
 // sorted position (bytes 4, in null), or one column of 4 or 8 bytes (in; it
@@ -225,6 +237,7 @@ struct lh_trie {
   uint32_t level_order[LH_MAX_KEYS];   // input key column of each level
   uint32_t key_bits[LH_MAX_KEYS];      // significant bits per level
   uint32_t key_max[LH_MAX_KEYS];       // largest key per level
+  uint64_t max_run = 1;                // most rows under one last-level node (a set: 1)
   // column statistics (learned order features), computed on first use
   bool col_stats = false;
   uint64_t col_distinct[LH_MAX_KEYS];  // distinct values of each level's column (kept rows)

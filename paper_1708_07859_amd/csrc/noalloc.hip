@@ -53,9 +53,20 @@ uint64_t run_plan_noalloc(const lh_plan_t* p, hipStream_t s, uint64_t max_rows, 
   arena.base = scratch_for_current_device();
   arena.cap = LH_NOALLOC_SCRATCH_BYTES;
   uint64_t n = 0;
+  std::unique_ptr<lh_result_impl> res;
   try {
     ArenaScope scope(arena);
-    std::unique_ptr<lh_result_impl> res(run_plan(p, s));
+    try {
+      res.reset(run_plan(p, s));
+    } catch (const Error& e) {
+      // some temporaries trade memory for speed (padded slots): what fits
+      // without that still runs
+      if (e.status != LH_ERR_OVERFLOW || !arena.full) throw;
+      LH_HIP(hipStreamSynchronize(s));
+      arena.used = 0;
+      arena.tight = true;
+      res.reset(run_plan(p, s));
+    }
     const lh_result& R = res->pub;
     n = R.n_rows;
     if (n > max_rows) {

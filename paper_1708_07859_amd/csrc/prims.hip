@@ -195,6 +195,29 @@ __global__ __launch_bounds__(256) void k_reduce_max_u32(const uint32_t* in, uint
   }
 }
 
+struct MaxCols {
+  const uint32_t* col[MAX_COLS];
+  uint64_t n[MAX_COLS];
+};
+
+// Row y of the grid: the largest of column y, into out[y] (cleared before).
+__global__ __launch_bounds__(256) void k_max_cols(MaxCols a, uint32_t* out) {
+  __shared__ uint32_t s_m[256 / WAVE];
+  const uint32_t* col = a.col[blockIdx.y];
+  const uint64_t n = a.n[blockIdx.y];
+  uint32_t m = 0;
+  for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (uint64_t)gridDim.x * 256) m = max(m, col[i]);
+#pragma unroll
+  for (int d = WAVE / 2; d > 0; d >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, d, WAVE));
+  if (lane_id() == 0) s_m[threadIdx.x / WAVE] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t b = 0;
+    for (int w = 0; w < 256 / WAVE; w++) b = max(b, s_m[w]);
+    if (b) atomicMax(&out[blockIdx.y], b);
+  }
+}
+
 __global__ void k_iota(uint32_t* out, uint64_t n) {
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
     out[i] = (uint32_t)i;
@@ -777,6 +800,28 @@ uint32_t reduce_max_u32(const uint32_t* in, uint64_t n, hipStream_t s) {
   return read_scalar(r.p, s);
 }
 
+void column_maxima(const uint32_t* const* cols, const uint64_t* n, uint32_t ncols, uint32_t* out, hipStream_t s) {
+  if (ncols > MAX_COLS) fail(LH_ERR_UNSUPPORTED, "more than 24 columns");
+  MaxCols a{};
+  uint64_t most = 0;
+  for (uint32_t c = 0; c < ncols; c++) {
+    a.col[c] = cols[c];
+    a.n[c] = n[c];
+    most = std::max(most, n[c]);
+  }
+  for (uint32_t c = 0; c < ncols; c++) out[c] = 0;
+  if (!most) return;
+  struct Maxima {
+    uint32_t v[MAX_COLS];
+  };
+  DBuf<Maxima> m(1, s);
+  LH_HIP(hipMemsetAsync(m.p, 0, sizeof(Maxima), s));
+  k_max_cols<<<dim3(std::min(grid_for((most + 7) / 8), 1024u), ncols), 256, 0, s>>>(a, m.p->v);
+  LH_HIP(hipGetLastError());
+  const Maxima h = read_scalar(m.p, s);
+  for (uint32_t c = 0; c < ncols; c++) out[c] = h.v[c];
+}
+
 uint64_t select_flagged(const uint32_t* flags, uint64_t n, uint32_t* out, hipStream_t s) {
   DBuf<uint64_t> off(n + 1, s);
   uint64_t m = scan_u32_to_u64(flags, off.p, n, s);
@@ -1089,6 +1134,23 @@ void radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* tkeys, uint32_t*
     LH_HIP(hipMemcpyAsync(keys, tkeys, n * sizeof(uint64_t), hipMemcpyDeviceToDevice, s));
     if (vals) LH_HIP(hipMemcpyAsync(vals, tvals, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
   }
+}
+
+uint32_t radix_sort_between(uint64_t* const k[2], uint32_t* const v[2], uint64_t n, uint32_t bits, hipStream_t s) {
+  if (n <= 1 || !bits) return 0;
+  if (n >= (1ull << 32)) fail(LH_ERR_OVERFLOW, "radix sort: more than 2^32 - 1 keys");
+  const uint32_t passes = (bits + 7) / 8;
+  RadixIO io;
+  io.kin = k[0];
+  io.vin = v[0];
+  io.vb = 4;
+  for (int i = 0; i < 2; i++) {
+    io.kbuf[i] = k[i];
+    io.vbuf[i] = v[i];
+  }
+  io.phase = 1;
+  radix_passes(io, n, 0, passes, s);
+  return passes & 1;
 }
 
 void lex_sort_perm(const uint32_t* const* cols, const uint32_t* bits, uint32_t ncols, uint64_t n, uint32_t* perm,

@@ -110,6 +110,7 @@ void register_arena_range(void* base, size_t cap) {
 }
 
 bool arena_active() { return t_arena != nullptr; }
+bool arena_tight() { return t_arena && t_arena->tight; }
 
 ArenaScope::ArenaScope(Arena& a) : prev(t_arena) {
   a.used = 0;
@@ -123,6 +124,7 @@ void* dalloc(size_t bytes, hipStream_t s) {
     Arena& a = *t_arena;
     const size_t off = (a.used + 255) & ~size_t(255);
     if (off > a.cap || bytes > a.cap - off) {
+      a.full = true;
       std::ostringstream os;
       os << "the static scratch of " << (a.cap >> 20) << " MiB cannot hold this join's temporaries (" << bytes
          << " more bytes at offset " << off << ")";

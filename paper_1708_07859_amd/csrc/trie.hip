@@ -297,6 +297,15 @@ __global__ void k_rank_delta(SetRange sr, uint64_t n_sets, const uint64_t* bs_wo
   }
 }
 
+// The longest of n runs given by their offsets, into *out (cleared before).
+__global__ __launch_bounds__(256) void k_max_run(const uint32_t* offs, uint64_t n, uint32_t* out) {
+  uint32_t m = 0;
+  for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (uint64_t)gridDim.x * 256)
+    m = max(m, offs[i + 1] - offs[i]);
+  for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
+  if ((threadIdx.x & 63) == 0 && m > 1) atomicMax(out, m);
+}
+
 unsigned grid_for(uint64_t n) {
   uint64_t b = (n + 255) / 256;
   return (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(b, 256 * 64));
@@ -639,6 +648,13 @@ lh_trie* build_trie(uint64_t n_rows, uint32_t n_keys, const uint32_t* const* key
   if (bag) {
     k_set_u32<<<1, 1, 0, s>>>(t->lv[n_keys - 1].offs.p + n_leaf, (uint32_t)n);
     LH_HIP(hipGetLastError());
+    if (n_leaf < n) {  // some key tuple repeats
+      DBuf<uint32_t> m(1, s);
+      LH_HIP(hipMemsetAsync(m.p, 0, sizeof(uint32_t), s));
+      k_max_run<<<std::min(grid_for(n_leaf), 1024u), 256, 0, s>>>(t->lv[n_keys - 1].offs.p, n_leaf, m.p);
+      LH_HIP(hipGetLastError());
+      t->max_run = read_scalar(m.p, s);
+    }
   }
 
   for (uint32_t l = 0; l < n_keys; l++) {
