@@ -89,7 +89,6 @@ struct DSet {
   const uint32_t* bs_base;
   const uint64_t* pool;
   const uint32_t* bs_rank;   // rank directory of the bitset sets, or null
-  const uint32_t* bs_delta;
   const uint64_t* root_bits; // root sets: level-0 bitmap with a rank per word, or null
   const uint32_t* root_rank;
   uint64_t root_span;
@@ -177,7 +176,7 @@ __device__ __forceinline__ bool dset_find(const DSet& st, uint32_t b, uint32_t e
     if (!((word >> (d & 63u)) & 1ull)) return false;
     if (need_pos) {
       if (st.bs_rank)
-        pos = st.bs_rank[w + (d >> 6)] + (uint32_t)__popcll(word & ((1ull << (d & 63u)) - 1ull)) + st.bs_delta[sidx];
+        pos = st.bs_rank[w + (d >> 6)] + (uint32_t)__popcll(word & ((1ull << (d & 63u)) - 1ull));
       else
         (void)sampled_find(st.keys, st.samp, b, e, x, pos);
     }
@@ -2038,7 +2037,6 @@ DSet make_dset(const lh_plan_t* p, const Participant& pt, const Frontier& F) {
   d.bs_base = L.bs_base.p;
   d.pool = L.pool.p;
   d.bs_rank = L.bs_rank.p;
-  d.bs_delta = L.bs_delta.p;
   if (pt.level == 0) {
     d.root_n = (uint32_t)t->lv[0].n;
     d.root_bits = t->root_bits.p;

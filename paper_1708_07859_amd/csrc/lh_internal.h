@@ -128,6 +128,26 @@ T read_scalar(const T* dptr, hipStream_t s) {
   return *h;
 }
 
+// A few words that a kernel stores for the host: p() is where (pinned memory,
+// or a device buffer where none may be had), get() waits and reads.  One at a
+// time per thread.
+template <class T>
+struct HostOut {
+  static_assert(sizeof(T) <= PINNED_BYTES, "HostOut: at most PINNED_BYTES");
+  hipStream_t s;
+  T* host;
+  DBuf<T> dev;
+  explicit HostOut(hipStream_t st) : s(st), host(static_cast<T*>(pinned_scratch_or_null())) {
+    if (!host) dev.alloc(1, s);
+  }
+  T* p() const { return host ? host : dev.p; }
+  T get() const {
+    if (!host) return read_scalar(dev.p, s);
+    LH_HIP(hipStreamSynchronize(s));
+    return *host;
+  }
+};
+
 // ---------------------------------------------------------------------------
 // Primitives (prims.hip)
 // ---------------------------------------------------------------------------
@@ -139,6 +159,7 @@ uint64_t scan_u64(const uint64_t* in, uint64_t* out, uint64_t n, hipStream_t s);
 uint32_t scan_u32(const uint32_t* in, uint32_t* out, uint64_t n, hipStream_t s);
 // The same without reading the total back (it stays in out[n]).
 void scan_u32_dev(const uint32_t* in, uint32_t* out, uint64_t n, hipStream_t s);
+void scan_u32_to_u64_dev(const uint32_t* in, uint64_t* out, uint64_t n, hipStream_t s);
 uint32_t reduce_max_u32(const uint32_t* in, uint64_t n, hipStream_t s);
 // Raise *out (device, set beforehand) to the largest of in[0, n); nothing is read back.
 void max_u32_into(const uint32_t* in, uint64_t n, uint32_t* out, hipStream_t s);
@@ -200,6 +221,15 @@ struct AnnoStats {
   uint32_t nonfinite;
 };
 AnnoStats anno_stats(const double* v, uint64_t n, hipStream_t s);
+// The same accumulated on the device into *acc (cleared before), decoded on
+// the host later.
+struct AnnoAcc {
+  unsigned long long maxabs;  // bits of the largest |v|
+  uint32_t qenc;              // INT32_MAX - qmin
+  uint32_t nonfinite;
+};
+void anno_stats_into(const double* v, uint64_t n, AnnoAcc* acc, hipStream_t s);
+AnnoStats decode_anno_stats(const AnnoAcc& a);
 
 // ---------------------------------------------------------------------------
 // Tries (trie.hip)
@@ -207,6 +237,11 @@ AnnoStats anno_stats(const double* v, uint64_t n, hipStream_t s);
 // A level's keys carry one sample per 2^LINE_SHIFT keys (one 128-byte
 // line): samp[j] = keys[j << LINE_SHIFT].
 constexpr uint32_t LINE_SHIFT = 5;
+
+template <class T>
+struct View {  // part of a buffer owned elsewhere
+  T* p = nullptr;
+};
 
 struct Level {
   uint64_t n = 0;            // nodes
@@ -216,14 +251,11 @@ struct Level {
   uint64_t n_sets = 0;       // sets at this level (1 at level 0, else nodes of level-1)
   DBuf<uint64_t> bs_word;    // n_sets: first word in pool, UINT64_MAX = uint layout
   DBuf<uint32_t> bs_base;    // n_sets: value of bit 0 (multiple of 64)
-  DBuf<uint64_t> pool;       // bitset words
+  View<uint64_t> pool;       // bitset words (in the trie's words)
   uint64_t pool_words = 0;
-  // rank directory of the bitset sets (levels whose positions are used):
-  // bs_rank[w] = set bits in the pool before word w, bs_delta[s] = first
-  // position of set s minus bs_rank of its first word (mod 2^32)
-  DBuf<uint32_t> bs_rank;    // pool_words + 1, or empty
-  DBuf<uint32_t> bs_delta;   // n_sets, or empty
-  uint64_t n_bitsets = 0;
+  // rank directory of the bitset sets (levels whose positions are used, else
+  // null): for a word holding a key, its first key's position in the level
+  View<uint32_t> bs_rank;
 };
 
 }  // namespace lh
@@ -247,8 +279,11 @@ struct lh_trie {
   // per 64-bit word, when the span is small next to the keys (membership
   // and position in one load each, whatever level 0's layout)
   uint64_t root_span = 0;
-  lh::DBuf<uint64_t> root_bits;
-  lh::DBuf<uint32_t> root_rank;
+  lh::View<uint64_t> root_bits;
+  lh::View<uint32_t> root_rank;
+  // the bitset words of all levels and the root index, and a rank per word
+  lh::DBuf<uint64_t> words;
+  lh::DBuf<uint32_t> ranks;
   // two-level tries whose column statistics were taken: the rows sorted by
   // (level 1, level 0), as level-1 and level-0 keys
   lh::DBuf<uint32_t> tsorted[2];
@@ -290,9 +325,6 @@ void ensure_column_stats(lh_trie* t, hipStream_t s);
 
 // Sets of level l stored as bitsets (a device count).
 uint64_t count_bitsets(const lh_trie* t, uint32_t l, hipStream_t s);
-
-// Per-set layout and bitset materialization for one level.
-void build_layouts(lh_trie* t, uint32_t level, uint32_t layout_flags, const uint32_t* parent, hipStream_t s);
 
 // Per-set layout choices from the registered learned layout model (0 plain
 // rule, 1 uint, 2 bitset); false when no model is registered.

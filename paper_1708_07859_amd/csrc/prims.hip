@@ -729,7 +729,7 @@ __device__ __forceinline__ int32_t lowest_bit_exp(double v) {
   return (int32_t)ex - 1075 + (int32_t)__builtin_ctzll(mant);
 }
 
-__global__ void k_anno_stats(const double* v, uint64_t n, int32_t* qmin, unsigned long long* maxabs, uint32_t* nonfinite) {
+__global__ void k_anno_stats(const double* v, uint64_t n, AnnoAcc* acc) {
   int32_t q = INT_MAX;
   uint64_t m = 0;
   uint32_t bad = 0;
@@ -765,10 +765,12 @@ __global__ void k_anno_stats(const double* v, uint64_t n, int32_t* qmin, unsigne
       m = max(m, (uint64_t)s_m[j]);
       bad |= s_b[j];
     }
-    if (q < __hip_atomic_load(qmin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(qmin, q);
-    if (m > __hip_atomic_load(maxabs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      atomicMax(maxabs, (unsigned long long)m);
-    if (bad && !__hip_atomic_load(nonfinite, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicOr(nonfinite, 1u);
+    const uint32_t qe = (uint32_t)(INT_MAX - (int64_t)q);
+    if (qe > __hip_atomic_load(&acc->qenc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&acc->qenc, qe);
+    if (m > __hip_atomic_load(&acc->maxabs, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(&acc->maxabs, (unsigned long long)m);
+    if (bad && !__hip_atomic_load(&acc->nonfinite, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicOr(&acc->nonfinite, 1u);
   }
 }
 
@@ -785,6 +787,9 @@ uint32_t scan_u32(const uint32_t* in, uint32_t* out, uint64_t n, hipStream_t s) 
 }
 void scan_u32_dev(const uint32_t* in, uint32_t* out, uint64_t n, hipStream_t s) {
   scan_dev<uint32_t, uint32_t>(in, out, n, s);
+}
+void scan_u32_to_u64_dev(const uint32_t* in, uint64_t* out, uint64_t n, hipStream_t s) {
+  scan_dev<uint32_t, uint64_t>(in, out, n, s);
 }
 
 void max_u32_into(const uint32_t* in, uint64_t n, uint32_t* out, hipStream_t s) {
@@ -1236,26 +1241,25 @@ bool sort_packed(const uint32_t* const* cols, const uint32_t* bits, uint32_t nco
   return true;
 }
 
-AnnoStats anno_stats(const double* v, uint64_t n, hipStream_t s) {
-  DBuf<int32_t> q(1, s);
-  DBuf<unsigned long long> m(1, s);
-  DBuf<uint32_t> bad(1, s);
-  k_fill<int32_t><<<1, 64, 0, s>>>(q.p, INT_MAX, 1);
+void anno_stats_into(const double* v, uint64_t n, AnnoAcc* acc, hipStream_t s) {
+  if (!n) return;
+  k_anno_stats<<<std::min(grid_for((n + 3) / 4), 4096u), 256, 0, s>>>(v, n, acc);
   LH_HIP(hipGetLastError());
-  LH_HIP(hipMemsetAsync(m.p, 0, sizeof(unsigned long long), s));
-  LH_HIP(hipMemsetAsync(bad.p, 0, sizeof(uint32_t), s));
-  if (n) {
-    k_anno_stats<<<grid_for(n), 256, 0, s>>>(v, n, q.p, m.p, bad.p);
-    LH_HIP(hipGetLastError());
-  }
+}
+
+AnnoStats decode_anno_stats(const AnnoAcc& a) {
   AnnoStats st;
-  st.qmin = read_scalar(q.p, s);
-  unsigned long long mb = read_scalar(m.p, s);
-  double md;
-  memcpy(&md, &mb, sizeof md);
-  st.maxabs = md;
-  st.nonfinite = read_scalar(bad.p, s);
+  st.qmin = (int32_t)((int64_t)INT_MAX - (int64_t)a.qenc);
+  memcpy(&st.maxabs, &a.maxabs, sizeof st.maxabs);
+  st.nonfinite = a.nonfinite;
   return st;
+}
+
+AnnoStats anno_stats(const double* v, uint64_t n, hipStream_t s) {
+  DBuf<AnnoAcc> acc(1, s);
+  LH_HIP(hipMemsetAsync(acc.p, 0, sizeof(AnnoAcc), s));
+  anno_stats_into(v, n, acc.p, s);
+  return decode_anno_stats(read_scalar(acc.p, s));
 }
 
 }  // namespace lh

@@ -65,7 +65,10 @@ struct EmitArgs {
   uint32_t* kept_out;                // set: sorted-row index of each kept row; may be null
   uint32_t* rowkeys_out[LH_MAX_KEYS]; // set: each kept row's keys of the levels above the last; null when not wanted
   uint32_t* parent_out[LH_MAX_KEYS]; // level l >= 1: the level l-1 node above each node; may be null
-  const uint32_t* tile_off;          // [l * ntiles + tile]
+  uint32_t* samp_out[LH_MAX_KEYS];   // line samples of each level
+  const uint32_t* tile_off;          // [l * ntiles + tile]: one scan over all levels' counts
+  uint32_t level_base[LH_MAX_KEYS];  // tile_off of the level's first tile
+  uint32_t level_n[LH_MAX_KEYS];     // nodes per level
   uint32_t ntiles;
 };
 
@@ -93,14 +96,16 @@ __global__ __launch_bounds__(TB_NT) void k_emit_levels(EmitArgs a, uint64_t n) {
     if (l >= L || !((m >> l) & 1u)) continue;
     uint32_t pre = 0;
     for (int j = 0; j < w; j++) pre += w_cnt[j][l];
-    uint32_t pos = a.tile_off[(uint64_t)l * a.ntiles + blockIdx.x] + pre + rank[l];
-    a.keys_out[l][pos] = a.c.k[l][r];
+    uint32_t pos = a.tile_off[(uint64_t)l * a.ntiles + blockIdx.x] - a.level_base[l] + pre + rank[l];
+    const uint32_t key = a.c.k[l][r];
+    a.keys_out[l][pos] = key;
+    if (!(pos & ((1u << LINE_SHIFT) - 1))) a.samp_out[l][pos >> LINE_SHIFT] = key;
     if (l > 0 && a.parent_out[l]) {
       // the parent is the last level l-1 node starting at or before row r
       uint32_t pp = 0;
       for (int j = 0; j < w; j++) pp += w_cnt[j][l - 1];
-      a.parent_out[l][pos] = a.tile_off[(uint64_t)(l - 1) * a.ntiles + blockIdx.x] + pp + rank[l - 1] +
-                             ((m >> (l - 1)) & 1u) - 1u;
+      a.parent_out[l][pos] = a.tile_off[(uint64_t)(l - 1) * a.ntiles + blockIdx.x] - a.level_base[l - 1] + pp +
+                             rank[l - 1] + ((m >> (l - 1)) & 1u) - 1u;
     }
     // a head at level l-1 is also a head at l: its first child is pos
     if (l > 0 && ((m >> (l - 1)) & 1u)) a.offs_out[l - 1][pos_prev] = pos;
@@ -113,68 +118,116 @@ __global__ __launch_bounds__(TB_NT) void k_emit_levels(EmitArgs a, uint64_t n) {
     }
     pos_prev = pos;
   }
+  if (r + 1 == n) {  // closing offsets
+#pragma unroll
+    for (uint32_t l = 0; l + 1 < LH_MAX_KEYS; l++)
+      if (l + 1 < L) a.offs_out[l][a.level_n[l]] = a.level_n[l + 1];
+#pragma unroll
+    for (uint32_t l = 0; l < LH_MAX_KEYS; l++)
+      if (l + 1 == L && a.run_out) a.run_out[a.level_n[l]] = (uint32_t)n;
+  }
+}
+
+// Nodes of each level, from the scan of all levels' tile counts.
+__global__ void k_level_totals(const uint32_t* tile_off, uint32_t ntiles, uint32_t n_levels, uint32_t* out) {
+  const uint32_t l = threadIdx.x;
+  if (l < n_levels) out[l] = tile_off[(uint64_t)(l + 1) * ntiles] - tile_off[(uint64_t)l * ntiles];
 }
 
 __global__ void k_set_u32(uint32_t* p, uint32_t v) { *p = v; }
 
-// Bit t-1 of a block's mask stays set while rows i-1, i are in
-// lexicographic order of the last t levels (equal tuples are in order),
-// for every i the block visits.  Bits only clear, and a wave stops once
-// none is left, so unsorted input costs a fraction of a pass.  Each block
-// writes its mask (atomics of every block on one address would serialize);
-// k_and_total combines them.
-__global__ __launch_bounds__(256) void k_sorted_tails(LevelCols c, uint64_t n, uint32_t all, uint32_t* part) {
-  __shared__ uint32_t s_m[256 / WAVE];
-  const int K = (int)c.n_levels;
-  uint32_t known = all;
-  const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t i0 = 1 + (uint64_t)blockIdx.x * blockDim.x; i0 < n && known; i0 += stride) {
-    const uint64_t i = i0 + threadIdx.x;
-    const int lane = threadIdx.x & 63;
-    uint32_t m = known;
-    bool ord = true;  // order of the suffix from level l on
-    // constant level indices: the column pointers stay in registers; each
-    // lane loads its row once and takes row i - 1 from the lane below
+// What the build needs to know of its input: every level's largest key and,
+// when asked, how much of it is in order (bit t-1 of the mask stays set while
+// rows i-1, i are in lexicographic order of the last t levels, for every i;
+// equal tuples are in order).
+struct InputStats {
+  uint32_t key_max[LH_MAX_KEYS];
+  uint32_t tail_mask;
+};
+
+// One pass over the columns, four rows in flight per thread; each lane takes
+// row i - 1 from the lane below.  A wave that has seen every order broken
+// compares no more.  Each block writes its result (atomics of every block on
+// one address would serialize); k_input_total combines them.
+template <bool TAIL>
+__global__ __launch_bounds__(256) void k_input_stats(LevelCols c, uint64_t n, uint32_t all, InputStats* part) {
+  constexpr int R = 4;
+  __shared__ InputStats s_st[256 / WAVE];
+  const int K = (int)c.n_levels, lane = lane_id();
+  uint32_t mx[LH_MAX_KEYS], known = all;
+#pragma unroll
+  for (int l = 0; l < LH_MAX_KEYS; l++) mx[l] = 0;
+  const uint64_t stride = (uint64_t)gridDim.x * 256 * R;
+  for (uint64_t i0 = (uint64_t)blockIdx.x * 256 * R; i0 < n; i0 += stride) {
+    const bool check = TAIL && __any(known != 0);
+    uint32_t m[R];
+    bool ord[R];
+#pragma unroll
+    for (int j = 0; j < R; j++) {
+      m[j] = all;
+      ord[j] = true;  // order of the suffix from level l on
+    }
+    // constant level indices: the column pointers stay in registers
 #pragma unroll
     for (int l = LH_MAX_KEYS - 1; l >= 0; l--) {
-      if (l < K) {
-        const uint32_t b = i < n ? c.k[l][i] : 0u;
-        uint32_t a = (uint32_t)__shfl_up((int)b, 1, 64);
-        if (lane == 0 && i < n) a = c.k[l][i - 1];
-        ord = a < b || (a == b && ord);
-        if (i < n && !ord) m &= ~(1u << (K - 1 - l));
+      if (l >= K) continue;
+      uint32_t b[R];
+#pragma unroll
+      for (int j = 0; j < R; j++) {
+        const uint64_t i = i0 + (uint64_t)j * 256 + threadIdx.x;
+        b[j] = i < n ? c.k[l][i] : 0u;
+        mx[l] = max(mx[l], b[j]);
+      }
+      if (!check) continue;
+#pragma unroll
+      for (int j = 0; j < R; j++) {
+        const uint64_t i = i0 + (uint64_t)j * 256 + threadIdx.x;
+        uint32_t a = (uint32_t)__shfl_up((int)b[j], 1, 64);
+        if (lane == 0 && i > 0 && i < n) a = c.k[l][i - 1];
+        if (i == 0 || i >= n) continue;
+        ord[j] = a < b[j] || (a == b[j] && ord[j]);
+        if (!ord[j]) m[j] &= ~(1u << (K - 1 - l));
       }
     }
-    for (int o = 32; o > 0; o >>= 1) m &= (uint32_t)__shfl_xor((int)m, o, 64);
-    known = m;  // uniform over the wave
+#pragma unroll
+    for (int j = 0; j < R; j++) known &= m[j];
   }
-  if ((threadIdx.x & 63) == 0) s_m[threadIdx.x / WAVE] = known;
+#pragma unroll
+  for (int l = 0; l < LH_MAX_KEYS; l++) {
+    if (l >= K) continue;
+    for (int o = 32; o > 0; o >>= 1) mx[l] = max(mx[l], (uint32_t)__shfl_xor((int)mx[l], o, 64));
+    if (lane == 0) s_st[threadIdx.x / WAVE].key_max[l] = mx[l];
+  }
+  for (int o = 32; o > 0; o >>= 1) known &= (uint32_t)__shfl_xor((int)known, o, 64);
+  if (lane == 0) s_st[threadIdx.x / WAVE].tail_mask = known;
   __syncthreads();
+  if ((int)threadIdx.x < K) {
+    uint32_t v = 0;
+    for (int w = 0; w < 256 / WAVE; w++) v = max(v, s_st[w].key_max[threadIdx.x]);
+    part[blockIdx.x].key_max[threadIdx.x] = v;
+  }
   if (threadIdx.x == 0) {
-    uint32_t m = all;
-    for (int w = 0; w < 256 / WAVE; w++) m &= s_m[w];
-    part[blockIdx.x] = m;
+    uint32_t v = all;
+    for (int w = 0; w < 256 / WAVE; w++) v &= s_st[w].tail_mask;
+    part[blockIdx.x].tail_mask = v;
   }
 }
 
-// AND of the blocks' masks, by one block.
-__global__ __launch_bounds__(256) void k_and_total(const uint32_t* part, uint32_t nb, uint32_t all, uint32_t* out) {
-  __shared__ uint32_t s_m[256 / WAVE];
-  uint32_t m = all;
-  for (uint32_t b = threadIdx.x; b < nb; b += blockDim.x) m &= part[b];
-  for (int o = 32; o > 0; o >>= 1) m &= (uint32_t)__shfl_xor((int)m, o, 64);
-  if ((threadIdx.x & 63) == 0) s_m[threadIdx.x / WAVE] = m;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t r = all;
-    for (int w = 0; w < 256 / WAVE; w++) r &= s_m[w];
-    *out = r;
+// The blocks' results combined by one block: thread group l takes level l.
+__global__ __launch_bounds__(576) void k_input_total(const InputStats* part, uint32_t nb, uint32_t n_levels,
+                                                     uint32_t all, InputStats* out) {
+  const uint32_t l = threadIdx.x / WAVE;  // wave 8: the mask
+  if (l < LH_MAX_KEYS) {
+    uint32_t v = 0;
+    for (uint32_t b = lane_id(); l < n_levels && b < nb; b += WAVE) v = max(v, part[b].key_max[l]);
+    for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o, 64));
+    if (lane_id() == 0) out->key_max[l] = v;
+  } else {
+    uint32_t v = all;
+    for (uint32_t b = lane_id(); b < nb; b += WAVE) v &= part[b].tail_mask;
+    for (int o = 32; o > 0; o >>= 1) v &= (uint32_t)__shfl_xor((int)v, o, 64);
+    if (lane_id() == 0) out->tail_mask = v;
   }
-}
-
-__global__ void k_line_samples(const uint32_t* keys, uint64_t n_samp, uint32_t* samp) {
-  for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n_samp; j += (uint64_t)gridDim.x * blockDim.x)
-    samp[j] = keys[j << LINE_SHIFT];
 }
 
 // ---- layouts ---------------------------------------------------------------
@@ -189,12 +242,32 @@ __device__ __forceinline__ void set_range(const SetRange& sr, uint64_t s, uint32
   else { b = sr.offs[s]; e = sr.offs[s + 1]; }
 }
 
-__global__ void k_layout_words(SetRange sr, const uint32_t* keys, uint64_t n_sets, uint32_t mode,
-                               const uint8_t* choice, uint64_t* words) {
-  for (uint64_t s = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; s < n_sets; s += (uint64_t)gridDim.x * blockDim.x) {
+// All levels' sets, numbered one level after another.
+struct LayoutSets {
+  SetRange sr[LH_MAX_KEYS];
+  const uint32_t* keys[LH_MAX_KEYS];
+  const uint8_t* choice[LH_MAX_KEYS];  // learned choices, or null
+  uint64_t first[LH_MAX_KEYS + 1];     // number of each level's first set
+  uint64_t* bs_word[LH_MAX_KEYS];
+  uint32_t* bs_base[LH_MAX_KEYS];
+  uint32_t n_levels;
+};
+
+// Set i of all: its level's entry of an array indexed by level.
+#define LH_LEVEL_OF(sets, i, l)                       \
+  uint32_t l = 0;                                     \
+  _Pragma("unroll") for (uint32_t q = 1; q < LH_MAX_KEYS; q++) \
+    if (q < (sets).n_levels && (i) >= (sets).first[q]) l = q
+
+// Words of each set's bitset (0: a sorted array).
+__global__ void k_layout_words(LayoutSets ls, uint64_t total, uint32_t mode, uint32_t* words) {
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (uint64_t)gridDim.x * blockDim.x) {
+    LH_LEVEL_OF(ls, i, l);
+    const uint64_t s = i - ls.first[l];
+    const uint32_t* keys = ls.keys[l];
     uint32_t b, e;
-    set_range(sr, s, b, e);
-    uint64_t nw = 0;
+    set_range(ls.sr[l], s, b, e);
+    uint32_t nw = 0;
     if (e > b) {
       uint32_t lo = keys[b], hi = keys[e - 1];
       uint64_t card = e - b;
@@ -203,22 +276,30 @@ __global__ void k_layout_words(SetRange sr, const uint32_t* keys, uint64_t n_set
       // plain rule: a bitset when the set fills at least 1/32 of its window
       if (mode == LH_LAYOUT_PLAIN || mode == LH_LAYOUT_LEARNED) bs = span <= 32ull * card;
       else if (mode == LH_LAYOUT_BITSET) bs = span <= 4096ull * card;
-      if (choice && choice[s]) bs = choice[s] == 2;
-      if (bs) nw = (((uint64_t)hi - (lo & ~63u)) >> 6) + 1;
+      if (ls.choice[l] && ls.choice[l][s]) bs = ls.choice[l][s] == 2;
+      if (bs) nw = ((hi - (lo & ~63u)) >> 6) + 1;
     }
-    words[s] = nw;
+    words[i] = nw;
   }
 }
 
-__global__ void k_layout_desc(SetRange sr, const uint32_t* keys, uint64_t n_sets, const uint64_t* words,
-                              const uint64_t* woff, uint64_t* bs_word, uint32_t* bs_base) {
-  for (uint64_t s = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; s < n_sets; s += (uint64_t)gridDim.x * blockDim.x) {
+// Null words: every set a sorted array.
+__global__ void k_layout_desc(LayoutSets ls, uint64_t total, const uint32_t* words, const uint64_t* woff) {
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (uint64_t)gridDim.x * blockDim.x) {
+    LH_LEVEL_OF(ls, i, l);
+    const uint64_t s = i - ls.first[l];
     uint32_t b, e;
-    set_range(sr, s, b, e);
-    bool bs = words[s] != 0;
-    bs_word[s] = bs ? woff[s] : UINT64_MAX;
-    bs_base[s] = (e > b) ? (keys[b] & ~63u) : 0u;
+    set_range(ls.sr[l], s, b, e);
+    const bool bs = words && words[i] != 0;
+    ls.bs_word[l][s] = bs ? woff[i] - woff[ls.first[l]] : UINT64_MAX;
+    ls.bs_base[l][s] = (e > b) ? (ls.keys[l][b] & ~63u) : 0u;
   }
+}
+
+// Bitset words before each level's first, and all of them.
+__global__ void k_layout_totals(LayoutSets ls, const uint64_t* woff, uint64_t* out) {
+  const uint32_t l = threadIdx.x;
+  if (l <= ls.n_levels) out[l] = woff[ls.first[l]];
 }
 
 // Bitset words from the keys.  A wave takes 64 consecutive keys; the keys
@@ -231,9 +312,13 @@ __global__ void k_layout_desc(SetRange sr, const uint32_t* keys, uint64_t n_sets
 // is in the same word) ORs its part atomically into the word (the pool
 // starts zeroed); words without keys stay zero.  Waves without a bitset key do no
 // lane exchange at all.  Null bs_word: the keys form one set whose window
-// starts at 0 at word 0 (the root index).
+// starts at 0 at word 0 (the root index).  rank (null: not wanted) gets, for
+// every word with a key, the position of its first key in the level: a
+// position inside a bitset is then one load and a popcount, and nothing has
+// to be counted or scanned for it.
 __global__ __launch_bounds__(256) void k_layout_fill(const uint32_t* keys, const uint32_t* parent, uint64_t n,
-                                                     const uint64_t* bs_word, const uint32_t* bs_base, uint64_t* pool) {
+                                                     const uint64_t* bs_word, const uint32_t* bs_base, uint64_t* pool,
+                                                     uint32_t* rank) {
   const int lane = threadIdx.x & 63;
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t j0 = (uint64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63u); j0 < n; j0 += stride) {
@@ -274,26 +359,12 @@ __global__ __launch_bounds__(256) void k_layout_fill(const uint32_t* keys, const
       bool shared = false;
       if (lane == 0 && j > 0)
         shared = (parent ? parent[j - 1] : 0u) == st && ((keys[j - 1] - base) >> 6) == word;
+      if (rank && !shared) rank[w] = (uint32_t)j;
       if (end == (uint32_t)WAVE && j0 + WAVE < n)
         shared = shared || ((parent ? parent[j0 + WAVE] : 0u) == st && ((keys[j0 + WAVE] - base) >> 6) == word);
       if (shared) atomicOr((unsigned long long*)&pool[w], (unsigned long long)bits);
       else pool[w] = bits;
     }
-  }
-}
-
-__global__ void k_word_popc(const uint64_t* pool, uint64_t n, uint32_t* cnt) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-    cnt[i] = (uint32_t)__popcll(pool[i]);
-}
-
-__global__ void k_rank_delta(SetRange sr, uint64_t n_sets, const uint64_t* bs_word, const uint32_t* rank,
-                             uint32_t* delta) {
-  for (uint64_t s = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; s < n_sets; s += (uint64_t)gridDim.x * blockDim.x) {
-    uint32_t b, e;
-    set_range(sr, s, b, e);
-    const uint64_t w = bs_word[s];
-    delta[s] = w != UINT64_MAX ? b - rank[w] : 0u;
   }
 }
 
@@ -333,41 +404,77 @@ uint64_t count_bitsets(const lh_trie* t, uint32_t l, hipStream_t s) {
   return read_scalar(c.p, s);
 }
 
-void build_layouts(lh_trie* t, uint32_t l, uint32_t mode, const uint32_t* parent, hipStream_t s) {
-  Level& L = t->lv[l];
-  L.n_sets = (l == 0) ? 1 : t->lv[l - 1].n;
-  SetRange sr{l == 0 ? nullptr : t->lv[l - 1].offs.p, t->lv[0].n};
-  L.bs_word.alloc(L.n_sets, s);
-  L.bs_base.alloc(L.n_sets, s);
-  if (L.n_sets == 0) return;
-  DBuf<uint64_t> words(L.n_sets, s), woff(L.n_sets + 1, s);
-  DBuf<uint8_t> choice;
-  const bool learned = mode == LH_LAYOUT_LEARNED && learned_layout_choices(t, l, s, choice);
-  k_layout_words<<<grid_for(L.n_sets), 256, 0, s>>>(sr, L.keys.p, L.n_sets, mode, learned ? choice.p : nullptr,
-                                                    words.p);
-  LH_HIP(hipGetLastError());
-  L.pool_words = scan_u64(words.p, woff.p, L.n_sets, s);
-  k_layout_desc<<<grid_for(L.n_sets), 256, 0, s>>>(sr, L.keys.p, L.n_sets, words.p, woff.p, L.bs_word.p, L.bs_base.p);
-  LH_HIP(hipGetLastError());
-  L.n_bitsets = 0;
-  if (L.pool_words) {
-    L.pool.alloc(L.pool_words, s);
-    ProfScope ps("layout_fill", s, L.n_sets, L.pool_words);
-    LH_HIP(hipMemsetAsync(L.pool.p, 0, L.pool_words * sizeof(uint64_t), s));
-    k_layout_fill<<<grid_for(L.n), 256, 0, s>>>(L.keys.p, parent, L.n, L.bs_word.p, L.bs_base.p, L.pool.p);
+// Per-set layouts of every level, their bitsets and the root index: sized
+// together (one round trip), cleared together, filled level by level.
+static void build_layouts(lh_trie* t, uint32_t mode, const std::vector<DBuf<uint32_t>>& parent, hipStream_t s) {
+  const uint32_t nl = t->n_levels;
+  LayoutSets ls{};
+  ls.n_levels = nl;
+  std::vector<DBuf<uint8_t>> choice(nl);
+  bool any = false;
+  for (uint32_t l = 0; l < nl; l++) {
+    Level& L = t->lv[l];
+    L.n_sets = (l == 0) ? 1 : t->lv[l - 1].n;
+    L.bs_word.alloc(L.n_sets, s);
+    L.bs_base.alloc(L.n_sets, s);
+    ls.sr[l] = SetRange{l == 0 ? nullptr : t->lv[l - 1].offs.p, t->lv[0].n};
+    ls.keys[l] = L.keys.p;
+    ls.bs_word[l] = L.bs_word.p;
+    ls.bs_base[l] = L.bs_base.p;
+    ls.first[l + 1] = ls.first[l] + L.n_sets;
+    if (mode == LH_LAYOUT_LEARNED && L.n_sets && learned_layout_choices(t, l, s, choice[l])) ls.choice[l] = choice[l].p;
+  }
+  const uint64_t total = ls.first[nl];
+  uint64_t base[LH_MAX_KEYS + 1] = {};
+  DBuf<uint32_t> words;
+  DBuf<uint64_t> woff;
+  if (mode != LH_LAYOUT_UINT && total) {
+    words.alloc(total, s);
+    woff.alloc(total + 1, s);
+    k_layout_words<<<grid_for(total), 256, 0, s>>>(ls, total, mode, words.p);
+    LH_HIP(hipGetLastError());
+    scan_u32_to_u64_dev(words.p, woff.p, total, s);
+    struct Bounds {
+      uint64_t v[LH_MAX_KEYS + 1];
+    };
+    HostOut<Bounds> out(s);
+    k_layout_totals<<<1, WAVE, 0, s>>>(ls, woff.p, out.p()->v);
+    LH_HIP(hipGetLastError());
+    const Bounds h = out.get();
+    for (uint32_t l = 0; l <= nl; l++) base[l] = h.v[l];
+  }
+  if (total) {
+    k_layout_desc<<<grid_for(total), 256, 0, s>>>(ls, total, base[nl] ? words.p : nullptr, woff.p);
     LH_HIP(hipGetLastError());
   }
-  // positions inside bitset sets are needed when a deeper level hangs below
-  // or the rows of a bag are reached through them: a rank directory turns
-  // them into one load and a popcount
-  if (L.pool_words && (l + 1 < t->n_levels || (t->flags & LH_BAG))) {
-    DBuf<uint32_t> pc(L.pool_words, s);
-    k_word_popc<<<grid_for(L.pool_words), 256, 0, s>>>(L.pool.p, L.pool_words, pc.p);
+  // root index, when level 0 holds at least one key per 64 of its span
+  const uint64_t n0 = t->lv[0].n;
+  const uint64_t span = (uint64_t)t->key_max[0] + 1;
+  const uint64_t root_words = n0 && span <= 64 * n0 && span <= (1ull << 32) ? (span + 63) / 64 : 0;
+  const uint64_t all = base[nl] + root_words;
+  if (!all) return;
+  t->words.alloc(all, s);
+  ProfScope ps("layout_fill", s, total, all);
+  LH_HIP(hipMemsetAsync(t->words.p, 0, all * sizeof(uint64_t), s));
+  t->ranks.alloc(all, s);
+  for (uint32_t l = 0; l < nl; l++) {
+    Level& L = t->lv[l];
+    L.pool_words = base[l + 1] - base[l];
+    if (!L.pool_words) continue;
+    L.pool.p = t->words.p + base[l];
+    // positions inside bitset sets are needed when a deeper level hangs
+    // below or the rows of a bag are reached through them
+    if (l + 1 < nl || (t->flags & LH_BAG)) L.bs_rank.p = t->ranks.p + base[l];
+    k_layout_fill<<<grid_for(L.n), 256, 0, s>>>(L.keys.p, l ? parent[l].p : nullptr, L.n, L.bs_word.p, L.bs_base.p,
+                                                L.pool.p, L.bs_rank.p);
     LH_HIP(hipGetLastError());
-    L.bs_rank.alloc(L.pool_words + 1, s);
-    scan_u32_dev(pc.p, L.bs_rank.p, L.pool_words, s);
-    L.bs_delta.alloc(L.n_sets, s);
-    k_rank_delta<<<grid_for(L.n_sets), 256, 0, s>>>(sr, L.n_sets, L.bs_word.p, L.bs_rank.p, L.bs_delta.p);
+  }
+  if (root_words) {
+    t->root_span = span;
+    t->root_bits.p = t->words.p + base[nl];
+    t->root_rank.p = t->ranks.p + base[nl];
+    k_layout_fill<<<grid_for(n0), 256, 0, s>>>(t->lv[0].keys.p, nullptr, n0, nullptr, nullptr, t->root_bits.p,
+                                               t->root_rank.p);
     LH_HIP(hipGetLastError());
   }
 }
@@ -444,22 +551,6 @@ void ensure_column_stats(lh_trie* t, hipStream_t s) {
   t->col_stats = true;
 }
 
-// The presorted-tail mask of the rows into *mask (device): bit t-1 set when
-// the rows are in lexicographic order of their last t levels.
-static void presorted_mask(const uint32_t* const* col, uint32_t n_keys, uint64_t n, uint32_t* mask, hipStream_t s) {
-  LevelCols c{};
-  c.n_levels = n_keys;
-  for (uint32_t l = 0; l < n_keys; l++) c.k[l] = col[l];
-  const uint32_t all = (1u << n_keys) - 1;
-  const unsigned nb = grid_for(n);
-  DBuf<uint32_t> part(nb, s);
-  ProfScope ps("trie_presorted", s, n, 0);
-  k_sorted_tails<<<nb, 256, 0, s>>>(c, n, all, part.p);
-  LH_HIP(hipGetLastError());
-  k_and_total<<<1, 256, 0, s>>>(part.p, nb, all, mask);
-  LH_HIP(hipGetLastError());
-}
-
 // The most trailing levels whose order a presorted-tail mask shows (0: not
 // even the last level's).
 static uint32_t tail_of_mask(uint32_t mask, uint32_t n_keys) {
@@ -467,6 +558,14 @@ static uint32_t tail_of_mask(uint32_t mask, uint32_t n_keys) {
     if (mask >> (t - 1) & 1u) return t;
   return 0;
 }
+
+namespace {
+constexpr uint32_t BUILD_ANNOS = 8;  // annotation columns whose statistics come with the rest
+struct BuildOut {
+  AnnoAcc anno[BUILD_ANNOS];
+  uint32_t max_run;
+};
+}  // namespace
 
 lh_trie* build_trie(uint64_t n_rows, uint32_t n_keys, const uint32_t* const* keys, uint32_t n_annos,
                     const double* const* annos, uint32_t n_meta, const uint32_t* const* meta,
@@ -495,24 +594,33 @@ lh_trie* build_trie(uint64_t n_rows, uint32_t n_keys, const uint32_t* const* key
     }
     col[l] = src;
   }
-  // every level's largest key and, when asked, the presorted tail: one
-  // read back for all of them
-  struct InputStats {
-    uint32_t key_max[LH_MAX_KEYS];
-    uint32_t tail_mask;
-  };
-  {
-    DBuf<InputStats> st(1, s);
-    LH_HIP(hipMemsetAsync(st.p, 0, sizeof(InputStats), s));
-    for (uint32_t l = 0; l < n_keys; l++) max_u32_into(col[l], n, &st.p->key_max[l], s);
+  // every level's largest key and, when asked, the presorted tail: one pass
+  // over the columns, one read back
+  if (n) {
+    LevelCols c{};
+    c.n_levels = n_keys;
+    for (uint32_t l = 0; l < n_keys; l++) c.k[l] = col[l];
     const bool detect = detect_sorted && sorted_tail == 0 && n > 1;
-    if (detect) presorted_mask(col, n_keys, n, &st.p->tail_mask, s);
-    const InputStats h = read_scalar(st.p, s);
+    const uint32_t all = (1u << n_keys) - 1;
+    const unsigned nb = std::min(grid_for((n + 3) / 4), 2048u);
+    DBuf<InputStats> part(nb, s);
+    HostOut<InputStats> out(s);
+    {
+      ProfScope ps("trie_input", s, n, 0);
+      if (detect) k_input_stats<true><<<nb, 256, 0, s>>>(c, n, all, part.p);
+      else k_input_stats<false><<<nb, 256, 0, s>>>(c, n, all, part.p);
+    }
+    LH_HIP(hipGetLastError());
+    k_input_total<<<1, (LH_MAX_KEYS + 1) * WAVE, 0, s>>>(part.p, nb, n_keys, all, out.p());
+    LH_HIP(hipGetLastError());
+    const InputStats h = out.get();
     for (uint32_t l = 0; l < n_keys; l++) {
       t->key_max[l] = h.key_max[l];
       t->key_bits[l] = bitlen(t->key_max[l]);
     }
     if (detect) sorted_tail = tail_of_mask(h.tail_mask, n_keys);
+  } else {
+    for (uint32_t l = 0; l < n_keys; l++) t->key_max[l] = t->key_bits[l] = 0;
   }
 
   // Keys of up to 96 bits are sorted packed and unpacked into the sorted
@@ -588,16 +696,27 @@ lh_trie* build_trie(uint64_t n_rows, uint32_t n_keys, const uint32_t* const* key
     k_head_counts<<<ntiles, TB_NT, 0, s>>>(lc, n, counts.p, ntiles);
     LH_HIP(hipGetLastError());
   }
-  // scan per level: offsets of level l start at toff[l*ntiles]
-  std::vector<uint64_t> level_n(n_keys, 0);
-  DBuf<uint32_t> tmp(ntiles + 1, s);
-  for (uint32_t l = 0; l < n_keys; l++) {
-    uint64_t tot = n ? scan_u32(counts.p + (uint64_t)l * ntiles, tmp.p, ntiles, s) : 0;
-    if (n) LH_HIP(hipMemcpyAsync(toff.p + (uint64_t)l * ntiles, tmp.p, ntiles * sizeof(uint32_t),
-                                 hipMemcpyDeviceToDevice, s));
-    level_n[l] = tot;
-  }
+  // one scan over all levels' tile counts (modulo 2^32: a level's offsets
+  // are differences from its first tile's)
   EmitArgs ea{};
+  std::vector<uint64_t> level_n(n_keys, 0);
+  if (n) {
+    scan_u32_dev(counts.p, toff.p, cn, s);
+    struct LevelTotals {
+      uint32_t v[LH_MAX_KEYS];
+    };
+    HostOut<LevelTotals> out(s);
+    k_level_totals<<<1, WAVE, 0, s>>>(toff.p, ntiles, n_keys, out.p()->v);
+    LH_HIP(hipGetLastError());
+    const LevelTotals h = out.get();
+    uint32_t at = 0;
+    for (uint32_t l = 0; l < n_keys; l++) {
+      level_n[l] = h.v[l];
+      ea.level_n[l] = h.v[l];
+      ea.level_base[l] = at;
+      at += h.v[l];
+    }
+  }
   ea.c = lc;
   ea.tile_off = toff.p;
   ea.ntiles = ntiles;
@@ -606,6 +725,8 @@ lh_trie* build_trie(uint64_t n_rows, uint32_t n_keys, const uint32_t* const* key
     L.n = level_n[l];
     L.keys.alloc(L.n, s);
     ea.keys_out[l] = L.keys.p;
+    L.samp.alloc((L.n + (1u << LINE_SHIFT) - 1) >> LINE_SHIFT, s);
+    ea.samp_out[l] = L.samp.p;
     if (l + 1 < n_keys) {
       L.offs.alloc(L.n + 1, s);
       ea.offs_out[l] = L.offs.p;
@@ -640,31 +761,18 @@ lh_trie* build_trie(uint64_t n_rows, uint32_t n_keys, const uint32_t* const* key
     k_emit_levels<<<ntiles, TB_NT, 0, s>>>(ea, n);
     LH_HIP(hipGetLastError());
   }
-  // closing offsets: offs_l[n_l] = n_{l+1}; run[n_leaf] = n
-  for (uint32_t l = 0; l + 1 < n_keys; l++) {
-    k_set_u32<<<1, 1, 0, s>>>(t->lv[l].offs.p + t->lv[l].n, (uint32_t)level_n[l + 1]);
-    LH_HIP(hipGetLastError());
+  if (!n) {  // closing offsets of an empty trie
+    for (uint32_t l = 0; l + 1 < n_keys; l++) fill_u32(t->lv[l].offs.p, 0, 1, s);
+    if (bag) fill_u32(t->lv[n_keys - 1].offs.p, 0, 1, s);
   }
-  if (bag) {
-    k_set_u32<<<1, 1, 0, s>>>(t->lv[n_keys - 1].offs.p + n_leaf, (uint32_t)n);
+  // what the host reads when everything is queued: the longest run, where
+  // some key tuple repeats, and the annotations' statistics
+  const bool runs = bag && n_leaf < n;
+  DBuf<BuildOut> bout(runs || n_annos ? 1 : 0, s);
+  if (bout.p) LH_HIP(hipMemsetAsync(bout.p, 0, sizeof(BuildOut), s));
+  if (runs) {
+    k_max_run<<<std::min(grid_for(n_leaf), 1024u), 256, 0, s>>>(t->lv[n_keys - 1].offs.p, n_leaf, &bout.p->max_run);
     LH_HIP(hipGetLastError());
-    if (n_leaf < n) {  // some key tuple repeats
-      DBuf<uint32_t> m(1, s);
-      LH_HIP(hipMemsetAsync(m.p, 0, sizeof(uint32_t), s));
-      k_max_run<<<std::min(grid_for(n_leaf), 1024u), 256, 0, s>>>(t->lv[n_keys - 1].offs.p, n_leaf, m.p);
-      LH_HIP(hipGetLastError());
-      t->max_run = read_scalar(m.p, s);
-    }
-  }
-
-  for (uint32_t l = 0; l < n_keys; l++) {
-    Level& L = t->lv[l];
-    const uint64_t ns = (L.n + (1u << LINE_SHIFT) - 1) >> LINE_SHIFT;
-    L.samp.alloc(ns, s);
-    if (ns) {
-      k_line_samples<<<grid_for(ns), 256, 0, s>>>(L.keys.p, ns, L.samp.p);
-      LH_HIP(hipGetLastError());
-    }
   }
 
   // Rows in trie order: bag keeps every sorted row, set keeps leaf heads.
@@ -690,6 +798,7 @@ lh_trie* build_trie(uint64_t n_rows, uint32_t n_keys, const uint32_t* const* key
   }
   // a presorted bag keeps its input rows in order: plain copies
   const bool same_rows = copy_order && bag && !sel;
+  std::vector<AnnoStats> late;
   for (uint32_t a = 0; a < n_annos; a++) {
     if (carry) t->annos.push_back(std::move(carry_anno));
     else t->annos.emplace_back(t->n_rows, s);
@@ -701,7 +810,8 @@ lh_trie* build_trie(uint64_t n_rows, uint32_t n_keys, const uint32_t* const* key
     } else {
       gather_f64(annos[a], rowmap, t->annos.back().p, t->n_rows, s);
     }
-    t->astats.push_back(anno_stats(t->annos.back().p, t->n_rows, s));
+    if (a < BUILD_ANNOS) anno_stats_into(t->annos.back().p, t->n_rows, &bout.p->anno[a], s);
+    else late.push_back(anno_stats(t->annos.back().p, t->n_rows, s));
   }
   for (uint32_t m = 0; m < n_meta; m++) {
     if (carry) t->meta.push_back(std::move(carry_meta));
@@ -716,25 +826,13 @@ lh_trie* build_trie(uint64_t n_rows, uint32_t n_keys, const uint32_t* const* key
     }
   }
 
-  uint32_t mode = flags & LH_LAYOUT_MASK;
-  for (uint32_t l = 0; l < n_keys; l++) build_layouts(t.get(), l, mode, l ? parent[l].p : nullptr, s);
-  // root index, when level 0 holds at least one key per 64 of its span
-  const uint64_t n0 = t->lv[0].n;
-  if (n0) {
-    const uint64_t span = (uint64_t)t->key_max[0] + 1;
-    if (span <= 64 * n0 && span <= (1ull << 32)) {
-      const uint64_t words = (span + 63) / 64;
-      t->root_span = span;
-      t->root_bits.alloc(words, s);
-      t->root_rank.alloc(words + 1, s);
-      LH_HIP(hipMemsetAsync(t->root_bits.p, 0, words * sizeof(uint64_t), s));
-      k_layout_fill<<<grid_for(n0), 256, 0, s>>>(t->lv[0].keys.p, nullptr, n0, nullptr, nullptr, t->root_bits.p);
-      LH_HIP(hipGetLastError());
-      DBuf<uint32_t> pc(words, s);
-      k_word_popc<<<grid_for(words), 256, 0, s>>>(t->root_bits.p, words, pc.p);
-      LH_HIP(hipGetLastError());
-      scan_u32_dev(pc.p, t->root_rank.p, words, s);
-    }
+  build_layouts(t.get(), flags & LH_LAYOUT_MASK, parent, s);
+  if (bout.p) {
+    const BuildOut h = read_scalar(bout.p, s);
+    if (runs) t->max_run = h.max_run;
+    t->astats.clear();
+    for (uint32_t a = 0; a < std::min(n_annos, BUILD_ANNOS); a++) t->astats.push_back(decode_anno_stats(h.anno[a]));
+    for (const AnnoStats& st : late) t->astats.push_back(st);
   }
   LH_HIP(hipStreamSynchronize(s));
   return t.release();
