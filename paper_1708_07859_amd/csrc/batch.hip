@@ -7,6 +7,7 @@
 // join-aggregate queries (the order i, j, k is the relaxed order of section
 // 4.1.2, whose last attribute is materialized by a GROUP BY on a key,
 // section 5).  Every row i of every instance is a work item:
+//  * vector rows (E(j)) are taken by eight lanes each, long ones by a block;
 //  * light rows (few products) are taken by one wave, which sums exactly
 //    into a private LDS hash keyed by k;
 //  * heavy rows are taken by a whole block: a symbolic pass marks the k the
@@ -19,8 +20,9 @@
 //    the entries of E transposed (built once per batch) are streamed
 //    through it, matches adding to per-column LDS accumulators.
 // Workers pull items from two device queues (heavy rows first, longest
-// first), so one launch balances thousands of instances.  The launch and
-// its queue resets are captured once in a hipGraph and replayed.  Sums are
+// first), so one launch balances thousands of instances.  Plans that come
+// a second time have the launch and its queue resets captured in a hipGraph
+// and replayed from then on.  Sums are
 // exact (the same accumulator as the single-plan path), so every instance's
 // result is bit-identical to running its plan alone.
 #include <algorithm>
@@ -60,8 +62,10 @@ struct BInst {
   const uint32_t* e_j;       // E level 0 keys
   uint32_t e_n0;
   uint32_t e_dense;          // E's first-level keys are exactly 0 .. e_n0 - 1
-  uint64_t e_bsw;            // E root set bitset word (UINT64_MAX: uint layout)
-  uint32_t e_bsb;
+  uint64_t e_bsw;            // E root set bitset word (UINT64_MAX: uint layout); both read
+  uint32_t e_bsb;            //   from the trie's descriptors by k_inst_roots
+  const uint64_t* e_bsw_of;
+  const uint32_t* e_bsb_of;
   const uint64_t* e_pool;
   const uint32_t* e_off;     // matrix: E level 0 child offsets
   const uint32_t* e_k;       // matrix: E level 1 keys
@@ -114,37 +118,115 @@ __device__ __forceinline__ void rows_of(const uint32_t* run, uint32_t node, uint
 
 // ---- setup: per-row product bounds and classes ----------------------------
 
-__global__ void k_row_setup(const BInst* inst, const uint64_t* inst_row0, uint32_t n_inst, uint64_t R,
-                            uint32_t light_max, uint32_t inner_ratio, uint32_t* row_inst, uint64_t* prod, uint32_t* ub,
-                            uint32_t* is_heavy, uint32_t* is_light, uint32_t* is_inner) {
-  for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < R; t += (uint64_t)gridDim.x * blockDim.x) {
-    const uint32_t ii = (uint32_t)upper_bound_minus1<uint64_t>(inst_row0, 0, n_inst, t);
-    const BInst& I = inst[ii];
-    const uint32_t p = (uint32_t)(t - inst_row0[ii]);
-    row_inst[t] = ii;
-    uint64_t u = 0;
-    for (uint32_t q = I.a_off[p]; q < I.a_off[p + 1]; q++) {
-      uint32_t pe;
-      if (!find_j(I, I.a_j[q], pe)) continue;
-      uint32_t ab, ae, eb, ee;
-      rows_of(I.a_run, q, ab, ae);
-      if (I.kind == 0) {
-        rows_of(I.e_run, pe, eb, ee);
-        u += (uint64_t)(ae - ab) * (ee - eb);
-      } else {
-        u += (uint64_t)(ae - ab) * (I.e_off[pe + 1] - I.e_off[pe]);
-      }
+__global__ void k_inst_roots(BInst* inst, uint32_t n) {
+  for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
+    BInst& I = inst[i];
+    if (!I.e_n0) continue;
+    I.e_bsw = *I.e_bsw_of;
+    I.e_bsb = *I.e_bsb_of;
+  }
+}
+
+// Products of entry q of A's second level.
+__device__ __forceinline__ uint64_t entry_products(const BInst& I, uint32_t q) {
+  uint32_t pe;
+  if (!find_j(I, I.a_j[q], pe)) return 0;
+  uint32_t ab, ae, eb, ee;
+  rows_of(I.a_run, q, ab, ae);
+  if (I.kind == 0) {
+    rows_of(I.e_run, pe, eb, ee);
+    return (uint64_t)(ae - ab) * (ee - eb);
+  }
+  return (uint64_t)(ae - ab) * (I.e_off[pe + 1] - I.e_off[pe]);
+}
+
+// Every row's instance, products and output bound.  A thread walks a row of
+// up to ROW_THREAD entries; longer ones are left to its wave, and those past
+// ROW_WAVE to its block (a thread walking a power-law hub's row alone took
+// 12.5 ms of a 16-instance setup; now 0.1 ms).
+constexpr uint32_t ROW_THREAD = 16, ROW_WAVE = 2048;
+__global__ __launch_bounds__(B_NT) void k_row_products(const BInst* inst, const uint64_t* inst_row0, uint32_t n_inst,
+                                                       uint64_t R, uint32_t* row_inst, uint64_t* prod, uint32_t* ub) {
+  __shared__ uint32_t s_long[B_NT];
+  __shared__ uint32_t s_n;
+  __shared__ uint64_t s_red[B_NW];
+  const int lane = lane_id();
+  for (uint64_t t0 = (uint64_t)blockIdx.x * B_NT; t0 < R; t0 += (uint64_t)gridDim.x * B_NT) {
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    const uint64_t t = t0 + threadIdx.x;
+    uint32_t ii = 0, qb = 0, len = 0;
+    if (t < R) {
+      ii = (uint32_t)upper_bound_minus1<uint64_t>(inst_row0, 0, n_inst, t);
+      const uint32_t p = (uint32_t)(t - inst_row0[ii]);
+      qb = inst[ii].a_off[p];
+      len = inst[ii].a_off[p + 1] - qb;
+      row_inst[t] = ii;
     }
-    prod[t] = u;
+    uint64_t u = 0;
+    if (len <= ROW_THREAD) {
+      for (uint32_t q = qb; q < qb + len; q++) u += entry_products(inst[ii], q);
+    } else if (len > ROW_WAVE) {
+      s_long[atomicAdd(&s_n, 1u)] = threadIdx.x;
+    }
+    for (uint64_t m = ballot(len > ROW_THREAD && len <= ROW_WAVE); m; m &= m - 1) {
+      const int l = __builtin_ctzll(m);
+      const BInst& I = inst[__shfl((int)ii, l, WAVE)];
+      const uint32_t b = (uint32_t)__shfl((int)qb, l, WAVE), n = (uint32_t)__shfl((int)len, l, WAVE);
+      uint64_t v = 0;
+      for (uint32_t k = lane; k < n; k += WAVE) v += entry_products(I, b + k);
+      v = wave_sum(v);
+      if (lane == l) u = v;
+    }
+    __syncthreads();
+    for (uint32_t i = 0; i < s_n; i++) {  // uniform over the block
+      const uint64_t tl = t0 + s_long[i];
+      const uint32_t il = (uint32_t)upper_bound_minus1<uint64_t>(inst_row0, 0, n_inst, tl);
+      const BInst& I = inst[il];
+      const uint32_t p = (uint32_t)(tl - inst_row0[il]);
+      const uint32_t b = I.a_off[p], e = I.a_off[p + 1];
+      uint64_t v = 0;
+      for (uint32_t k = b + threadIdx.x; k < e; k += 4 * B_NT) {
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+          if (k + j * B_NT < e) v += entry_products(I, k + j * B_NT);
+      }
+      v = block_sum<uint64_t, B_NT>(v, s_red);
+      if (threadIdx.x == s_long[i]) u = v;
+    }
+    if (t < R) {
+      prod[t] = u;
+      ub[t] = inst[ii].kind == 0 ? 1u : (uint32_t)min<uint64_t>(u, inst[ii].n_k);
+    }
+    __syncthreads();  // s_long and s_n are free again
+  }
+}
+
+// The class of every row under a tuning; n_inner[instance] is set where the
+// instance has inner-product rows.
+__global__ void k_row_classes(const BInst* inst, const uint32_t* row_inst, const uint64_t* prod, uint64_t R,
+                              uint32_t light_max, uint32_t inner_ratio, uint32_t* is_heavy, uint32_t* is_light,
+                              uint32_t* is_inner, uint32_t* n_inner) {
+  for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < R; t += (uint64_t)gridDim.x * blockDim.x) {
+    const BInst& I = inst[row_inst[t]];
+    const uint64_t u = prod[t];
     const bool heavy = I.kind == 1 && u > light_max;
     // inner-product form when walking all of E costs less than inner_ratio
     // scattered updates per product
-    const bool inner = heavy && I.bt_k && I.n_j <= KW_MAX && u * inner_ratio >= I.nnz_e;
-    ub[t] = I.kind == 0 ? 1u : (uint32_t)min<uint64_t>(u, I.n_k);
+    const bool inner = heavy && I.n_j <= KW_MAX && u * inner_ratio >= I.nnz_e;
     is_heavy[t] = heavy && !inner ? 1u : 0u;
-    is_light[t] = heavy ? 0u : 1u;
+    is_light[t] = I.kind == 1 && !heavy ? 1u : 0u;
     is_inner[t] = inner ? 1u : 0u;
+    if (inner) n_inner[row_inst[t]] = 1u;
   }
+}
+
+// Heavy rows longest first: keys that ascend as products fall.
+constexpr uint32_t HEAVY_KEY_BITS = 40;
+__global__ void k_heavy_keys(const uint32_t* rows, uint64_t n, const uint64_t* prod, uint64_t* key) {
+  constexpr uint64_t top = (1ull << HEAVY_KEY_BITS) - 1;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
+    key[i] = top - min(prod[rows[i]], top);
 }
 
 __global__ void k_fill_u32_dev(uint32_t* p, uint32_t v, uint64_t n) {
@@ -164,7 +246,7 @@ struct BatchArgs {
   uint64_t n_light;
   const uint32_t* inner;     // inner-product rows, grouped by instance
   uint64_t n_inner;
-  uint32_t* qhead;           // [0] heavy queue, [1] light queue, [2] inner queue
+  uint32_t* qhead;           // [0] heavy queue, [1] light queue, [2] inner queue, [3] long vector rows
   uint32_t* row_nnz;         // outputs per row
   uint32_t* ub_k;
   uint64_t* ub_cnt;
@@ -435,23 +517,60 @@ __global__ __launch_bounds__(B_NT) void k_batch_heavy(BatchArgs a) {
   if (bad) atomicOr(a.err, 1u);
 }
 
+// The products of one matched entry e (with j) of an inner-product row into
+// its column's LDS accumulator.
+__device__ __forceinline__ void inner_product(const BInst& I, uint32_t e, uint32_t j,
+                                              const unsigned long long* bm,
+                                              const uint32_t* pre, const uint32_t* soff, uint32_t nk, uint32_t qb,
+                                              unsigned long long* ccnt, long long* cdig, bool bounded, uint32_t& bad) {
+  // column of entry e: the last c with soff[c] <= e
+  uint32_t c = 0, n = nk;
+  while (n > 1) {
+    const uint32_t half = n >> 1;
+    c = (soff[c + half] <= e) ? c + half : c;
+    n -= half;
+  }
+  const uint64_t word = bm[j >> 6];
+  const uint32_t q = qb + pre[j >> 6] + (uint32_t)__popcll(word & ((1ull << (j & 63u)) - 1ull));
+  uint32_t ab, ae, eb, ee;
+  rows_of(I.a_run, q, ab, ae);
+  rows_of(I.bt_run, e, eb, ee);
+  atomicAdd(&ccnt[c], (unsigned long long)(ae - ab) * (ee - eb));
+  if (!I.sum) return;
+  for (uint32_t ra = ab; ra < ae; ra++)
+    for (uint32_t re = eb; re < ee; re++) {
+      double hi, lo;
+      two_prod(I.a_val[ra], I.bt_val[re], hi, lo);
+      bool ok = lds_add_term(cdig + c * DSTRIDE, hi, I.lsb, I.D, bounded);
+      ok = lds_add_term(cdig + c * DSTRIDE, lo, I.lsb, I.D, bounded) && ok;
+      if (!ok) bad = 1;
+    }
+}
+
 // Inner-product rows: one block per row.  A's row is marked in an LDS
 // bitmap over j with per-word rank prefixes (the position of j in the row).
-// E transposed is then streamed chunk by chunk (256 columns k at a time):
+// E transposed is then streamed chunk by chunk (I_NT columns k at a time):
 // the block's threads take the chunk's (k, j) entries in order, coalesced
-// and independent, probe j in the bitmap, and add each matching product's
-// exact digits to its column's LDS accumulator (the column found by
-// bisecting the chunk's offsets); the columns are then emitted in k order
-// and their accumulators cleared.
-__global__ __launch_bounds__(B_NT) void k_batch_inner(BatchArgs a) {
+// and independent, probe j in the bitmap and queue the matching entries;
+// full waves of them then add each product's exact digits to its column's
+// LDS accumulator (the column found by bisecting the chunk's offsets); the
+// columns are then emitted in k order and their accumulators cleared.
+// Threads of a block, columns of a chunk: a row is one block's, and its
+// stream of E's entries is a chain of load latencies, so a block is large.
+constexpr int I_NT = 1024;
+constexpr int I_NW = I_NT / WAVE;
+constexpr int I_WPT = (int)(KW_MAX / 64) / I_NT;  // bitmap words per thread
+static_assert(I_WPT >= 1 && I_WPT * I_NT == (int)(KW_MAX / 64), "bitmap words per thread");
+__global__ __launch_bounds__(I_NT) void k_batch_inner(BatchArgs a) {
   __shared__ unsigned long long bm[KW_MAX / 64];
   __shared__ uint32_t pre[KW_MAX / 64];
-  __shared__ uint32_t soff[B_NT + 1];                 // the chunk's column offsets
-  __shared__ unsigned long long ccnt[B_NT];           // per column of the chunk
-  __shared__ long long cdig[B_NT * DSTRIDE];
+  __shared__ uint32_t soff[I_NT + 1];                 // the chunk's column offsets
+  __shared__ unsigned long long ccnt[I_NT];           // per column of the chunk
+  __shared__ long long cdig[I_NT * DSTRIDE];
+  __shared__ uint32_t s_qe[I_NW][2 * WAVE], s_qj[I_NW][2 * WAVE];  // matched entries waiting, per wave
   __shared__ uint32_t s_item;
-  __shared__ uint32_t s_wsum[B_NW];
-  const int tid = threadIdx.x;
+  __shared__ uint32_t s_wsum[I_NW];
+  const int tid = threadIdx.x, w = tid / WAVE, lane = lane_id();
   uint32_t bad = 0;
   ccnt[tid] = 0;
 #pragma unroll
@@ -468,9 +587,9 @@ __global__ __launch_bounds__(B_NT) void k_batch_inner(BatchArgs a) {
     const uint32_t qb = I.a_off[p], qe = I.a_off[p + 1];
     const bool bounded = a.prod[t] < BOUNDED_PRODUCTS;
     const uint32_t nwords = (I.n_j + 63) / 64;
-    for (uint32_t s = tid; s < nwords; s += B_NT) bm[s] = 0;
+    for (uint32_t s = tid; s < nwords; s += I_NT) bm[s] = 0;
     __syncthreads();
-    for (uint32_t q = qb + tid; q < qe; q += B_NT) {
+    for (uint32_t q = qb + tid; q < qe; q += I_NT) {
       const uint32_t j = I.a_j[q];
       atomicOr(&bm[j >> 6], 1ull << (j & 63u));
     }
@@ -478,15 +597,15 @@ __global__ __launch_bounds__(B_NT) void k_batch_inner(BatchArgs a) {
     {
       uint32_t c = 0;
 #pragma unroll
-      for (int i = 0; i < 4; i++) {
-        const uint32_t wi = 4 * tid + i;
+      for (int i = 0; i < I_WPT; i++) {
+        const uint32_t wi = I_WPT * tid + i;
         c += wi < nwords ? (uint32_t)__popcll(bm[wi]) : 0u;
       }
       uint32_t tot;
-      uint32_t r = block_excl_scan<uint32_t, B_NT>(c, s_wsum, tot);
+      uint32_t r = block_excl_scan<uint32_t, I_NT>(c, s_wsum, tot);
 #pragma unroll
-      for (int i = 0; i < 4; i++) {
-        const uint32_t wi = 4 * tid + i;
+      for (int i = 0; i < I_WPT; i++) {
+        const uint32_t wi = I_WPT * tid + i;
         if (wi < nwords) {
           pre[wi] = r;
           r += (uint32_t)__popcll(bm[wi]);
@@ -495,56 +614,57 @@ __global__ __launch_bounds__(B_NT) void k_batch_inner(BatchArgs a) {
     }
     const uint64_t out = a.ub_off[t];
     uint32_t nnz = 0;
-    for (uint32_t kb0 = 0; kb0 < I.bt_n0; kb0 += B_NT) {
-      const uint32_t nk = min((uint32_t)B_NT, I.bt_n0 - kb0);
+    for (uint32_t kb0 = 0; kb0 < I.bt_n0; kb0 += I_NT) {
+      const uint32_t nk = min((uint32_t)I_NT, I.bt_n0 - kb0);
       soff[tid] = I.bt_off[kb0 + min((uint32_t)tid, nk)];
-      if (tid == 0) soff[B_NT] = I.bt_off[kb0 + nk];
+      if (tid == 0) soff[I_NT] = I.bt_off[kb0 + nk];
       __syncthreads();
       const uint32_t e0 = soff[0], e1 = soff[nk];
-      // four entries per thread per round: their loads are independent and
-      // in flight together (few entries match, so the loop is load latency)
+      // Four entries per thread per round: their loads are independent and
+      // in flight together.  Entries whose j the row holds (2 to 30% of
+      // them) are queued per wave in LDS and worked on 64 at a time: worked
+      // on where they were found, nearly every wave ran the whole product
+      // path for one or two lanes (6.1 ms of a 16-instance batch).
+      // With blocks of 1024 threads for 256: 2.1 ms.
       constexpr uint32_t UNR = 4;
-      for (uint32_t eb = e0 + tid; eb < e1; eb += UNR * B_NT) {
+      uint32_t qn = 0;  // queued entries (uniform over the wave)
+      for (uint32_t eb = e0 + tid; eb - lane < e1; eb += UNR * I_NT) {
         uint32_t jv[UNR];
 #pragma unroll
         for (uint32_t u = 0; u < UNR; u++) {
-          const uint32_t e = eb + u * B_NT;
+          const uint32_t e = eb + u * I_NT;
           jv[u] = e < e1 ? I.bt_j[e] : UINT32_MAX;
         }
 #pragma unroll
         for (uint32_t u = 0; u < UNR; u++) {
-        const uint32_t e = eb + u * B_NT;
-        const uint32_t j = jv[u];
-        if (j >= I.n_j) continue;
-        const uint64_t word = bm[j >> 6];
-        if (!((word >> (j & 63u)) & 1ull)) continue;
-        // column of entry e: the last c with soff[c] <= e
-        uint32_t c = 0, n = nk;
-        while (n > 1) {
-          const uint32_t half = n >> 1;
-          c = (soff[c + half] <= e) ? c + half : c;
-          n -= half;
-        }
-        const uint32_t q = qb + pre[j >> 6] + (uint32_t)__popcll(word & ((1ull << (j & 63u)) - 1ull));
-        uint32_t ab, ae, eb, ee;
-        rows_of(I.a_run, q, ab, ae);
-        rows_of(I.bt_run, e, eb, ee);
-        atomicAdd(&ccnt[c], (unsigned long long)(ae - ab) * (ee - eb));
-        if (I.sum)
-          for (uint32_t ra = ab; ra < ae; ra++)
-            for (uint32_t re = eb; re < ee; re++) {
-              double hi, lo;
-              two_prod(I.a_val[ra], I.bt_val[re], hi, lo);
-              bool ok = lds_add_term(cdig + c * DSTRIDE, hi, I.lsb, I.D, bounded);
-              ok = lds_add_term(cdig + c * DSTRIDE, lo, I.lsb, I.D, bounded) && ok;
-              if (!ok) bad = 1;
+          const uint32_t j = jv[u];
+          const bool hit = j < I.n_j && ((bm[j >> 6] >> (j & 63u)) & 1ull);
+          const uint64_t hits = ballot(hit);
+          if (hit) {
+            const uint32_t at = qn + lanes_below(hits);
+            s_qe[w][at] = eb + u * I_NT;
+            s_qj[w][at] = j;
+          }
+          qn += (uint32_t)__popcll(hits);
+          if (qn >= WAVE) {
+            wave_lds_sync();
+            inner_product(I, s_qe[w][lane], s_qj[w][lane], bm, pre, soff, nk, qb, ccnt, cdig, bounded, bad);
+            qn -= WAVE;
+            wave_lds_sync();
+            if (lane < (int)qn) {
+              s_qe[w][lane] = s_qe[w][WAVE + lane];
+              s_qj[w][lane] = s_qj[w][WAVE + lane];
             }
+            wave_lds_sync();
+          }
         }
       }
+      wave_lds_sync();
+      if (lane < (int)qn) inner_product(I, s_qe[w][lane], s_qj[w][lane], bm, pre, soff, nk, qb, ccnt, cdig, bounded, bad);
       __syncthreads();
       const uint64_t cnt = (uint32_t)tid < nk ? ccnt[tid] : 0ull;
       uint32_t tot;
-      const uint32_t r = block_excl_scan<uint32_t, B_NT>(cnt ? 1u : 0u, s_wsum, tot);
+      const uint32_t r = block_excl_scan<uint32_t, I_NT>(cnt ? 1u : 0u, s_wsum, tot);
       if (cnt) {
         const uint64_t o = out + nnz + r;
         a.ub_k[o] = I.bt_k[kb0 + tid];
@@ -595,43 +715,6 @@ __global__ __launch_bounds__(B_NT) void k_batch_light(BatchArgs a) {
     const uint32_t p = t - (uint32_t)a.inst_row0[a.row_inst[t]];
     const uint32_t qb = I.a_off[p], qe = I.a_off[p + 1];
     const uint64_t out = a.ub_off[t];
-    if (I.kind == 0) {
-      // vector: one output per row, reduced across the wave
-      RegAcc acc;
-      acc.clear();
-      uint64_t cnt = 0;
-      for (uint32_t q = qb + lane; q < qe; q += WAVE) {
-        uint32_t pe;
-        if (!find_j(I, I.a_j[q], pe)) continue;
-        uint32_t ab, ae, eb, ee;
-        rows_of(I.a_run, q, ab, ae);
-        rows_of(I.e_run, pe, eb, ee);
-        cnt += (uint64_t)(ae - ab) * (ee - eb);
-        if (I.sum)
-          for (uint32_t ra = ab; ra < ae; ra++)
-            for (uint32_t re = eb; re < ee; re++) {
-              double hi, lo;
-              two_prod(I.a_val[ra], I.e_val[re], hi, lo);
-              bool ok = acc.add(hi, I.lsb, I.D, 1);
-              ok = acc.add(lo, I.lsb, I.D, 1) && ok;
-              if (!ok) bad = 1;
-            }
-      }
-      if (I.sum) acc.normalize(I.D);
-      cnt = wave_sum(cnt);
-      int64_t tot[EXACT_MAXD];
-#pragma unroll
-      for (int s = 0; s < EXACT_MAXD; s++) tot[s] = wave_sum(acc.s[s]);
-      if (lane == 0) {
-        if (cnt) {
-          a.ub_k[out] = 0;
-          a.ub_cnt[out] = cnt;
-          if (I.sum) a.ub_sum[out] = exact_round(tot, I.D, I.lsb, a.err);
-        }
-        a.row_nnz[t] = cnt ? 1u : 0u;
-      }
-      continue;
-    }
     // matrix: hash the row's products by k
     const bool bounded = a.prod[t] < BOUNDED_PRODUCTS;
     for (int s = lane; s < HS; s += WAVE) {
@@ -744,6 +827,100 @@ __global__ __launch_bounds__(B_NT) void k_batch_light(BatchArgs a) {
   if (bad) atomicOr(a.err, 1u);
 }
 
+// ---- vector rows ------------------------------------------------------------
+
+// Products of A's entries qb + from, qb + from + step, ... below qe.
+__device__ __forceinline__ void vector_products(const BInst& I, uint32_t qb, uint32_t qe, uint32_t from, uint32_t step,
+                                                uint64_t& cnt, RegAcc& acc, uint32_t& bad) {
+  for (uint32_t q = qb + from; q < qe; q += step) {
+    uint32_t pe;
+    if (!find_j(I, I.a_j[q], pe)) continue;
+    uint32_t ab, ae, eb, ee;
+    rows_of(I.a_run, q, ab, ae);
+    rows_of(I.e_run, pe, eb, ee);
+    cnt += (uint64_t)(ae - ab) * (ee - eb);
+    if (!I.sum) continue;
+    for (uint32_t ra = ab; ra < ae; ra++)
+      for (uint32_t re = eb; re < ee; re++) {
+        double hi, lo;
+        two_prod(I.a_val[ra], I.e_val[re], hi, lo);
+        bool ok = acc.add(hi, I.lsb, I.D, 1);
+        ok = acc.add(lo, I.lsb, I.D, 1) && ok;
+        if (!ok) bad = 1;
+      }
+  }
+}
+
+// A vector row's single output, by the thread that holds its sums.
+__device__ __forceinline__ void vector_output(const BatchArgs& a, const BInst& I, uint64_t t, uint64_t cnt,
+                                              const int64_t* digits) {
+  if (cnt) {
+    const uint64_t out = a.ub_off[t];
+    a.ub_k[out] = 0;
+    a.ub_cnt[out] = cnt;
+    if (I.sum) a.ub_sum[out] = exact_round(digits, I.D, I.lsb, a.err);
+  }
+  a.row_nnz[t] = cnt ? 1u : 0u;
+}
+
+// Rows of vector instances: eight lanes take a row of up to VEC_SHORT
+// entries (most rows of a power-law matrix hold one to three, and a wave
+// each spent itself on reducing them); longer rows are listed.
+constexpr uint32_t VEC_SHORT = 128;
+__global__ __launch_bounds__(B_NT) void k_batch_vec(BatchArgs a, uint64_t R, uint32_t* longs) {
+  constexpr int LPR = 8;
+  const int l = lane_id() % LPR;
+  uint32_t bad = 0;
+  for (uint64_t t = ((uint64_t)blockIdx.x * B_NT + threadIdx.x) / LPR; t < R;
+       t += (uint64_t)gridDim.x * (B_NT / LPR)) {  // (a row's lanes stay together)
+    const uint32_t ii = a.row_inst[t];
+    const BInst& I = a.inst[ii];
+    if (I.kind != 0) continue;
+    const uint32_t p = (uint32_t)(t - a.inst_row0[ii]);
+    const uint32_t qb = I.a_off[p], qe = I.a_off[p + 1];
+    if (qe - qb > VEC_SHORT) {
+      if (l == 0) longs[atomicAdd(&a.qhead[3], 1u)] = (uint32_t)t;
+      continue;
+    }
+    RegAcc acc;
+    acc.clear();
+    uint64_t cnt = 0;
+    vector_products(I, qb, qe, (uint32_t)l, LPR, cnt, acc, bad);
+    cnt = unit_sum<LPR>(cnt);
+    if (I.sum) {
+      acc.normalize(I.D);
+#pragma unroll
+      for (int i = 0; i < EXACT_MAXD; i++) acc.s[i] = unit_sum<LPR>(acc.s[i]);
+    }
+    // (sums of normalized digits: below 2^35, a valid shared-form value)
+    if (l == 0) vector_output(a, I, t, cnt, acc.s);
+  }
+  if (bad) atomicOr(a.err, 1u);
+}
+
+// The listed long rows, a block each.
+__global__ __launch_bounds__(B_NT) void k_batch_vec_long(BatchArgs a, const uint32_t* longs) {
+  __shared__ int64_t s_red[B_NW];
+  const uint32_t n = a.qhead[3];
+  for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+    const uint32_t t = longs[i];
+    const uint32_t ii = a.row_inst[t];
+    const BInst& I = a.inst[ii];
+    const uint32_t p = t - (uint32_t)a.inst_row0[ii];
+    RegAcc acc;
+    acc.clear();
+    uint64_t cnt = 0;
+    uint32_t bad = 0;
+    vector_products(I, I.a_off[p], I.a_off[p + 1], threadIdx.x, B_NT, cnt, acc, bad);
+    if (bad) atomicOr(a.err, 1u);
+    cnt = (uint64_t)block_sum<int64_t, B_NT>((int64_t)cnt, s_red);
+    acc.normalize(I.D);
+#pragma unroll
+    for (int q = 0; q < EXACT_MAXD; q++) acc.s[q] = block_sum<int64_t, B_NT>(acc.s[q], s_red);
+    if (threadIdx.x == 0) vector_output(a, I, t, cnt, acc.s);
+  }
+}
+
 // Copy each row's outputs from its upper-bound slots to the packed result.
 struct PackArgs2 {
   const BInst* inst;
@@ -761,70 +938,51 @@ struct PackArgs2 {
   uint64_t R;
 };
 
-// A wave takes 64 consecutive rows: lane l loads row t0 + l's offsets, its
-// instance and its i, then the wave copies the rows' outputs as one flat
-// range (the rows' packed outputs are contiguous), each lane finding the
-// row of its output by bisecting the rows' output offsets across the
-// lanes.  Every lane does useful copies whatever the rows' lengths.
-__global__ void k_pack_rows(PackArgs2 a) {
+// A wave takes PACK_SPAN consecutive outputs (rows may hold none or tens of
+// thousands: a wave per 64 rows waited for its hub rows).  It finds its first
+// output's row by bisection; 64 outputs at a time, the offsets of the 64
+// rows from the current one are loaded by the lanes and each lane finds its
+// output's row among them by bisecting across the lanes, window after window
+// where rows without outputs leave it further on.
+constexpr uint32_t PACK_SPAN = 2048;
+__global__ __launch_bounds__(B_NT) void k_pack_rows(PackArgs2 a, uint64_t total) {
   const int lane = lane_id();
-  const uint64_t nw = (uint64_t)gridDim.x * (blockDim.x / WAVE);
-  for (uint64_t t0 = ((uint64_t)blockIdx.x * (blockDim.x / WAVE) + threadIdx.x / WAVE) * WAVE; t0 < a.R;
-       t0 += nw * WAVE) {
-    const uint64_t t = t0 + lane;
-    const bool row = t < a.R;
-    // lanes past the last row start where the group ends
-    const uint64_t oo = a.out_off[row ? t : a.R];
-    const uint64_t base = a.out_off[t0], end = a.out_off[min<uint64_t>(t0 + WAVE, a.R)];
-    uint32_t iv = 0, flags = 0;
-    uint64_t uo = 0;
-    if (row) {
-      const uint32_t ii = a.row_inst[t];
-      const BInst& I = a.inst[ii];
-      iv = I.a_i[t - a.inst_row0[ii]];
-      flags = (I.kind == 1 ? 1u : 0u) | (I.sum ? 2u : 0u);
-      uo = a.ub_off[t];
-    }
-    if (end - base >= (1ull << 32)) {
-      // more than 2^32 outputs in the group: row by row
-      for (int l = 0; l < WAVE; l++) {
-        const uint64_t o0 = (uint64_t)__shfl((long long)oo, l, WAVE);
-        const uint64_t o1 = l + 1 < WAVE ? (uint64_t)__shfl((long long)oo, l + 1, WAVE) : end;
-        const uint64_t u0 = (uint64_t)__shfl((long long)uo, l, WAVE);
-        const uint32_t il = (uint32_t)__shfl((int)iv, l, WAVE), fl = (uint32_t)__shfl((int)flags, l, WAVE);
-        for (uint64_t e = o0 + lane; e < o1; e += WAVE) {
-          a.out_i[e] = il;
-          if (fl & 1u) a.out_k[e] = a.ub_k[u0 + (e - o0)];
-          a.out_cnt[e] = a.ub_cnt[u0 + (e - o0)];
-          if (fl & 2u) a.out_sum[e] = a.ub_sum[u0 + (e - o0)];
-        }
-      }
-      continue;
-    }
-    const uint32_t rel = (uint32_t)(oo - base);
-    const uint32_t uo_lo = (uint32_t)uo, uo_hi = (uint32_t)(uo >> 32);
-    for (uint64_t e0 = base; e0 < end; e0 += WAVE) {   // uniform: every lane takes part in the shuffles
-      const uint64_t e = e0 + (uint64_t)lane;
-      const uint32_t re = (uint32_t)(e - base);
-      // the row of output e: the last lane whose first output is <= e
+  const uint64_t wave = ((uint64_t)blockIdx.x * B_NT + threadIdx.x) / WAVE;
+  const uint64_t base = wave * PACK_SPAN;
+  if (base >= total) return;
+  const uint64_t end = min<uint64_t>(total, base + PACK_SPAN);
+  uint64_t r0 = upper_bound_minus1<uint64_t>(a.out_off, 0, a.R, base);
+  for (uint64_t e0 = base; e0 < end; e0 += WAVE) {   // uniform: every lane takes part in the shuffles
+    const uint64_t e = min<uint64_t>(e0 + lane, end - 1);
+    uint64_t row = 0;
+    bool found = false;
+    for (uint64_t rw = r0; !__all(found); rw += WAVE) {
+      // offsets of rows rw .. rw + 63 (past the last row: the end), and the
+      // next window's first
+      const uint64_t off = a.out_off[min<uint64_t>(rw + lane, a.R)];
+      const uint64_t next = a.out_off[min<uint64_t>(rw + WAVE, a.R)];
       uint32_t src = 0;
 #pragma unroll
       for (int step = WAVE / 2; step > 0; step >>= 1) {
-        const uint32_t r = (uint32_t)__shfl((int)rel, (int)(src + step), WAVE);
-        src = r <= re ? src + step : src;
+        const uint64_t o = (uint64_t)__shfl((unsigned long long)off, (int)(src + step), WAVE);
+        src = o <= e ? src + step : src;
       }
-      const uint32_t rs = (uint32_t)__shfl((int)rel, (int)src, WAVE);
-      const uint32_t is = (uint32_t)__shfl((int)iv, (int)src, WAVE);
-      const uint32_t fs = (uint32_t)__shfl((int)flags, (int)src, WAVE);
-      const uint64_t us = (uint64_t)(uint32_t)__shfl((int)uo_lo, (int)src, WAVE) |
-                          ((uint64_t)(uint32_t)__shfl((int)uo_hi, (int)src, WAVE) << 32);
-      if (e >= end) continue;
-      const uint64_t u = us + (re - rs);
-      a.out_i[e] = is;
-      if (fs & 1u) a.out_k[e] = a.ub_k[u];
-      a.out_cnt[e] = a.ub_cnt[u];
-      if (fs & 2u) a.out_sum[e] = a.ub_sum[u];
+      if (!found && (next > e || rw + WAVE >= a.R)) {
+        row = min<uint64_t>(rw + src, a.R - 1);
+        found = true;
+      }
     }
+    const uint32_t ii = a.row_inst[row];
+    const BInst& I = a.inst[ii];
+    const uint32_t iv = I.a_i[row - a.inst_row0[ii]];
+    const uint64_t u = a.ub_off[row] + (e - a.out_off[row]);
+    if (e0 + lane < end) {
+      a.out_i[e] = iv;
+      if (I.kind == 1) a.out_k[e] = a.ub_k[u];
+      a.out_cnt[e] = a.ub_cnt[u];
+      if (I.sum) a.out_sum[e] = a.ub_sum[u];
+    }
+    r0 = (uint64_t)__shfl((unsigned long long)row, WAVE - 1, WAVE);
   }
 }
 
@@ -884,6 +1042,8 @@ struct BatchState {
   DBuf<double> ub_sum;
   uint32_t kw = 64;
   uint64_t n_heavy = 0, n_light = 0, n_inner = 0;
+  bool has_vec = false;        // some instance is a matrix-vector product
+  DBuf<uint32_t> longs;        // its long rows, listed by k_batch_vec
   std::vector<uint64_t> h_inst_row0;
   std::vector<BInst> h_inst;
   hipGraph_t graph = nullptr;
@@ -910,7 +1070,7 @@ BInst describe(const lh_plan_t* p) {
   b.a_i = ta->lv[0].keys.p;
   b.a_off = ta->lv[0].offs.p;
   b.a_j = ta->lv[1].keys.p;
-  b.a_run = A.bag ? ta->lv[1].offs.p : nullptr;
+  b.a_run = run_offsets(ta);
   b.sum = p->agg == LH_AGG_SUM ? 1u : 0u;
   b.a_val = (b.sum && A.anno >= 0) ? ta->annos[A.anno].p : nullptr;
   b.e_j = te->lv[0].keys.p;
@@ -920,16 +1080,15 @@ BInst describe(const lh_plan_t* p) {
   b.e_pool = te->lv[0].pool.p;
   b.e_bsw = UINT64_MAX;
   b.e_bsb = 0;
-  if (b.e_n0) {
-    LH_HIP(hipMemcpy(&b.e_bsw, te->lv[0].bs_word.p, sizeof(uint64_t), hipMemcpyDeviceToHost));
-    LH_HIP(hipMemcpy(&b.e_bsb, te->lv[0].bs_base.p, sizeof(uint32_t), hipMemcpyDeviceToHost));
-  }
+  b.e_bsw_of = te->lv[0].bs_word.p;
+  b.e_bsb_of = te->lv[0].bs_base.p;
   if (b.kind == 1) {
     b.e_off = te->lv[0].offs.p;
     b.e_k = te->lv[1].keys.p;
     b.n_k = te->key_max[1] + 1;
   }
-  b.e_run = E.bag ? te->lv[E.n_levels - 1].offs.p : nullptr;
+  b.e_run = run_offsets(te);
+  b.nnz_e = E.n_levels == 2 ? te->lv[1].n : 0;
   b.e_val = (b.sum && E.anno >= 0) ? te->annos[E.anno].p : nullptr;
   b.lsb = p->exact_lsb;
   b.D = p->exact_digits;
@@ -957,9 +1116,8 @@ void attach_transpose(BInst& b, const lh_plan_t* p, Transposes& tr, hipStream_t 
   b.bt_k = t->lv[0].keys.p;
   b.bt_off = t->lv[0].offs.p;
   b.bt_j = t->lv[1].keys.p;
-  b.bt_run = t->lv[1].offs.p;
+  b.bt_run = run_offsets(t);
   b.bt_val = anno >= 0 ? t->annos[0].p : nullptr;
-  b.nnz_e = t->lv[1].n;
 }
 
 std::string cache_path() {
@@ -969,16 +1127,28 @@ std::string cache_path() {
   return std::string(h ? h : "/tmp") + "/.cache/lh_autotune.txt";
 }
 
-std::string signature(const BatchState& b) {
-  hipDeviceProp_t prop;
+// "<arch>_cu<CUs>" of the current device (its properties are asked for once).
+std::string device_name() {
+  static std::mutex mu;
+  static std::map<int, std::string> names;
   int dev = 0;
   (void)hipGetDevice(&dev);
-  (void)hipGetDeviceProperties(&prop, dev);
+  std::lock_guard<std::mutex> lk(mu);
+  auto it = names.find(dev);
+  if (it == names.end()) {
+    hipDeviceProp_t prop;
+    (void)hipGetDeviceProperties(&prop, dev);
+    it = names.emplace(dev, std::string(prop.gcnArchName) + "_cu" + std::to_string(prop.multiProcessorCount)).first;
+  }
+  return it->second;
+}
+
+std::string signature(const BatchState& b) {
   std::ostringstream os;
   uint64_t rows_log = 0, ub_log = 0;
   while ((1ull << rows_log) < b.R) rows_log++;
   while ((1ull << ub_log) < b.UB) ub_log++;
-  os << "v4_" << prop.gcnArchName << "_cu" << prop.multiProcessorCount << "_inst" << b.plans.size() << "_r" << rows_log
+  os << "v5_" << device_name() << "_inst" << b.plans.size() << "_r" << rows_log
      << "_u" << ub_log;
   return os.str();
 }
@@ -1004,15 +1174,15 @@ void save_tuning(const std::string& sig, const Tuning& t) {
   f << sig << " " << t.light_max << " " << t.blocks_per_cu << " " << t.inner_ratio << "\n";
 }
 
-void setup(BatchState& b, hipStream_t s) {
+// What the plans alone decide: instances, rows, products, output bounds.
+void setup_rows(BatchState& b, hipStream_t s) {
   const uint32_t n = (uint32_t)b.plans.size();
   b.s = s;
   b.h_inst.resize(n);
   b.h_inst_row0.assign(n + 1, 0);
-  if (!b.tr) b.tr = std::make_shared<Transposes>();
+  b.tr = std::make_shared<Transposes>();
   for (uint32_t i = 0; i < n; i++) {
     b.h_inst[i] = describe(b.plans[i]);
-    if (b.h_inst[i].kind == 1) attach_transpose(b.h_inst[i], b.plans[i], *b.tr, s);
     b.h_inst[i].row_base = b.h_inst_row0[i];
     b.h_inst_row0[i + 1] = b.h_inst_row0[i] + b.h_inst[i].n_rows;
   }
@@ -1022,66 +1192,95 @@ void setup(BatchState& b, hipStream_t s) {
   LH_HIP(hipMemcpyAsync(b.inst.p, b.h_inst.data(), n * sizeof(BInst), hipMemcpyHostToDevice, s));
   b.inst_row0.alloc(n + 1, s);
   LH_HIP(hipMemcpyAsync(b.inst_row0.p, b.h_inst_row0.data(), (n + 1) * sizeof(uint64_t), hipMemcpyHostToDevice, s));
+  k_inst_roots<<<1, 256, 0, s>>>(b.inst.p, n);
+  LH_HIP(hipGetLastError());
   b.row_inst.alloc(b.R, s);
   b.prod.alloc(b.R, s);
   b.ub.alloc(b.R, s);
-  b.heavy_f.alloc(b.R, s);
-  b.light_f.alloc(b.R, s);
-  b.inner_f.alloc(b.R, s);
   if (b.R) {
-    k_row_setup<<<grid_for(b.R), 256, 0, s>>>(b.inst.p, b.inst_row0.p, n, b.R, b.tune.light_max, b.tune.inner_ratio,
-                                              b.row_inst.p, b.prod.p, b.ub.p, b.heavy_f.p, b.light_f.p, b.inner_f.p);
+    k_row_products<<<(unsigned)std::min<uint64_t>((b.R + B_NT - 1) / B_NT, 1u << 16), B_NT, 0, s>>>(
+        b.inst.p, b.inst_row0.p, n, b.R, b.row_inst.p, b.prod.p, b.ub.p);
     LH_HIP(hipGetLastError());
   }
   b.ub_off.alloc(b.R + 1, s);
-  b.UB = scan_u32_to_u64(b.ub.p, b.ub_off.p, b.R, s);
   b.h_nj.assign(n, 0);
+  DBuf<uint64_t> dnj(n, s);
   if (n) {
-    DBuf<uint64_t> dnj(n, s);
     k_inst_sums<<<n, B_NT, 0, s>>>(b.prod.p, b.inst_row0.p, dnj.p);
     LH_HIP(hipGetLastError());
     LH_HIP(hipMemcpyAsync(b.h_nj.data(), dnj.p, n * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-    LH_HIP(hipStreamSynchronize(s));
   }
+  b.UB = scan_u32_to_u64(b.ub.p, b.ub_off.p, b.R, s);
+  b.heavy_f.alloc(b.R, s);
+  b.light_f.alloc(b.R, s);
+  b.inner_f.alloc(b.R, s);
   b.heavy.alloc(b.R, s);
   b.light.alloc(b.R, s);
-  b.n_heavy = select_flagged(b.heavy_f.p, b.R, b.heavy.p, s);
-  b.n_light = select_flagged(b.light_f.p, b.R, b.light.p, s);
   b.inner.alloc(b.R, s);
-  b.n_inner = select_flagged(b.inner_f.p, b.R, b.inner.p, s);   // in row order: grouped by instance
-  // heavy rows longest first (LPT): sort their ids by descending product count
-  if (b.n_heavy > 1) {
-    DBuf<uint64_t> key(b.n_heavy, s), tk(b.n_heavy, s);
-    DBuf<uint32_t> tv(b.n_heavy, s);
-    std::vector<uint32_t> hrows(b.n_heavy);
-    std::vector<uint64_t> hp(b.R);
-    LH_HIP(hipMemcpyAsync(hrows.data(), b.heavy.p, b.n_heavy * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    LH_HIP(hipMemcpyAsync(hp.data(), b.prod.p, b.R * sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-    LH_HIP(hipStreamSynchronize(s));
-    std::stable_sort(hrows.begin(), hrows.end(), [&](uint32_t x, uint32_t y) { return hp[x] > hp[y]; });
-    LH_HIP(hipMemcpyAsync(b.heavy.p, hrows.data(), b.n_heavy * sizeof(uint32_t), hipMemcpyHostToDevice, s));
-  }
-  b.qhead.alloc(3, s);
+  b.qhead.alloc(4, s);
+  b.has_vec = false;
+  for (const BInst& I : b.h_inst) b.has_vec = b.has_vec || I.kind == 0;
+  b.longs.alloc(b.has_vec ? b.R : 0, s);
   b.row_nnz.alloc(b.R, s);
   b.ub_k.alloc(b.UB, s);
   b.ub_cnt.alloc(b.UB, s);
   b.ub_sum.alloc(b.UB, s);
   b.err.alloc(1, s);
   // heavy rows: the window of k values their bitmap covers
-  {
-    uint32_t nk = 0;
-    for (const BInst& I : b.h_inst)
-      if (I.kind == 1) nk = std::max(nk, I.n_k);
-    b.kw = std::max<uint32_t>(64, std::min<uint32_t>(KW_MAX, (nk + 63) / 64 * 64));
+  uint32_t nk = 0;
+  for (const BInst& I : b.h_inst)
+    if (I.kind == 1) nk = std::max(nk, I.n_k);
+  b.kw = std::max<uint32_t>(64, std::min<uint32_t>(KW_MAX, (nk + 63) / 64 * 64));
+}
+
+// What the tuning decides as well: row classes, their queues, and E
+// transposed for the instances that have inner-product rows.
+void setup_classes(BatchState& b, hipStream_t s) {
+  const uint32_t n = (uint32_t)b.plans.size();
+  b.n_heavy = b.n_light = b.n_inner = 0;
+  if (!b.R) return;
+  DBuf<uint32_t> has_inner(n, s);
+  fill_u32(has_inner.p, 0, n, s);
+  k_row_classes<<<grid_for(b.R), 256, 0, s>>>(b.inst.p, b.row_inst.p, b.prod.p, b.R, b.tune.light_max,
+                                              b.tune.inner_ratio, b.heavy_f.p, b.light_f.p, b.inner_f.p, has_inner.p);
+  LH_HIP(hipGetLastError());
+  std::vector<uint32_t> h(n);
+  LH_HIP(hipMemcpyAsync(h.data(), has_inner.p, n * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+  b.n_heavy = select_flagged(b.heavy_f.p, b.R, b.heavy.p, s);
+  b.n_light = select_flagged(b.light_f.p, b.R, b.light.p, s);
+  b.n_inner = select_flagged(b.inner_f.p, b.R, b.inner.p, s);   // in row order: grouped by instance
+  if (b.n_inner) {
+    bool added = false;
+    for (uint32_t i = 0; i < n; i++)
+      if (h[i] && !b.h_inst[i].bt_k) {
+        attach_transpose(b.h_inst[i], b.plans[i], *b.tr, s);
+        added = true;
+      }
+    if (added) {
+      LH_HIP(hipMemcpyAsync(b.inst.p, b.h_inst.data(), n * sizeof(BInst), hipMemcpyHostToDevice, s));
+      k_inst_roots<<<1, 256, 0, s>>>(b.inst.p, n);
+      LH_HIP(hipGetLastError());
+    }
   }
-  LH_HIP(hipStreamSynchronize(s));
+  if (b.n_heavy > 1) {
+    // heavy rows longest first (LPT)
+    DBuf<uint64_t> k0(b.n_heavy, s), k1(b.n_heavy, s);
+    DBuf<uint32_t> other(b.n_heavy, s);
+    k_heavy_keys<<<grid_for(b.n_heavy), 256, 0, s>>>(b.heavy.p, b.n_heavy, b.prod.p, k0.p);
+    LH_HIP(hipGetLastError());
+    uint64_t* const kb[2] = {k0.p, k1.p};
+    uint32_t* const vb[2] = {b.heavy.p, other.p};
+    if (radix_sort_between(kb, vb, b.n_heavy, HEAVY_KEY_BITS, s))
+      LH_HIP(hipMemcpyAsync(b.heavy.p, other.p, b.n_heavy * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
+  }
+  LH_HIP(hipStreamSynchronize(s));  // the host's arrays were read
 }
 
 void launch_compute(BatchState& b, hipStream_t s) {
   int dev = 0, cus = 256;
   (void)hipGetDevice(&dev);
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  k_fill_u32_dev<<<1, 64, 0, s>>>(b.qhead.p, 0u, 3);
+  k_fill_u32_dev<<<1, 64, 0, s>>>(b.qhead.p, 0u, 4);
   k_fill_u32_dev<<<1, 64, 0, s>>>(b.err.p, 0u, 1);
   BatchArgs a{};
   a.inst = b.inst.p;
@@ -1103,13 +1302,22 @@ void launch_compute(BatchState& b, hipStream_t s) {
   a.prod = b.prod.p;
   a.kw = b.kw;
   const unsigned grid = (unsigned)(cus * std::min(b.tune.blocks_per_cu, MAX_BLOCKS_PER_CU));
-  if (b.n_inner) k_batch_inner<<<grid, B_NT, 0, s>>>(a);
+  if (b.n_inner) k_batch_inner<<<grid, I_NT, 0, s>>>(a);
   if (b.n_heavy) k_batch_heavy<<<grid, B_NT, 0, s>>>(a);
+  if (b.has_vec && b.R) {
+    k_batch_vec<<<(unsigned)std::min<uint64_t>((b.R * 8 + B_NT - 1) / B_NT, 1u << 16), B_NT, 0, s>>>(a, b.R, b.longs.p);
+    k_batch_vec_long<<<(unsigned)(4 * cus), B_NT, 0, s>>>(a, b.longs.p);
+  }
+  if (!b.n_light) return;
   if (b.tune.light_max <= 64) k_batch_light<128><<<grid, B_NT, 0, s>>>(a);
   else k_batch_light<256><<<grid, B_NT, 0, s>>>(a);
 }
 
 void build_graph(BatchState& b) {
+  if (b.exec) (void)hipGraphExecDestroy(b.exec);
+  if (b.graph) (void)hipGraphDestroy(b.graph);
+  b.exec = nullptr;
+  b.graph = nullptr;
   if (!b.cap) LH_HIP(hipStreamCreateWithFlags(&b.cap, hipStreamNonBlocking));
   LH_HIP(hipStreamBeginCapture(b.cap, hipStreamCaptureModeThreadLocal));
   launch_compute(b, b.cap);
@@ -1135,76 +1343,35 @@ float time_replay(BatchState& b, hipStream_t s) {
 
 // The project's autotuner: time each candidate's graph, keep the fastest,
 // remember it per device and batch signature.  The light/heavy split and
-// the inner-product ratio change the setup (row classes and queues); the
-// grid only changes the captured launch, so it is tried on each setup.
-// Only the best setup so far is kept alive (each holds the output bounds).
-void autotune(std::unique_ptr<BatchState>& cur, lh_plan_t* const* plans, uint32_t n, hipStream_t s) {
-  const std::string sig = signature(*cur);
-  Tuning t;
-  if (load_tuning(sig, t)) {
-    if (t.light_max != cur->tune.light_max || t.blocks_per_cu != cur->tune.blocks_per_cu ||
-        t.inner_ratio != cur->tune.inner_ratio) {
-      auto nb = std::make_unique<BatchState>();
-      nb->plans = cur->plans;
-      nb->tr = cur->tr;
-      nb->tune = t;
-      cur.reset();
-      setup(*nb, s);
-      build_graph(*nb);
-      cur = std::move(nb);
-    }
+// the inner-product ratio change the row classes and queues; the grid only
+// changes the captured launch, so it is tried on each of them.
+void autotune(BatchState& b, hipStream_t s) {
+  const std::string sig = signature(b);
+  if (load_tuning(sig, b.tune)) {
+    setup_classes(b, s);
     return;
   }
-  const uint32_t lights[] = {64, 128};
-  const uint32_t ratios[] = {4, 16, 64};
-  const uint32_t bpcs[] = {1, 2, 4};
-  const std::vector<const lh_plan_t*> pv(plans, plans + n);
-  std::shared_ptr<Transposes> tr = cur->tr;
   float best = 3.0e38f;
-  std::unique_ptr<BatchState> winner;
-  for (uint32_t lm : lights)
-    for (uint32_t ir : ratios) {
-      std::unique_ptr<BatchState> cand;
-      if (cur && lm == cur->tune.light_max && ir == cur->tune.inner_ratio) {
-        cand = std::move(cur);
-      } else {
-        cand = std::make_unique<BatchState>();
-        cand->plans = pv;
-        cand->tr = tr;
-        cand->tune.light_max = lm;
-        cand->tune.inner_ratio = ir;
-        setup(*cand, s);
-      }
-      float cand_best = 3.0e38f;
-      uint32_t cand_bp = cand->tune.blocks_per_cu;
-      for (uint32_t bp : bpcs) {
-        if (cand->exec) (void)hipGraphExecDestroy(cand->exec);
-        if (cand->graph) (void)hipGraphDestroy(cand->graph);
-        cand->exec = nullptr;
-        cand->graph = nullptr;
-        cand->tune.blocks_per_cu = bp;
-        build_graph(*cand);
-        const float ms = time_replay(*cand, s);
-        if (ms < cand_best) {
-          cand_best = ms;
-          cand_bp = bp;
+  Tuning win = b.tune;
+  for (uint32_t lm : {64u, 128u})
+    for (uint32_t ir : {4u, 16u, 64u}) {
+      b.tune.light_max = lm;
+      b.tune.inner_ratio = ir;
+      setup_classes(b, s);
+      for (uint32_t bp : {1u, 2u, 4u}) {
+        b.tune.blocks_per_cu = bp;
+        build_graph(b);
+        const float ms = time_replay(b, s);
+        if (ms < best) {
+          best = ms;
+          win = b.tune;
         }
       }
-      if (cand->tune.blocks_per_cu != cand_bp) {
-        (void)hipGraphExecDestroy(cand->exec);
-        (void)hipGraphDestroy(cand->graph);
-        cand->exec = nullptr;
-        cand->graph = nullptr;
-        cand->tune.blocks_per_cu = cand_bp;
-        build_graph(*cand);
-      }
-      if (cand_best < best) {
-        best = cand_best;
-        winner = std::move(cand);
-      }
     }
-  save_tuning(sig, winner->tune);
-  cur = std::move(winner);
+  b.tune = win;
+  setup_classes(b, s);
+  build_graph(b);
+  save_tuning(sig, win);
 }
 
 struct SharedOut {
@@ -1247,15 +1414,18 @@ bool run_batch(lh_plan_t* const* plans, uint32_t n, hipStream_t s, std::vector<l
     g_batch.reset();
     auto b = std::make_unique<BatchState>();
     b->plans = pv;
-    setup(*b, s);
-    build_graph(*b);
-    autotune(b, plans, n, s);
+    setup_rows(*b, s);
+    autotune(*b, s);
     g_batch = std::move(b);
+  } else if (!g_batch->exec) {
+    build_graph(*g_batch);  // plans that come again are replayed
   }
   BatchState& b = *g_batch;
   {
     ProfScope ps("batch_graph", s, b.R, b.UB);
-    LH_HIP(hipGraphLaunch(b.exec, s));
+    if (b.exec) LH_HIP(hipGraphLaunch(b.exec, s));
+    else launch_compute(b, s);
+    LH_HIP(hipGetLastError());
   }
   // pack: scan the per-row output counts, one shared output block
   DBuf<uint64_t> out_off(b.R + 1, s);
@@ -1280,9 +1450,11 @@ bool run_batch(lh_plan_t* const* plans, uint32_t n, hipStream_t s, std::vector<l
   pa.out_cnt = sh->out_cnt.p;
   pa.out_sum = sh->out_sum.p;
   pa.R = b.R;
-  if (b.R) {
+  if (total) {
     ProfScope ps("batch_pack", s, b.R, total);
-    k_pack_rows<<<grid_for(b.R), 256, 0, s>>>(pa);
+    const uint64_t per = (uint64_t)PACK_SPAN * B_NW;
+    if (total / per >= (1ull << 31)) fail(LH_ERR_OVERFLOW, "batch: too many output rows");
+    k_pack_rows<<<(unsigned)((total + per - 1) / per), B_NT, 0, s>>>(pa, total);
     LH_HIP(hipGetLastError());
   }
   // each instance's rows are contiguous: its outputs are [offs[i], offs[i + 1])

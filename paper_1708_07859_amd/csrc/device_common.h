@@ -108,6 +108,38 @@ __device__ __forceinline__ T block_sum(T v, T* lds) {
   return total;
 }
 
+__device__ __forceinline__ void wave_lds_sync() {
+  // LDS operations of one wave complete in order; this keeps the compiler
+  // from moving them across the point where lanes read what others wrote
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// v of the lane that a DPP control names (a register move, no LDS trip).
+template <int CTRL, class T>
+__device__ __forceinline__ T dpp64(T v) {
+  static_assert(sizeof(T) == 8, "dpp64");
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)((uint64_t)v >> 32), CTRL, 0xf, 0xf, true);
+  return (T)(((uint64_t)hi << 32) | lo);
+}
+
+// Sum over the LPR consecutive lanes of a unit; every lane gets it.
+template <int LPR, class T>
+__device__ __forceinline__ T unit_sum(T v) {
+  if constexpr (LPR == 8) {
+    v += dpp64<0xB1>(v);    // quad_perm [1,0,3,2]
+    v += dpp64<0x4E>(v);    // quad_perm [2,3,0,1]: every lane holds its quad's sum
+    v += dpp64<0x141>(v);   // row_half_mirror: the other quad's
+    return v;
+  } else {
+#pragma unroll
+    for (int d = LPR / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, WAVE);
+    return v;
+  }
+}
+
 // Largest index i in [lo, hi) with a[i] <= x, given a non-decreasing array
 // whose a[lo] <= x (a load-balanced-search helper).
 template <class T>

@@ -148,14 +148,6 @@ __device__ __forceinline__ uint32_t sampled_lower_bound(const uint32_t* keys, co
   return keys[pos] < x ? pos + 1 : pos;
 }
 
-__device__ __forceinline__ void wave_lds_sync() {
-  // LDS operations of one wave complete in order; this keeps the compiler
-  // from moving them across the point where lanes read what others wrote
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Membership of x in set [b, e) (descriptor sidx); its position if asked.
 __device__ __forceinline__ bool dset_find(const DSet& st, uint32_t b, uint32_t e, uint64_t sidx, uint32_t x,
                                           bool need_pos, uint32_t& pos) {
@@ -505,30 +497,6 @@ __device__ __forceinline__ bool next_combo(const LeafArgs& L, const HitRows<NA>&
     }
   }
   return !carry;
-}
-
-// v of the lane that a DPP control names (a register move, no LDS trip).
-template <int CTRL, class T>
-__device__ __forceinline__ T dpp64(T v) {
-  static_assert(sizeof(T) == 8, "dpp64");
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, 0xf, 0xf, true);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)((uint64_t)v >> 32), CTRL, 0xf, 0xf, true);
-  return (T)(((uint64_t)hi << 32) | lo);
-}
-
-// Sum over the LPR consecutive lanes of a unit; every lane gets it.
-template <int LPR, class T>
-__device__ __forceinline__ T unit_sum(T v) {
-  if constexpr (LPR == 8) {
-    v += dpp64<0xB1>(v);    // quad_perm [1,0,3,2]
-    v += dpp64<0x4E>(v);    // quad_perm [2,3,0,1]: every lane holds its quad's sum
-    v += dpp64<0x141>(v);   // row_half_mirror: the other quad's
-    return v;
-  } else {
-#pragma unroll
-    for (int d = LPR / 2; d > 0; d >>= 1) v += __shfl_xor(v, d, WAVE);
-    return v;
-  }
 }
 
 // A unit's carried count and sum into its group's slots: stored when `only`
@@ -2497,7 +2465,7 @@ lh_result_impl* run_full(const lh_plan_t* p, hipStream_t s) {
     for (uint32_t e = 0; e < na; e++) {
       const PlanAtom& A = p->atoms[e];
       fa.pos[e] = F.pos[e].p;
-      fa.run[e] = A.bag ? A.trie->lv[A.n_levels - 1].offs.p : nullptr;
+      fa.run[e] = run_offsets(A.trie);
     }
     k_full_counts<<<grid_for(n), 256, 0, s>>>(fa, n);
     LH_HIP(hipGetLastError());
@@ -2610,7 +2578,7 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
     for (uint32_t i = 0; i < p->parts[leaf].size(); i++)
       if (p->parts[leaf][i].atom == e) LA.part = (int32_t)i;
     LA.pos = F.pos[e].p;
-    LA.run = A.bag ? A.trie->lv[A.n_levels - 1].offs.p : nullptr;
+    LA.run = run_offsets(A.trie);
     LA.anno = (is_sum && A.anno >= 0) ? A.trie->annos[A.anno].p : nullptr;
     LA.gmeta = nullptr;
     for (uint32_t g = 0; g < ngc; g++)

@@ -303,6 +303,14 @@ inline const uint32_t* row_keys(const lh_trie* t, uint32_t l) {
   return (!(t->flags & LH_BAG) && l + 1 == t->n_levels) ? t->lv[l].keys.p : t->skeys[l].p;
 }
 
+// Run offsets of a bag trie's last level, or null where every node has one
+// row (a set, or a bag without repeated key tuples): node and row positions
+// are then the same, and nobody reads offsets to find that out.
+inline const uint32_t* run_offsets(const lh_trie* t) {
+  const Level& last = t->lv[t->n_levels - 1];
+  return (t->flags & LH_BAG) && t->n_rows != last.n ? last.offs.p : nullptr;
+}
+
 constexpr uint32_t TRIE_MAGIC = 0x54524945u;
 constexpr uint32_t PLAN_MAGIC = 0x504c414eu;
 constexpr uint32_t RESULT_MAGIC = 0x52534c54u;
