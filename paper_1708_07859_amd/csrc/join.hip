@@ -235,8 +235,10 @@ constexpr uint32_t GLDS_MAX = 256;
 struct ElemArgs {
   uint32_t np;
   DSet set[MAXP];
-  const uint64_t* W;      // exclusive scan of per-row work, nrows + 1 entries
+  const uint32_t* work;   // driver elements of each row
   const uint8_t* drv;     // driving participant of each row
+  uint32_t single;        // the only row is the empty binding (the first attribute): its work is
+  uint32_t drv0;          //   `total` and its driver drv0, known to the host
   uint64_t nrows;
   uint64_t total;
   const uint64_t* U;      // exclusive scan of per-row work units, nrows + 1 entries
@@ -295,22 +297,29 @@ constexpr uint8_t DRV_AND = 0xff;
 // (MERGE_TILE merged elements per unit).
 constexpr uint8_t DRV_MERGE = 0xfe;
 
+// What a depth's rows add up to: work units, driver elements, and a two-set
+// leaf's units of the top bucket and of merged rows.
+struct WorkTotals {
+  uint64_t units, work, top, merge;
+};
+
 // leaf2: the row's two sets feed the two-set leaf (word-AND and merge
-// allowed; top-bucket rows get units of TOP_EL elements, counted into
-// n_units[0]; merged rows units of MERGE_TILE, counted into n_units[1]).
-__global__ void k_work(WorkArgs a, uint64_t nrows, uint32_t* work, uint8_t* drv, uint32_t* units, uint32_t unit_el,
-                       uint32_t leaf2, unsigned long long* n_units) {
+// allowed; top-bucket rows get units of TOP_EL elements, merged rows units
+// of MERGE_TILE).  Each block writes its part of the totals.
+template <int NP>
+__global__ __launch_bounds__(256) void k_work(WorkArgs a, uint64_t nrows, uint32_t* work, uint8_t* drv, uint32_t* units,
+                                              uint32_t unit_el, uint32_t leaf2, WorkTotals* part) {
   __shared__ uint64_t s_red[256 / WAVE];
-  uint64_t top_units = 0, merge_units = 0;
+  uint64_t top_units = 0, merge_units = 0, all_work = 0;
   for (uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; r < nrows; r += (uint64_t)gridDim.x * blockDim.x) {
     // Driver: the set whose elements are cheapest to stream and probe into
     // the others; probing a bitset costs one word load, probing a sorted
     // uint array a binary search of ~log2(card) loads.
-    uint32_t card[MAXP];
-    float probe[MAXP];
+    uint32_t card[NP];
+    float probe[NP];
     uint32_t bi = 0;
 #pragma unroll
-    for (int p = 0; p < MAXP; p++) {
+    for (int p = 0; p < NP; p++) {
       card[p] = 0;
       probe[p] = 1.0f;
       if (p >= (int)a.np) continue;
@@ -323,11 +332,11 @@ __global__ void k_work(WorkArgs a, uint64_t nrows, uint32_t* work, uint8_t* drv,
     }
     float best_cost = 3.0e38f;
 #pragma unroll
-    for (int p = 0; p < MAXP; p++) {
+    for (int p = 0; p < NP; p++) {
       if (p >= (int)a.np) continue;
       float c = 0.0f;
 #pragma unroll
-      for (int q = 0; q < MAXP; q++)
+      for (int q = 0; q < NP; q++)
         if (q < (int)a.np && q != p) c += probe[q];
       c = (float)card[p] * (c + 1.0f);
       if (c < best_cost) {
@@ -338,7 +347,7 @@ __global__ void k_work(WorkArgs a, uint64_t nrows, uint32_t* work, uint8_t* drv,
     uint32_t best = 0;
     bool empty = false;
 #pragma unroll
-    for (int p = 0; p < MAXP; p++) {
+    for (int p = 0; p < NP; p++) {
       if (p == (int)bi) best = card[p];
       if (p < (int)a.np && card[p] == 0) empty = true;
     }
@@ -382,6 +391,7 @@ __global__ void k_work(WorkArgs a, uint64_t nrows, uint32_t* work, uint8_t* drv,
       }
     }
     work[r] = best;
+    all_work += best;
     drv[r] = dv;
     const bool top = leaf2 && a.np == 2 && dv != DRV_MERGE && (uint64_t)card[0] + card[1] >= TOP_MIN;
     if (top) {
@@ -392,12 +402,30 @@ __global__ void k_work(WorkArgs a, uint64_t nrows, uint32_t* work, uint8_t* drv,
     if (top) top_units += units[r];
     if (dv == DRV_MERGE) merge_units += units[r];
   }
-  if (n_units) {
-    const uint64_t t = block_sum<uint64_t, 256>(top_units, s_red);
-    if (threadIdx.x == 0 && t) atomicAdd(&n_units[0], (unsigned long long)t);
-    const uint64_t m = block_sum<uint64_t, 256>(merge_units, s_red);
-    if (threadIdx.x == 0 && m) atomicAdd(&n_units[1], (unsigned long long)m);
+  const uint64_t w = block_sum<uint64_t, 256>(all_work, s_red);
+  uint64_t t = 0, m = 0;
+  if (leaf2) {
+    t = block_sum<uint64_t, 256>(top_units, s_red);
+    m = block_sum<uint64_t, 256>(merge_units, s_red);
   }
+  if (threadIdx.x == 0) part[blockIdx.x] = WorkTotals{0, w, t, m};
+}
+
+// The blocks' parts added up by one block, with the units' scan total.
+__global__ __launch_bounds__(256) void k_work_totals(const WorkTotals* part, uint32_t nb, const uint64_t* units,
+                                                     WorkTotals* out) {
+  __shared__ uint64_t s_red[256 / WAVE];
+  WorkTotals v{0, 0, 0, 0};
+  for (uint32_t i = threadIdx.x; i < nb; i += 256) {
+    v.work += part[i].work;
+    v.top += part[i].top;
+    v.merge += part[i].merge;
+  }
+  v.work = block_sum<uint64_t, 256>(v.work, s_red);
+  v.top = block_sum<uint64_t, 256>(v.top, s_red);
+  v.merge = block_sum<uint64_t, 256>(v.merge, s_red);
+  v.units = *units;
+  if (threadIdx.x == 0) *out = v;
 }
 
 // Rows of a leaf hit: for each atom, the range of rows of its leaf node.
@@ -606,10 +634,14 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
     // the unit's row and chunk (uniform across its lanes)
     uint64_t r = 0;
     uint32_t chunk = 0, work = 0, d = 0;
-    if (unit_valid) {
+    if (unit_valid && a.single) {
+      chunk = (uint32_t)u;
+      work = (uint32_t)a.total;
+      d = a.drv0;
+    } else if (unit_valid) {
       r = a.urow[u];
       chunk = (uint32_t)(u - a.U[r]);
-      work = (uint32_t)(a.W[r + 1] - a.W[r]);
+      work = a.work[r];
       d = a.drv[r];
     }
     uint32_t b[NP], e[NP];
@@ -679,7 +711,8 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
       for (int it = 0; it < U_IT; it++) wc += (uint32_t)__popcll(ballot(hit[it]));
       if (lane == 0) s_wcnt[w] = wc;
       __syncthreads();
-      uint64_t off = a.blk_off[vb];
+      // (no counts: one participant, every element of the single row a hit)
+      uint64_t off = a.blk_off ? a.blk_off[vb] : vb * J_NW * UPW * UNIT_EL;
       for (int j = 0; j < w; j++) off += s_wcnt[j];
       // the wave's units one after another: hits of the units below first
       const int u0 = lane - ul;
@@ -1051,26 +1084,47 @@ void launch_elem(const ElemArgs& a, unsigned grid, hipStream_t s) {
 }
 
 // Row of every work unit.  A thread writes up to UROW_SMALL units of its
-// row; rows with more are listed and finished by whole blocks.
+// row; rows with more are finished by its whole block.  Where the average
+// row has more, the block would be short of threads: k_unit_search.
 constexpr uint64_t UROW_SMALL = 16;
 
-__global__ void k_unit_rows(const uint64_t* U, uint64_t nrows, uint32_t* urow, uint32_t* big, uint32_t* nbig) {
-  for (uint64_t r = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; r < nrows; r += (uint64_t)gridDim.x * blockDim.x) {
-    const uint64_t u0 = U[r];
-    uint64_t u1 = U[r + 1];
-    if (u1 - u0 > UROW_SMALL) {
-      big[atomicAdd(nbig, 1u)] = (uint32_t)r;
-      u1 = u0 + UROW_SMALL;
+__global__ __launch_bounds__(256) void k_unit_rows(const uint64_t* U, uint64_t nrows, uint32_t* urow) {
+  __shared__ uint32_t s_big[256];
+  __shared__ uint32_t s_n;
+  for (uint64_t r0 = (uint64_t)blockIdx.x * 256; r0 < nrows; r0 += (uint64_t)gridDim.x * 256) {
+    if (threadIdx.x == 0) s_n = 0;
+    __syncthreads();
+    const uint64_t r = r0 + threadIdx.x;
+    if (r < nrows) {
+      const uint64_t u0 = U[r];
+      uint64_t u1 = U[r + 1];
+      if (u1 - u0 > UROW_SMALL) {
+        s_big[atomicAdd(&s_n, 1u)] = (uint32_t)r;
+        u1 = u0 + UROW_SMALL;
+      }
+      for (uint64_t u = u0; u < u1; u++) urow[u] = (uint32_t)r;
     }
-    for (uint64_t u = u0; u < u1; u++) urow[u] = (uint32_t)r;
+    __syncthreads();
+    for (uint32_t i = 0; i < s_n; i++) {
+      const uint32_t b = s_big[i];
+      for (uint64_t u = U[b] + UROW_SMALL + threadIdx.x; u < U[b + 1]; u += 256) urow[u] = b;
+    }
+    __syncthreads();
   }
 }
 
-__global__ void k_unit_rows_big(const uint64_t* U, const uint32_t* big, const uint32_t* nbig, uint32_t* urow) {
-  const uint32_t nb = *nbig;
-  for (uint32_t i = blockIdx.x; i < nb; i += gridDim.x) {
-    const uint32_t r = big[i];
-    for (uint64_t u = U[r] + UROW_SMALL + threadIdx.x; u < U[r + 1]; u += blockDim.x) urow[u] = r;
+// The same by search: a thread looks for its unit's row (few rows, so the
+// offsets stay in the cache).
+__global__ __launch_bounds__(256) void k_unit_search(const uint64_t* U, uint64_t nrows, uint64_t units,
+                                                     uint32_t* urow) {
+  for (uint64_t u = (uint64_t)blockIdx.x * 256 + threadIdx.x; u < units; u += (uint64_t)gridDim.x * 256) {
+    uint64_t lo = 0, n = nrows;  // the last row that starts at or before u
+    while (n > 1) {
+      const uint64_t h = n / 2;
+      if (U[lo + h] <= u) lo += h;
+      n -= h;
+    }
+    urow[u] = (uint32_t)lo;
   }
 }
 
@@ -1712,11 +1766,6 @@ __global__ __launch_bounds__(M_NT) void k_leaf2_merge(Leaf2Args a, const MergeTi
 
 // ---- finalization ------------------------------------------------------------
 
-__global__ void k_nonzero_flags(const uint64_t* cnt, uint64_t n, uint32_t* flags) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-    flags[i] = cnt[i] != 0 ? 1u : 0u;
-}
-
 __global__ void k_tag_flags(const uint32_t* tag, uint64_t n, uint32_t* flags) {
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
     flags[i] = tag[i] == SLOT_READY ? 1u : 0u;
@@ -1836,10 +1885,10 @@ __device__ __forceinline__ uint64_t finish_group(const GroupFin& f, uint64_t slo
   return c;
 }
 
-__device__ __forceinline__ void add_join_tuples(const GroupFin& f, uint64_t c) {
+__device__ __forceinline__ void add_join_tuples(uint64_t* n_join, uint64_t c) {
   __shared__ uint64_t s_red[GU_NT / WAVE];
   const uint64_t t = block_sum<uint64_t, GU_NT>(c, s_red);
-  if (threadIdx.x == 0 && t) atomicAdd((unsigned long long*)f.n_join, (unsigned long long)t);
+  if (threadIdx.x == 0 && t) atomicAdd((unsigned long long*)n_join, (unsigned long long)t);
 }
 
 // Dense GROUP BY: a non-empty index becomes the next output row; its keys
@@ -1859,7 +1908,7 @@ __global__ __launch_bounds__(GU_NT) void k_dense_finalize(GroupFin f, uint64_t n
     }
     sum += finish_group(f, i, at[j]);
   }
-  add_join_tuples(f, sum);
+  add_join_tuples(f.n_join, sum);
 }
 
 // Hash GROUP BY: output row i is the i-th group in key order.
@@ -1879,13 +1928,14 @@ __global__ __launch_bounds__(GU_NT) void k_hash_finalize(GroupFin f, uint64_t n)
     }
     sum += finish_group(f, slot, i);
   }
-  add_join_tuples(f, sum);
+  add_join_tuples(f.n_join, sum);
 }
 
 struct FinA {
   const uint64_t* gcount;
   const int64_t* gacc;
-  const uint64_t* off;      // exclusive scan of nonzero flags (null: keep all)
+  const uint64_t* off;      // output rows before each tile of GU_TILE groups (null: keep all)
+  uint64_t* n_join;         // all counts together (cleared before), or null
   uint32_t n_cols;
   const uint32_t* key_in[MAXV];
   uint32_t* key_out[MAXV];
@@ -1898,18 +1948,47 @@ struct FinA {
   uint32_t* err;
 };
 
-__global__ void k_finalize_groups(FinA f, uint64_t n) {
-  for (uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n; g += (uint64_t)gridDim.x * blockDim.x) {
-    uint64_t o = g;
-    if (f.off) {
-      if (f.off[g + 1] == f.off[g]) continue;
-      o = f.off[g];
+// A block takes a tile of groups; those without a tuple leave no row.
+__global__ __launch_bounds__(GU_NT) void k_finalize_groups(FinA f, uint64_t n) {
+  uint64_t at[GU_ITEMS], sum = 0;
+  uint32_t mask = 0;
+  const uint64_t base = (uint64_t)blockIdx.x * GU_TILE;
+  if (f.off) {
+    mask = used_ranks(DenseUsed{reinterpret_cast<const int64_t*>(f.gcount), 1}, n, f.off, at);
+  } else {
+#pragma unroll
+    for (int j = 0; j < GU_ITEMS; j++) {
+      at[j] = base + (uint64_t)j * GU_NT + threadIdx.x;
+      if (at[j] < n) mask |= 1u << j;
     }
+  }
+#pragma unroll
+  for (int j = 0; j < GU_ITEMS; j++) {
+    if (!(mask >> j & 1u)) continue;
+    const uint64_t g = base + (uint64_t)j * GU_NT + threadIdx.x, o = at[j];
     for (uint32_t c = 0; c < f.n_cols; c++) f.key_out[c][o] = f.key_in[c][g];
-    f.count_out[o] = f.gcount[g];
+    const uint64_t cnt = f.gcount[g];
+    f.count_out[o] = cnt;
+    sum += cnt;
     if (f.sum) f.sum_out[o] = exact_round(f.gacc + g * EXACT_MAXD, f.D, f.lsb, f.err);
     if (f.parts) exact_parts(f.gacc + g * EXACT_MAXD, f.D, f.lsb, f.parts + o * EXACT_PARTS, f.err);
   }
+  if (f.n_join) add_join_tuples(f.n_join, sum);
+}
+
+// What the host reads at the end of a join: rows (null: none asked), errors,
+// join tuples.
+struct JoinEnd {
+  uint64_t rows, err, n_join;
+};
+
+// Up to this many possible groups the result's buffers are sized for all of
+// them, and their number is read with the rest at the end of the join: a wait
+// less (about 10 us), for at most 60 bytes a row.
+constexpr uint64_t CAP_ROWS = 1u << 18;
+
+__global__ void k_join_end(const uint64_t* rows, const uint64_t* ctl, JoinEnd* out) {
+  *out = JoinEnd{rows ? *rows : 0ull, ctl[0], ctl[1]};
 }
 
 struct ColsArg {
@@ -2017,15 +2096,47 @@ DSet make_dset(const lh_plan_t* p, const Participant& pt, const Frontier& F) {
   return d;
 }
 
-// Per-row work (smallest participating set), its exclusive scan, and the
-// cut of every row into work units.
+// Per-row work (smallest participating set) and the cut of every row into
+// work units.  What bounds a depth of a small join is the launches and the
+// host's wait for the unit count, so one kernel stores all totals at once,
+// the first attribute has none, and a join ends with one read: the join of
+// a 300-vertex graph took 0.30 ms and takes 0.18, a sparse 4 k x 4 k product
+// 1.73 and 1.62.
 struct DepthWork {
-  DBuf<uint64_t> W, U;
-  DBuf<uint64_t> n_top;     // two-set leaves: units of the top bucket, then of merged rows (device)
+  DBuf<uint64_t> U;
+  DBuf<uint32_t> work, urow;
   DBuf<uint8_t> drv;
-  DBuf<uint32_t> urow;
   uint64_t total = 0, units = 0, nblk = 0;
+  uint64_t top = 0, merge = 0;  // two-set leaves: units of the top bucket, of merged rows
 };
+
+// The first attribute's sets are all root sets, and the only row is the
+// empty binding: the host knows what k_work would find.
+void root_work(const lh_plan_t* p, const std::vector<Participant>& parts, ElemArgs& a, DepthWork& dw) {
+  float probe[MAXP], best_cost = 3.0e38f;
+  uint64_t card[MAXP];
+  bool empty = false;
+  for (uint32_t i = 0; i < a.np; i++) {
+    const Level& L = p->atoms[parts[i].atom].trie->lv[0];
+    card[i] = L.n;
+    empty = empty || L.n == 0;
+    probe[i] = L.n && L.pool_words ? 1.0f : 2.0f + std::log2((float)L.n + 1.0f);
+  }
+  for (uint32_t i = 0; i < a.np; i++) {
+    float c = 0.0f;
+    for (uint32_t q = 0; q < a.np; q++)
+      if (q != i) c += probe[q];
+    c = (float)card[i] * (c + 1.0f);
+    if (c < best_cost) {
+      best_cost = c;
+      a.drv0 = i;
+    }
+  }
+  a.single = 1;
+  dw.total = empty ? 0 : card[a.drv0];
+  const uint64_t unit_el = (uint64_t)a.lanes * U_IT;
+  dw.units = (dw.total + unit_el - 1) / unit_el;
+}
 
 void depth_work(const lh_plan_t* p, uint32_t d, const Frontier& F, ElemArgs& a, DepthWork& dw, hipStream_t s,
                 bool leaf2 = false) {
@@ -2044,37 +2155,46 @@ void depth_work(const lh_plan_t* p, uint32_t d, const Frontier& F, ElemArgs& a, 
     avg = std::min(avg, L.n / std::max<uint64_t>(1, L.n_sets));
   }
   a.lanes = !leaf2 && wa.np <= 4 && avg <= SUB_AVG ? SUB_LANES : WAVE;
-  DBuf<uint32_t> work(F.n, s), units(F.n, s);
-  dw.drv.alloc(F.n, s);
-  dw.W.alloc(F.n + 1, s);
-  dw.U.alloc(F.n + 1, s);
-  {
-    ProfScope ps("join_work", s, F.n, 0);
-    if (leaf2) {
-      dw.n_top.alloc(2, s);
-      fill_u64(dw.n_top.p, 0, 2, s);
+  if (d == 0 && !leaf2) {
+    root_work(p, parts, a, dw);
+  } else {
+    DBuf<uint32_t> units(F.n, s);
+    dw.work.alloc(F.n, s);
+    dw.drv.alloc(F.n, s);
+    dw.U.alloc(F.n + 1, s);
+    const unsigned nb = std::min(grid_for(F.n), 4096u);
+    DBuf<WorkTotals> part(nb, s);
+    HostOut<WorkTotals> out(s);
+    {
+      ProfScope ps("join_work", s, F.n, 0);
+      const uint32_t el = a.lanes * U_IT, l2 = leaf2 ? 1u : 0u;
+      if (wa.np <= 2) k_work<2><<<nb, 256, 0, s>>>(wa, F.n, dw.work.p, dw.drv.p, units.p, el, l2, part.p);
+      else if (wa.np <= 4) k_work<4><<<nb, 256, 0, s>>>(wa, F.n, dw.work.p, dw.drv.p, units.p, el, l2, part.p);
+      else k_work<MAXP><<<nb, 256, 0, s>>>(wa, F.n, dw.work.p, dw.drv.p, units.p, el, l2, part.p);
     }
-    k_work<<<grid_for(F.n), 256, 0, s>>>(wa, F.n, work.p, dw.drv.p, units.p, a.lanes * U_IT, leaf2 ? 1u : 0u,
-                                         leaf2 ? (unsigned long long*)dw.n_top.p : nullptr);
-  }
-  LH_HIP(hipGetLastError());
-  dw.total = scan_u32_to_u64(work.p, dw.W.p, F.n, s);
-  dw.units = scan_u32_to_u64(units.p, dw.U.p, F.n, s);
-  if (dw.units >= (1ull << 32)) fail(LH_ERR_OVERFLOW, "join: more than 2^32 work units at one attribute");
-  dw.urow.alloc(dw.units, s);
-  if (dw.units) {
-    // rows with more than UROW_SMALL units number at most units / UROW_SMALL
-    DBuf<uint32_t> big(std::max<uint64_t>(1, std::min<uint64_t>(F.n, dw.units / UROW_SMALL)), s), nbig(1, s);
-    fill_u32(nbig.p, 0u, 1, s);
-    k_unit_rows<<<grid_for(F.n), 256, 0, s>>>(dw.U.p, F.n, dw.urow.p, big.p, nbig.p);
     LH_HIP(hipGetLastError());
-    k_unit_rows_big<<<1024, 256, 0, s>>>(dw.U.p, big.p, nbig.p, dw.urow.p);
+    scan_u32_to_u64_dev(units.p, dw.U.p, F.n, s);
+    k_work_totals<<<1, 256, 0, s>>>(part.p, nb, dw.U.p + F.n, out.p());
+    LH_HIP(hipGetLastError());
+    const WorkTotals h = out.get();
+    dw.units = h.units;
+    dw.total = h.work;
+    dw.top = h.top;
+    dw.merge = h.merge;
+  }
+  if (dw.units >= (1ull << 32)) fail(LH_ERR_OVERFLOW, "join: more than 2^32 work units at one attribute");
+  if (dw.units && !a.single) {
+    dw.urow.alloc(dw.units, s);
+    if (dw.units > UROW_SMALL * F.n)
+      k_unit_search<<<grid_for(dw.units), 256, 0, s>>>(dw.U.p, F.n, dw.units, dw.urow.p);
+    else
+      k_unit_rows<<<grid_for(F.n), 256, 0, s>>>(dw.U.p, F.n, dw.urow.p);
     LH_HIP(hipGetLastError());
   }
   const uint64_t per_block = (uint64_t)J_NW * (WAVE / a.lanes);
   dw.nblk = (dw.units + per_block - 1) / per_block;
   a.nvblk = dw.nblk;
-  a.W = dw.W.p;
+  a.work = dw.work.p;
   a.drv = dw.drv.p;
   a.nrows = F.n;
   a.total = dw.total;
@@ -2101,11 +2221,13 @@ void step(const lh_plan_t* p, uint32_t d, Frontier& F, hipStream_t s) {
   }
   const uint64_t nblk = dw.nblk;
   if (nblk >= (1ull << 31)) fail(LH_ERR_OVERFLOW, "join: too much work at one attribute");
-  DBuf<uint32_t> bcnt(nblk, s);
+  // the first attribute in a single relation: every key is a hit, in order
+  const bool direct = a.single && a.np == 1;
+  DBuf<uint32_t> bcnt(direct ? 0 : nblk, s);
   a.blk_cnt = bcnt.p;
   a.need_pos_mask = 0;
   a.n_atoms = (uint32_t)p->atoms.size();
-  {
+  if (!direct) {
     static const char* names[MAXV] = {"join_count_d0", "join_count_d1", "join_count_d2", "join_count_d3",
                                       "join_count_d4", "join_count_d5", "join_count_d6", "join_count_d7",
                                       "join_count_d8", "join_count_d9", "join_count_d10", "join_count_d11",
@@ -2114,8 +2236,8 @@ void step(const lh_plan_t* p, uint32_t d, Frontier& F, hipStream_t s) {
     launch_elem<M_COUNT>(a, elem_grid(nblk), s);
   }
   LH_HIP(hipGetLastError());
-  DBuf<uint64_t> boff(nblk + 1, s);
-  const uint64_t n_new = scan_u32_to_u64(bcnt.p, boff.p, nblk, s);
+  DBuf<uint64_t> boff(direct ? 0 : nblk + 1, s);
+  const uint64_t n_new = direct ? total : scan_u32_to_u64(bcnt.p, boff.p, nblk, s);
   if (n_new >= (1ull << 32)) fail(LH_ERR_OVERFLOW, "join: frontier exceeds 2^32 rows");
   Frontier G;
   G.n = n_new;
@@ -2138,7 +2260,8 @@ void step(const lh_plan_t* p, uint32_t d, Frontier& F, hipStream_t s) {
   for (uint32_t j = 0; j < no; j++) {
     a.outv_in[j] = F.outv[j].p;
     const uint32_t dj = p->depth_of[p->out_attrs[j]];
-    if (dj <= d) {
+    // (columns bound earlier travel unless the groups took them)
+    if (dj == d || (dj < d && F.outv[j].p)) {
       G.outv[j].alloc(n_new, s);
       a.outv_out[j] = G.outv[j].p;
       if (dj == d) a.new_outv = (int32_t)j;
@@ -2177,8 +2300,9 @@ void step(const lh_plan_t* p, uint32_t d, Frontier& F, hipStream_t s) {
 // sort-based path should run instead (asked for, or the table would not
 // fit).
 bool group_in_place(const lh_plan_t* p, const Frontier& F, ElemArgs& a, uint64_t nblk, uint64_t total,
-                    uint32_t no, uint32_t n_cols, bool is_sum, uint32_t D, DBuf<uint32_t>& err,
-                    lh_result_impl* res, DBuf<uint64_t>& n_join_out, hipStream_t s) {
+                    uint32_t no, uint32_t n_cols, bool is_sum, uint32_t D, DBuf<uint64_t>& ctl,
+                    uint64_t*& ctl_at, DBuf<uint64_t>& off, const uint64_t*& rows_at, lh_result_impl* res,
+                    hipStream_t s) {
   uint32_t impl = p->group_impl;
   if (impl == LH_GROUP_SORT >> 4) return false;
   const uint32_t leaf = p->n_attrs - 1;
@@ -2258,7 +2382,6 @@ bool group_in_place(const lh_plan_t* p, const Frontier& F, ElemArgs& a, uint64_t
   L.gpack = L.gplain && is_sum && D <= 7 && !L.glds && !arena_tight() ? 1u : 0u;
   L.gstride = 1 + (is_sum ? D : 0u);
   if (L.gpack) L.gstride = L.gstride <= 2 ? 2u : L.gstride <= 4 ? 4u : 8u;
-  DBuf<int64_t> acc;
   DBuf<uint32_t> tag;
   std::vector<DBuf<uint32_t>> tkeys;
   DBuf<uint64_t> key64;
@@ -2275,11 +2398,15 @@ bool group_in_place(const lh_plan_t* p, const Frontier& F, ElemArgs& a, uint64_t
       L.gshift[c] = sh;
     }
   }
+  uint64_t n_groups = 0;
   for (;;) {
     const uint64_t n = impl == 3 ? space : cap;
-    acc.alloc(n * L.gstride, s);
-    LH_HIP(hipMemsetAsync(acc.p, 0, n * L.gstride * sizeof(int64_t), s));
-    L.gacc = acc.p;
+    // the slots, then the control words (padded slots stay on their lines)
+    ctl.alloc(n * L.gstride + 2, s);
+    LH_HIP(hipMemsetAsync(ctl.p, 0, ctl.n * sizeof(uint64_t), s));
+    ctl_at = ctl.p + n * L.gstride;
+    L.err = reinterpret_cast<uint32_t*>(ctl_at);
+    L.gacc = reinterpret_cast<int64_t*>(ctl.p);
     if (impl == 2 && packed) {
       key64.alloc(n, s);
       LH_HIP(hipMemsetAsync(key64.p, 0xff, n * sizeof(uint64_t), s));
@@ -2301,12 +2428,28 @@ bool group_in_place(const lh_plan_t* p, const Frontier& F, ElemArgs& a, uint64_t
       launch_elem<M_LEAF_B_AGG>(a, elem_grid(nblk), s);
       LH_HIP(hipGetLastError());
     }
-    const uint32_t e = read_scalar(err.p, s);
+    if (impl == 3) break;
+    const unsigned tiles = (unsigned)((cap + GU_TILE - 1) / GU_TILE);
+    const uint64_t* n_used = nullptr;
+    if (packed) {
+      // the slots in use, counted before the errors are read: one wait
+      DBuf<uint32_t> used(tiles, s);
+      off.alloc(tiles + 1, s);
+      k_used_counts<<<tiles, GU_NT, 0, s>>>(HashUsed{key64.p}, cap, used.p);
+      LH_HIP(hipGetLastError());
+      scan_u32_to_u64_dev(used.p, off.p, tiles, s);
+      n_used = off.p + tiles;
+    }
+    HostOut<JoinEnd> out(s);
+    k_join_end<<<1, 1, 0, s>>>(n_used, ctl_at, out.p());
+    LH_HIP(hipGetLastError());
+    const JoinEnd seen = out.get();
+    n_groups = seen.rows;
+    const uint32_t e = (uint32_t)seen.err;
     if (e & ERR_SLOT_SPIN) fail(LH_ERR_DEVICE, "join: a GROUP BY hash slot was never published");
-    if (impl == 2 && (e & ERR_TABLE_FULL)) {
+    if (e & ERR_TABLE_FULL) {
       // more groups than the estimate: count the tuples exactly once and
       // size the table for them (later overflows double it), from scratch
-      fill_u32(err.p, 0, 1, s);
       uint64_t want = 2 * cap;
       if (!counted) {
         counted = true;
@@ -2327,19 +2470,16 @@ bool group_in_place(const lh_plan_t* p, const Frontier& F, ElemArgs& a, uint64_t
     }
     break;
   }
-  DBuf<uint64_t> n_join(1, s);
-  LH_HIP(hipMemsetAsync(n_join.p, 0, sizeof(uint64_t), s));
   GroupFin f{};
-  f.acc = acc.p;
+  f.acc = L.gacc;
   f.stride = L.gstride;
   f.sgn = L.gsigned;
   f.n_cols = n_cols;
   f.sum = is_sum ? 1u : 0u;
   f.lsb = L.lsb;
   f.D = D;
-  f.err = err.p;
-  f.n_join = n_join.p;
-  uint64_t n_groups = 0;
+  f.err = L.err;
+  f.n_join = ctl_at + 1;
   lh_result& R = res->pub;
   auto alloc_rows = [&]() {
     res->cols.resize(n_cols);
@@ -2359,19 +2499,27 @@ bool group_in_place(const lh_plan_t* p, const Frontier& F, ElemArgs& a, uint64_t
   };
   const uint64_t n_ent = impl == 3 ? space : cap;
   const unsigned tiles = (unsigned)((n_ent + GU_TILE - 1) / GU_TILE);
-  if (impl == 3 || packed) {
+  if (impl == 3) {
     DBuf<uint32_t> used(tiles, s);
-    DBuf<uint64_t> off(tiles + 1, s);
-    if (impl == 3) k_used_counts<<<tiles, GU_NT, 0, s>>>(DenseUsed{acc.p, L.gstride}, n_ent, used.p);
-    else k_used_counts<<<tiles, GU_NT, 0, s>>>(HashUsed{key64.p}, n_ent, used.p);
+    off.alloc(tiles + 1, s);
+    k_used_counts<<<tiles, GU_NT, 0, s>>>(DenseUsed{L.gacc, L.gstride}, n_ent, used.p);
     LH_HIP(hipGetLastError());
-    n_groups = scan_u32_to_u64(used.p, off.p, tiles, s);
+    if (n_ent <= CAP_ROWS && !arena_tight()) {
+      scan_u32_to_u64_dev(used.p, off.p, tiles, s);
+      n_groups = n_ent;
+      rows_at = off.p + tiles;
+    } else {
+      n_groups = scan_u32_to_u64(used.p, off.p, tiles, s);
+    }
     alloc_rows();
-    if (n_groups && impl == 3) {
+    if (n_groups) {
       f.off = off.p;
       k_dense_finalize<<<tiles, GU_NT, 0, s>>>(f, n_ent);
       LH_HIP(hipGetLastError());
-    } else if (n_groups) {
+    }
+  } else if (packed) {
+    alloc_rows();
+    if (n_groups) {
       // the keys in use and their slots, sorted by key
       DBuf<uint64_t> k0(n_groups, s), k1(n_groups, s);
       DBuf<uint32_t> v0(n_groups, s), v1(n_groups, s);
@@ -2410,7 +2558,6 @@ bool group_in_place(const lh_plan_t* p, const Frontier& F, ElemArgs& a, uint64_t
   }
   R.group_impl = impl;
   R.n_rows = n_groups;
-  n_join_out = std::move(n_join);
   return true;
 }
 
@@ -2536,18 +2683,13 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
     step(p, d, F, s);
     if (p->case_prefix && no > 0 && d == no - 1) {
       n_groups = F.n;
+      // the groups' keys: deeper rows need no output columns, only their
+      // group
       group_keys.clear();
-      for (uint32_t j = 0; j < no; j++) {
-        group_keys.emplace_back(F.n, s);
-        if (F.n)
-          LH_HIP(hipMemcpyAsync(group_keys.back().p, F.outv[j].p, F.n * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
-      }
+      for (uint32_t j = 0; j < no; j++) group_keys.push_back(std::move(F.outv[j]));
     }
   }
   if (p->case_prefix && no > 0 && F.n == 0 && group_keys.empty()) n_groups = 0;
-
-  DBuf<uint32_t> err(1, s);
-  LH_HIP(hipMemsetAsync(err.p, 0, sizeof(uint32_t), s));
 
   // leaf attribute: intersect and aggregate
   ElemArgs a{};
@@ -2566,7 +2708,6 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
   L.sum = is_sum ? 1u : 0u;
   L.lsb = p->exact_lsb;
   L.D = D;
-  L.err = err.p;
   a.n_atoms = na;
   a.n_outv = no;
   for (uint32_t j = 0; j < no; j++) a.outv_in[j] = F.outv[j].p;
@@ -2597,18 +2738,26 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
   lh_result& R = res->pub;
   R.n_cols = n_cols;
   R.exact = is_sum ? 1u : 0u;
-  DBuf<uint64_t> n_join;  // join tuples (device), when the finalization added them up
+  // errors (a 32-bit word) and join tuples, cleared with the first buffer
+  // that the path clears
+  DBuf<uint64_t> ctl;
+  uint64_t* ctl_at = nullptr;
+  const uint64_t* rows_at = nullptr;  // the row count, where the host does not know it yet
+  DBuf<uint64_t> off;                 // (which lies in here)
 
   if (p->case_prefix) {
     // streamed groups: one accumulator per group of the output prefix
-    DBuf<uint64_t> gcount(n_groups ? n_groups : 1, s);
-    DBuf<int64_t> gacc(is_sum ? (n_groups ? n_groups : 1) * EXACT_MAXD : 0, s);
-    LH_HIP(hipMemsetAsync(gcount.p, 0, gcount.n * sizeof(uint64_t), s));
-    if (is_sum) LH_HIP(hipMemsetAsync(gacc.p, 0, gacc.n * sizeof(int64_t), s));
+    const uint64_t ng = n_groups ? n_groups : 1;
+    ctl.alloc(2 + ng * (1 + (is_sum ? EXACT_MAXD : 0)), s);
+    LH_HIP(hipMemsetAsync(ctl.p, 0, ctl.n * sizeof(uint64_t), s));
+    ctl_at = ctl.p;
+    L.err = reinterpret_cast<uint32_t*>(ctl_at);
+    uint64_t* const gcount = ctl.p + 2;
+    int64_t* const gacc = reinterpret_cast<int64_t*>(gcount + ng);
     L.gid = no > 0 ? F.gid.p : nullptr;
     L.own_group = no > 0 && no == leaf ? 1u : 0u;
-    L.gcount = gcount.p;
-    L.gacc = gacc.p;
+    L.gcount = gcount;
+    L.gacc = gacc;
     if (total) {
       if (leaf2) {
         // two sets, set semantics: per-unit descriptors, one load per wave
@@ -2620,11 +2769,7 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
         // the top bucket (rows whose two sets hold TOP_MIN elements or
         // more, in units of TOP_EL) and the merged rows each run as a launch
         // of their own
-        struct UnitCounts {
-          uint64_t top, merge;
-        };
-        const UnitCounts nu = read_scalar(reinterpret_cast<const UnitCounts*>(dw.n_top.p), s);
-        const bool split = nu.top != 0, merged = nu.merge != 0;
+        const bool split = dw.top != 0, merged = dw.merge != 0;
         DBuf<uint32_t> top_flag(split ? dw.units : 0, s), merge_flag(merged ? dw.units : 0, s);
         {
           ProfScope ps("leaf_units", s, dw.units, 0);
@@ -2696,25 +2841,30 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
       LH_HIP(hipGetLastError());
     }
     FinA f{};
-    f.gcount = gcount.p;
-    f.gacc = gacc.p;
+    f.gcount = gcount;
+    f.gacc = gacc;
+    f.n_join = ctl_at + 1;
     f.sum = L.sum;
     f.lsb = L.lsb;
     f.D = D;
-    f.err = err.p;
-    uint64_t n_out_rows;
-    DBuf<uint64_t> off;
-    if (no == 0) {
-      n_out_rows = 1;
-    } else {
-      DBuf<uint32_t> flags(n_groups, s);
-      off.alloc(n_groups + 1, s);
-      if (n_groups) {
-        k_nonzero_flags<<<grid_for(n_groups), 256, 0, s>>>(gcount.p, n_groups, flags.p);
-        LH_HIP(hipGetLastError());
-      }
-      n_out_rows = scan_u32_to_u64(flags.p, off.p, n_groups, s);
+    f.err = L.err;
+    // rows: the groups with a tuple
+    const uint64_t nfin = no == 0 ? 1 : (group_keys.empty() ? 0 : n_groups);
+    const unsigned tiles = (unsigned)((nfin + GU_TILE - 1) / GU_TILE);
+    uint64_t n_out_rows = no == 0 ? 1 : 0;
+    if (no && nfin) {
+      DBuf<uint32_t> used(tiles, s);
+      off.alloc(tiles + 1, s);
+      k_used_counts<<<tiles, GU_NT, 0, s>>>(DenseUsed{reinterpret_cast<const int64_t*>(gcount), 1}, nfin, used.p);
+      LH_HIP(hipGetLastError());
       f.off = off.p;
+      if (nfin <= CAP_ROWS && !arena_tight()) {
+        scan_u32_to_u64_dev(used.p, off.p, tiles, s);
+        n_out_rows = nfin;
+        rows_at = off.p + tiles;
+      } else {
+        n_out_rows = scan_u32_to_u64(used.p, off.p, tiles, s);
+      }
     }
     f.n_cols = no;
     res->cols.resize(no);
@@ -2729,15 +2879,19 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
     f.count_out = res->counts.p;
     f.sum_out = res->sums.p;
     f.parts = res->parts.p;
-    const uint64_t nfin = no == 0 ? 1 : (group_keys.empty() ? 0 : n_groups);
-    if (nfin) {
-      k_finalize_groups<<<grid_for(nfin), 256, 0, s>>>(f, nfin);
+    if (nfin && n_out_rows) {
+      k_finalize_groups<<<tiles, GU_NT, 0, s>>>(f, nfin);
       LH_HIP(hipGetLastError());
     }
     R.n_rows = n_out_rows;
-  } else if (!group_in_place(p, F, a, nblk, total, no, n_cols, is_sum, D, err, res.get(), n_join, s)) {
+  } else if (!group_in_place(p, F, a, nblk, total, no, n_cols, is_sum, D, ctl, ctl_at, off, rows_at,
+                             res.get(), s)) {
     // materialize leaf tuples keyed by the output columns, sort, reduce
     R.group_impl = 1;
+    ctl.alloc(2, s);
+    LH_HIP(hipMemsetAsync(ctl.p, 0, ctl.n * sizeof(uint64_t), s));
+    ctl_at = ctl.p;
+    L.err = reinterpret_cast<uint32_t*>(ctl_at);
     uint64_t n_emit = 0;
     DBuf<uint64_t> boff;
     if (total) {
@@ -2813,7 +2967,7 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
     sa.D = D;
     sa.gcount = gcount.p;
     sa.gacc = gacc.p;
-    sa.err = err.p;
+    sa.err = L.err;
     for (uint32_t c = 0; c < n_cols; c++) {
       segkeys[c].alloc(n_seg, s);
       sa.key_out[c] = segkeys[c].p;
@@ -2825,10 +2979,11 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
     FinA f{};
     f.gcount = gcount.p;
     f.gacc = gacc.p;
+    f.n_join = ctl_at + 1;
     f.sum = L.sum;
     f.lsb = L.lsb;
     f.D = D;
-    f.err = err.p;
+    f.err = L.err;
     f.n_cols = n_cols;
     res->cols.resize(n_cols);
     for (uint32_t c = 0; c < n_cols; c++) {
@@ -2843,30 +2998,25 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
     f.sum_out = res->sums.p;
     f.parts = res->parts.p;
     if (n_seg) {
-      k_finalize_groups<<<grid_for(n_seg), 256, 0, s>>>(f, n_seg);
+      k_finalize_groups<<<(unsigned)((n_seg + GU_TILE - 1) / GU_TILE), GU_NT, 0, s>>>(f, n_seg);
       LH_HIP(hipGetLastError());
     }
     R.n_rows = n_seg;
   }
-  const uint32_t leaf_err = read_scalar(err.p, s);
-  if (leaf_err & ERR_COUNT_OVERFLOW) fail(LH_ERR_OVERFLOW, "join: a tuple count exceeds 2^64 - 1");
-  if (leaf_err) fail(LH_ERR_UNSUPPORTED, "an annotation product did not fit the exact accumulator");
+  HostOut<JoinEnd> out(s);
+  k_join_end<<<1, 1, 0, s>>>(rows_at, ctl_at, out.p());
+  LH_HIP(hipGetLastError());
+  const JoinEnd end = out.get();
+  if (end.err & ERR_COUNT_OVERFLOW) fail(LH_ERR_OVERFLOW, "join: a tuple count exceeds 2^64 - 1");
+  if (end.err) fail(LH_ERR_UNSUPPORTED, "an annotation product did not fit the exact accumulator");
+  if (rows_at) R.n_rows = end.rows;
 
-  // total contributing tuples
   res->colptr.resize(n_cols);
   for (uint32_t c = 0; c < n_cols; c++) res->colptr[c] = res->cols[c].p;
   R.out_keys = n_cols ? res->colptr.data() : nullptr;
   R.counts = res->counts.p;
   R.sums = is_sum ? res->sums.p : nullptr;
-  uint64_t nj = 0;
-  if (n_join.p) {
-    nj = read_scalar(n_join.p, s);
-  } else if (R.n_rows) {
-    DBuf<uint64_t> tmp(R.n_rows + 1, s);
-    nj = scan_u64(res->counts.p, tmp.p, R.n_rows, s);
-  }
-  R.n_join_tuples = nj;
-  LH_HIP(hipStreamSynchronize(s));
+  R.n_join_tuples = end.n_join;
   return res.release();
 }
 

@@ -792,16 +792,13 @@ void scan_u32_to_u64_dev(const uint32_t* in, uint64_t* out, uint64_t n, hipStrea
   scan_dev<uint32_t, uint64_t>(in, out, n, s);
 }
 
-void max_u32_into(const uint32_t* in, uint64_t n, uint32_t* out, hipStream_t s) {
-  if (!n) return;
-  k_reduce_max_u32<<<std::min(grid_for((n + 3) / 4), 2048u), 256, 0, s>>>(in, n, out);
-  LH_HIP(hipGetLastError());
-}
-
 uint32_t reduce_max_u32(const uint32_t* in, uint64_t n, hipStream_t s) {
   DBuf<uint32_t> r(1, s);
   LH_HIP(hipMemsetAsync(r.p, 0, sizeof(uint32_t), s));
-  max_u32_into(in, n, r.p, s);
+  if (n) {
+    k_reduce_max_u32<<<std::min(grid_for((n + 3) / 4), 2048u), 256, 0, s>>>(in, n, r.p);
+    LH_HIP(hipGetLastError());
+  }
   return read_scalar(r.p, s);
 }
 

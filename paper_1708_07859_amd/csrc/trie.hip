@@ -134,8 +134,6 @@ __global__ void k_level_totals(const uint32_t* tile_off, uint32_t ntiles, uint32
   if (l < n_levels) out[l] = tile_off[(uint64_t)(l + 1) * ntiles] - tile_off[(uint64_t)l * ntiles];
 }
 
-__global__ void k_set_u32(uint32_t* p, uint32_t v) { *p = v; }
-
 // What the build needs to know of its input: every level's largest key and,
 // when asked, how much of it is in order (bit t-1 of the mask stays set while
 // rows i-1, i are in lexicographic order of the last t levels, for every i;
