@@ -1283,11 +1283,9 @@ struct Leaf2Args {
   const uint64_t* pool[2];
   const UnitDesc* desc;
   const uint32_t* list;   // top-bucket launch: the units to run (units = their number)
-  uint64_t n_desc;        // descriptors (all units of the leaf)
   uint64_t* ucnt;         // grouped: count of every unit; null: one group, summed into gcount[0]
   uint64_t* gcount;
   uint64_t units;
-  uint64_t nvblk;
 };
 
 // Groups own contiguous runs of units (frontier rows are in group order):
@@ -1308,144 +1306,188 @@ __global__ void k_group_add(const uint64_t* gstart, const uint64_t* gend, uint64
 }
 
 
-// Membership of x[it] (it < nit) in the strictly increasing keys a[0, m),
-// m >= 1: a branchless bisection whose trip count depends on m only, so the
-// probes of a lane's values are issued together.  nit is wave-uniform.
-template <int NIT, class Arr>
-__device__ __forceinline__ uint32_t count_members(Arr a, uint32_t m, const uint32_t* x, const bool* v, uint32_t nit) {
-  uint32_t lo[NIT];
+// A unit's probes are compiled for its number of driver keys a lane holds:
+// the scalar unit, which the four SIMDs of a CU share, was as busy as the
+// memory with loop counters and masks of keys that a lane might not hold
+// (172 scalar instructions a staged unit).  Loads that would pass a range's
+// end read its last key instead, so none needs a mask.  Scale-22 triangles,
+// 104 M units: 13.2 G scalar instructions and 38.0 ms before, 8.4 G and
+// 30.3 ms now, at 7.5 TB/s beyond the L2.
+
+// The driver keys of a unit: x[it] is key it * WAVE + lane of k[0, n),
+// (N - 1) * WAVE < n <= N * WAVE; lanes past the end hold the last key.
+template <int N>
+__device__ __forceinline__ void driver_keys(const uint32_t* k, uint32_t n, int lane, uint32_t* x) {
 #pragma unroll
-  for (int it = 0; it < NIT; it++) lo[it] = 0;
-  uint32_t n = m;
-  while (n > 1) {
-    const uint32_t half = n >> 1;
-#pragma unroll
-    for (int it = 0; it < NIT; it++)
-      if (it < (int)nit) lo[it] = (a[lo[it] + half] <= x[it]) ? lo[it] + half : lo[it];
-    n -= half;
-  }
+  for (int it = 0; it + 1 < N; it++) x[it] = k[it * WAVE + lane];
+  x[N - 1] = k[min((uint32_t)((N - 1) * WAVE + lane), n - 1)];
+}
+
+// Of the keys x (held as driver_keys loads them) those with hit[it] set.
+template <int N>
+__device__ __forceinline__ uint32_t count_hits(const bool* hit, uint32_t n, int lane) {
   uint32_t c = 0;
 #pragma unroll
-  for (int it = 0; it < NIT; it++)
-    if (it < (int)nit) c += (v[it] && a[lo[it]] == x[it]) ? 1u : 0u;
-  return c;
+  for (int it = 0; it + 1 < N; it++) c += hit[it] ? 1u : 0u;
+  return c + (hit[N - 1] && (uint32_t)((N - 1) * WAVE + lane) < n ? 1u : 0u);
 }
 
-// Number of entries <= x[it] in the sorted a[0, n), n >= 1, for it < nit:
-// branchless, trip count set by n alone.
-template <int NIT, class Arr>
-__device__ __forceinline__ void count_le(Arr a, uint32_t n0, const uint32_t* x, uint32_t nit, uint32_t* k) {
+// Number of entries <= x[it] in the sorted a[0, n), n >= 1: branchless, trip
+// count set by n alone.
+template <int N, class Arr>
+__device__ __forceinline__ void count_le(Arr a, uint32_t n, const uint32_t* x, uint32_t* k) {
 #pragma unroll
-  for (int it = 0; it < NIT; it++) k[it] = 0;
-  uint32_t n = n0;
+  for (int it = 0; it < N; it++) k[it] = 0;
   while (n > 1) {
     const uint32_t half = n >> 1;
 #pragma unroll
-    for (int it = 0; it < NIT; it++)
-      if (it < (int)nit) k[it] = (a[k[it] + half - 1] <= x[it]) ? k[it] + half : k[it];
+    for (int it = 0; it < N; it++) k[it] = (a[k[it] + half - 1] <= x[it]) ? k[it] + half : k[it];
     n -= half;
   }
 #pragma unroll
-  for (int it = 0; it < NIT; it++)
-    if (it < (int)nit) k[it] += (a[k[it]] <= x[it]) ? 1u : 0u;
+  for (int it = 0; it < N; it++) k[it] += (a[k[it]] <= x[it]) ? 1u : 0u;
 }
 
-// The wave copies src[0, m) to LDS, U_IT loads in flight per lane.
+// The wave copies src[0, m) (1 <= m <= L2_CAP) to LDS, four loads in flight
+// per lane; up to the next multiple of 256 words the last key is repeated.
 __device__ __forceinline__ void wave_stage(uint32_t* dst, const uint32_t* src, uint32_t m, int lane) {
-  for (uint32_t k0 = 0; k0 < m; k0 += U_IT * WAVE) {
-    uint32_t t[U_IT];
+  static_assert(L2_CAP % (4 * WAVE) == 0, "whole rounds");
+  for (uint32_t k0 = 0; k0 < m; k0 += 4 * WAVE) {
+    uint32_t t[4];
 #pragma unroll
-    for (int j = 0; j < U_IT; j++) {
-      const uint32_t i = k0 + j * WAVE + lane;
-      t[j] = i < m ? src[i] : 0u;
-    }
+    for (int j = 0; j < 4; j++) t[j] = src[min(k0 + j * WAVE + lane, m - 1)];
 #pragma unroll
-    for (int j = 0; j < U_IT; j++) {
-      const uint32_t i = k0 + j * WAVE + lane;
-      if (i < m) dst[i] = t[j];
-    }
+    for (int j = 0; j < 4; j++) dst[k0 + j * WAVE + lane] = t[j];
   }
 }
 
-// Probe path of a unit: the unit's driver keys against the probed set's
-// bitset, its LDS-staged keys, or its line samples.
-template <int NIT>
+// Probe paths of a unit: its driver keys against the probed set's bitset ...
+template <int N>
+__device__ __forceinline__ uint32_t probe_bits(const uint32_t* dk, uint32_t n, const uint64_t* words, uint32_t base,
+                                               uint32_t last, int lane) {
+  uint32_t x[N], word[N], dd[N];
+  driver_keys<N>(dk, n, lane, x);
+  const uint32_t* w32 = reinterpret_cast<const uint32_t*>(words);  // bit b of a set: bit b & 31 of half word b >> 5
+  bool hit[N];
+#pragma unroll
+  for (int it = 0; it < N; it++) {
+    dd[it] = x[it] - base;  // (keys below the base wrap past the last value)
+    hit[it] = dd[it] <= last - base;
+    word[it] = w32[hit[it] ? dd[it] >> 5 : 0u];
+  }
+#pragma unroll
+  for (int it = 0; it < N; it++) hit[it] &= (word[it] >> (dd[it] & 31u) & 1u) != 0;
+  return count_hits<N>(hit, n, lane);
+}
+
+// ... against the keys pk[lo, hi), staged in LDS ...
+template <int N>
+__device__ __forceinline__ uint32_t probe_staged(const uint32_t* dk, uint32_t n, const uint32_t* pk, uint32_t m,
+                                                 uint32_t* stage, int lane) {
+  uint32_t x[N], k[N];
+  driver_keys<N>(dk, n, lane, x);
+  wave_stage(stage, pk, m, lane);
+  wave_lds_sync();
+#pragma unroll
+  for (int it = 0; it < N; it++) k[it] = 0;
+  uint32_t left = m;
+  while (left > 1) {
+    const uint32_t half = left >> 1;
+#pragma unroll
+    for (int it = 0; it < N; it++) k[it] = (stage[k[it] + half] <= x[it]) ? k[it] + half : k[it];
+    left -= half;
+  }
+  bool hit[N];
+#pragma unroll
+  for (int it = 0; it < N; it++) hit[it] = stage[k[it]] == x[it];
+  wave_lds_sync();
+  return count_hits<N>(hit, n, lane);
+}
+
+// ... or, for a large range, through its line samples (staged in LDS when
+// they fit) and the one line that can hold the key: three keys that quarter
+// the line, then the quarter's eight in two loads, instead of a bisection's
+// six loads one after another.  hi - lo >= 4.
+template <int N>
+__device__ __forceinline__ uint32_t probe_lines(const uint32_t* dk, uint32_t n, const uint32_t* pk, const uint32_t* sp,
+                                                uint32_t lo, uint32_t hi, uint32_t* stage, int lane) {
+  static_assert(LINE_SHIFT == 5, "a line is four quarters of eight keys");
+  struct __attribute__((packed, aligned(4))) Four {
+    uint32_t k[4];
+  };
+  uint32_t x[N], k[N];
+  driver_keys<N>(dk, n, lane, x);
+  // Samples j in [jf, jl] start lines inside [lo, hi); keys before the first
+  // of them belong to the range's first, partial line.
+  const uint32_t jf = (lo + (1u << LINE_SHIFT) - 1) >> LINE_SHIFT;
+  const uint32_t jl = (hi - 1) >> LINE_SHIFT;
+#pragma unroll
+  for (int it = 0; it < N; it++) k[it] = 0;
+  if (jl >= jf) {
+    const uint32_t ns = jl - jf + 1;
+    if (ns <= (uint32_t)L2_CAP) {
+      wave_stage(stage, sp + jf, ns, lane);
+      wave_lds_sync();
+      count_le<N>(stage, ns, x, k);
+      wave_lds_sync();
+    } else {
+      count_le<N>(sp + jf, ns, x, k);
+    }
+  }
+  uint32_t p[N], e[N], q[N][3];
+#pragma unroll
+  for (int it = 0; it < N; it++) {
+    // the line's keys are pk[p, e]; a first line without keys reads pk[lo],
+    // which is larger than x
+    p[it] = k[it] ? (jf + k[it] - 1) << LINE_SHIFT : lo;
+    e[it] = (uint32_t)min<uint64_t>(hi, (uint64_t)(jf + k[it]) << LINE_SHIFT);
+    e[it] = max(e[it], p[it] + 1) - 1;
+#pragma unroll
+    for (int j = 0; j < 3; j++) q[it][j] = pk[min(p[it] + 8 * (j + 1), e[it])];
+  }
+  Four v[N][2];
+#pragma unroll
+  for (int it = 0; it < N; it++) {
+    uint32_t at = 0;
+#pragma unroll
+    for (int j = 0; j < 3; j++) at = (p[it] + 8 * (j + 1) <= e[it] && q[it][j] <= x[it]) ? 8 * (j + 1) : at;
+    // (four keys of the range from there or from its end: all the row's own)
+#pragma unroll
+    for (int j = 0; j < 2; j++) v[it][j] = *reinterpret_cast<const Four*>(pk + min(p[it] + at + 4 * j, hi - 4));
+  }
+  bool hit[N];
+#pragma unroll
+  for (int it = 0; it < N; it++) {
+    hit[it] = false;
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+#pragma unroll
+      for (int l = 0; l < 4; l++) hit[it] |= v[it][j].k[l] == x[it];
+  }
+  return count_hits<N>(hit, n, lane);
+}
+
+// Of a unit, with N driver keys a lane.
+template <int N>
 __device__ __forceinline__ uint32_t probe_unit(const Leaf2Args& a, const UnitDesc& t, uint32_t next_lo, uint32_t* stage,
                                                int lane) {
-  uint32_t c = 0;
-  const uint32_t* dk = t.drv ? a.keys[1] : a.keys[0];
+  const uint32_t* dk = (t.drv ? a.keys[1] : a.keys[0]) + t.dstart;
+  if (t.pword != UINT64_MAX)
+    return probe_bits<N>(dk, t.dcount, (t.drv ? a.pool[0] : a.pool[1]) + t.pword, t.plo, t.phi, lane);
   const uint32_t* pk = t.drv ? a.keys[0] : a.keys[1];
-  const uint64_t* pool = t.drv ? a.pool[0] : a.pool[1];
-  const uint32_t nit = (t.dcount + WAVE - 1) / WAVE;
-  uint32_t x[NIT];
-  bool v[NIT];
-#pragma unroll
-  for (int it = 0; it < NIT; it++) {
-    const uint32_t i = it * WAVE + lane;
-    v[it] = i < t.dcount;
-    x[it] = v[it] ? dk[t.dstart + i] : 0u;
-  }
-  if (t.pword != UINT64_MAX) {
-#pragma unroll
-    for (int it = 0; it < NIT; it++) {
-      if (!v[it] || x[it] < t.plo || x[it] > t.phi) continue;
-      const uint32_t dd = x[it] - t.plo;
-      c += (uint32_t)((pool[t.pword + (dd >> 6)] >> (dd & 63u)) & 1ull);
-    }
+  const uint32_t lo = t.plo, hi = t.phi == UINT32_MAX ? next_lo : t.phi;
+  const uint32_t m = hi - lo;
+  if (m == 0) return 0;
+  if (m <= (uint32_t)L2_CAP && m <= L2_STAGE_RATIO * t.dcount)
+    return probe_staged<N>(dk, t.dcount, pk + lo, m, stage, lane);
+  const uint32_t* sp = t.drv ? a.samp[0] : a.samp[1];
+  if constexpr (N <= U_IT) {
+    return probe_lines<N>(dk, t.dcount, pk, sp, lo, hi, stage, lane);
   } else {
-    const uint32_t lo = t.plo;
-    const uint32_t hi = t.phi == UINT32_MAX ? next_lo : t.phi;
-    const uint32_t m = hi - lo;
-    if (m > 0 && m <= (uint32_t)L2_CAP && m <= L2_STAGE_RATIO * t.dcount) {
-      wave_stage(stage, pk + lo, m, lane);
-      wave_lds_sync();
-      c = count_members<NIT>(stage, m, x, v, nit);
-      wave_lds_sync();
-    } else if (m > 0) {
-      // A large range: bisect the line samples inside it (staged in LDS
-      // when they fit), then search the one line that can hold x.
-      // Samples j in [jf, jl] start lines inside [lo, hi); keys before
-      // the first of them belong to the range's first, partial line.
-      const uint32_t* sp = t.drv ? a.samp[0] : a.samp[1];
-      const uint32_t jf = (lo + (1u << LINE_SHIFT) - 1) >> LINE_SHIFT;
-      const uint32_t jl = (hi - 1) >> LINE_SHIFT;
-      uint32_t k[NIT];
-#pragma unroll
-      for (int it = 0; it < NIT; it++) k[it] = 0;
-      if (jl >= jf) {
-        const uint32_t ns = jl - jf + 1;
-        if (ns <= (uint32_t)L2_CAP) {
-          wave_stage(stage, sp + jf, ns, lane);
-          wave_lds_sync();
-          count_le<NIT>(stage, ns, x, nit, k);
-          wave_lds_sync();
-        } else {
-          count_le<NIT>(sp + jf, ns, x, nit, k);
-        }
-      }
-      uint32_t pos[NIT], len[NIT];
-#pragma unroll
-      for (int it = 0; it < NIT; it++) {
-        const uint32_t sb = k[it] ? (jf + k[it] - 1) << LINE_SHIFT : lo;
-        const uint32_t se = (uint32_t)min<uint64_t>(hi, (uint64_t)(jf + k[it]) << LINE_SHIFT);
-        pos[it] = sb;
-        len[it] = se > sb ? se - sb : 0;
-      }
-#pragma unroll
-      for (int step = 0; step < (int)LINE_SHIFT; step++)
-#pragma unroll
-        for (int it = 0; it < NIT; it++)
-          if (it < (int)nit && len[it] > 1) {
-            const uint32_t half = len[it] >> 1;
-            pos[it] = (pk[pos[it] + half] <= x[it]) ? pos[it] + half : pos[it];
-            len[it] -= half;
-          }
-#pragma unroll
-      for (int it = 0; it < NIT; it++)
-        if (it < (int)nit) c += (v[it] && len[it] > 0 && pk[pos[it]] == x[it]) ? 1u : 0u;
-    }
+    // (in two parts: the keys of eight lines a lane would not fit registers)
+    return probe_lines<U_IT>(dk, U_EL, pk, sp, lo, hi, stage, lane) +
+           probe_lines<N - U_IT>(dk + U_EL, t.dcount - U_EL, pk, sp, lo, hi, stage, lane);
   }
-  return c;
 }
 
 typedef const UnitDesc __attribute__((address_space(4)))* CDesc;
@@ -1479,28 +1521,23 @@ __global__ __launch_bounds__(J_NT) void k_leaf2_count(Leaf2Args a) {
   // on, so its latency overlaps the current unit's key loads.
   // descriptors are read-only here: read through the constant address space
   const CDesc desc = (CDesc)a.desc;
-  auto unit_of = [&](uint64_t i) -> uint64_t { return LIST ? (uint64_t)a.list[i] : i; };
+  const uint32_t units = (uint32_t)a.units, stride = gridDim.x * J_NW;
+  uint32_t i = xcd_block(blockIdx.x, gridDim.x) * J_NW + w;
   UnitDesc nt{};
-  uint64_t nu = 0;
-  uint32_t nlo = 0;
-  const uint64_t vb0 = xcd_block(blockIdx.x, gridDim.x);
-  if (vb0 < a.nvblk && vb0 * J_NW + w < a.units) {
-    nu = unit_of(vb0 * J_NW + w);
+  uint32_t nu = 0, nlo = 0;
+  bool more = i < units;
+  auto load_unit = [&](uint32_t k) {
+    nu = LIST ? a.list[k] : k;
     nt = load_desc(desc, nu);
-    nlo = (nu + 1 < a.n_desc) ? desc[nu + 1].plo : 0u;
-  }
-  for (uint64_t vb = vb0; vb < a.nvblk; vb += gridDim.x) {
-    const uint64_t i = vb * J_NW + w;
-    const uint64_t u = nu;
+    nlo = desc[nu + 1].plo;
+  };
+  if (more) load_unit(i);
+  while (more) {
+    const uint32_t u = nu, next_lo = nlo;
     const UnitDesc t = nt;
-    const uint32_t next_lo = nlo;
-    const uint64_t in = (vb + gridDim.x) * J_NW + w;
-    if (vb + gridDim.x < a.nvblk && in < a.units) {
-      nu = unit_of(in);
-      nt = load_desc(desc, nu);
-      nlo = (nu + 1 < a.n_desc) ? desc[nu + 1].plo : 0u;
-    }
-    if (i >= a.units) continue;      // wave-uniform; no barrier inside the loop
+    more = units - i > stride;
+    i += stride;
+    if (more) load_unit(i);
     if (!LIST && t.top) continue;    // the top bucket's own launch runs it
     uint32_t c = 0;
     if (t.drv == DRV_AND) {
@@ -1511,7 +1548,17 @@ __global__ __launch_bounds__(J_NT) void k_leaf2_count(Leaf2Args a) {
         if (k < t.dcount) c += (uint32_t)__popcll(a.pool[0][w0 + k] & a.pool[1][t.pword + k]);
       }
     } else {
-      c = probe_unit<NIT>(a, t, next_lo, stage, lane);
+      const uint32_t nit = (t.dcount + WAVE - 1) / WAVE;  // 1..NIT
+      switch (nit) {
+        case 1: c = probe_unit<1>(a, t, next_lo, stage, lane); break;
+        case 2: c = probe_unit<2>(a, t, next_lo, stage, lane); break;
+        case 3: c = probe_unit<3>(a, t, next_lo, stage, lane); break;
+        case 4: c = probe_unit<4>(a, t, next_lo, stage, lane); break;
+        case 5: if constexpr (NIT >= 5) c = probe_unit<5>(a, t, next_lo, stage, lane); break;
+        case 6: if constexpr (NIT >= 6) c = probe_unit<6>(a, t, next_lo, stage, lane); break;
+        case 7: if constexpr (NIT >= 7) c = probe_unit<7>(a, t, next_lo, stage, lane); break;
+        default: if constexpr (NIT >= 8) c = probe_unit<8>(a, t, next_lo, stage, lane); break;
+      }
     }
     if (a.ucnt) {
       // grouped: one count per unit; groups are summed by a scan afterwards
@@ -2761,7 +2808,7 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
     if (total) {
       if (leaf2) {
         // two sets, set semantics: per-unit descriptors, one load per wave
-        DBuf<UnitDesc> desc(dw.units, s);
+        DBuf<UnitDesc> desc(dw.units + 1, s);  // (one more: a unit reads the next one's plo)
         WorkArgs wa{};
         wa.np = 2;
         wa.set[0] = a.set[0];
@@ -2795,8 +2842,6 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
         l2.desc = desc.p;
         l2.gcount = L.gcount;
         l2.units = dw.units;
-        l2.n_desc = dw.units;
-        l2.nvblk = nblk;
         DBuf<uint64_t> ucnt(L.gid ? dw.units : 0, s);
         l2.ucnt = ucnt.p;
         {
@@ -2808,9 +2853,8 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
           Leaf2Args lt = l2;
           lt.list = top_list.p;
           lt.units = top_units;
-          lt.nvblk = (top_units + J_NW - 1) / J_NW;
           ProfScope ps("leaf_top", s, top_units, 0);
-          k_leaf2_count<true, TOP_IT><<<leaf_grid(lt.nvblk), J_NT, 0, s>>>(lt);
+          k_leaf2_count<true, TOP_IT><<<leaf_grid((top_units + J_NW - 1) / J_NW), J_NT, 0, s>>>(lt);
         }
         LH_HIP(hipGetLastError());
         if (merge_units) {
