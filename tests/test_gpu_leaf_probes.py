@@ -1,7 +1,9 @@
 """The two-set COUNT leaf's probes of sorted sets at the edges of their forms:
 one to five driver keys a lane, probed ranges that are staged whole, searched
 through staged samples or through samples in memory, lines cut by a range's
-ends, and values at both ends of the key range.  Counts must equal numpy's."""
+ends, values at both ends of the key range, and bitsets that are probed as
+bitsets or, sparse and hardly larger than the driver, by their sorted keys.
+Counts must equal numpy's."""
 import sys
 
 import numpy as np
@@ -27,7 +29,7 @@ PROBED = [1, 3, 8, 9, 31, 32, 33, 64, 500, 1023, 1024, 1025, 2600, 9000, 40_000]
 
 @pytest.mark.parametrize("space", [60_000, 1 << 32])
 @pytest.mark.parametrize("grouped", [False, True])
-@pytest.mark.parametrize("layout", ["uint", "plain"])
+@pytest.mark.parametrize("layout", ["uint", "plain", "bitset"])
 def test_probes(lh, space, grouped, layout):
     print(space, grouped, layout, file=sys.stderr, flush=True)
     rng = synth.rng_for(500)
