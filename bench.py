@@ -282,7 +282,8 @@ def main():
                 "avg_launch_ms": round(avg_ms, 4), "top_bucket_ms": round(top_ms, 4), "top_bucket": top_bucket,
                 "merge_ms": round(prof.get("leaf_merge", {"total_ms": 0.0})["total_ms"] / e["launches"], 4),
                 "alg_bytes_per_launch": int(b_min),
-                "alg_bytes": "minimum bytes: 4 B per wedge (S(b) streamed per edge) + 4 B per edge (T(a) once) + "
+                "alg_bytes": "bytes with no reuse in the caches (with it, the rate can pass the peak; traffic is "
+                             "measured): 4 B per wedge (S(b) streamed per edge) + 4 B per edge (T(a) once) + "
                              "8 B per vertex (offsets)",
                 "model_bytes_per_launch": int(model_bytes),
                 "model_frac": round(model_bytes / (avg_ms / 1000) / 1e9 / HBM_PEAK_GBS, 4),

@@ -138,16 +138,6 @@ __device__ __forceinline__ bool sampled_find(const uint32_t* keys, const uint32_
   return keys[lo] == x;
 }
 
-// First position in the sorted keys [b, e) holding a key >= x (e if none),
-// through the line samples.
-__device__ __forceinline__ uint32_t sampled_lower_bound(const uint32_t* keys, const uint32_t* samp, uint32_t b,
-                                                        uint32_t e, uint32_t x) {
-  if (b >= e) return b;
-  uint32_t pos = b;
-  if (sampled_find(keys, samp, b, e, x, pos)) return pos;
-  return keys[pos] < x ? pos + 1 : pos;
-}
-
 // Membership of x in set [b, e) (descriptor sidx); its position if asked.
 __device__ __forceinline__ bool dset_find(const DSet& st, uint32_t b, uint32_t e, uint64_t sidx, uint32_t x,
                                           bool need_pos, uint32_t& pos) {
@@ -1165,17 +1155,6 @@ struct UnitDesc {
   uint32_t top;      // 1: the unit's row is in the top bucket; 2: a merge tile (each class
                      // runs as a launch of its own)
 };
-
-
-
-// First index in [lo, hi) whose value is > x (hi if none).
-__device__ __forceinline__ uint32_t upper_bound_u32(const uint32_t* a, uint32_t lo, uint32_t hi, uint32_t x) {
-  while (lo < hi) {
-    uint32_t mid = lo + (hi - lo) / 2;
-    if (a[mid] <= x) lo = mid + 1; else hi = mid;
-  }
-  return lo;
-}
 
 // Merge path: the number of elements of the sorted a[0, na) among the
 // first d elements of the merge of a and b[0, nb), where an element of a

@@ -15,8 +15,6 @@ constexpr int SC_NT = 256;
 constexpr int SC_ITEMS = 8;
 constexpr int SC_TILE = SC_NT * SC_ITEMS;
 
-inline unsigned blocks_for(uint64_t n, uint64_t per) { return (unsigned)((n + per - 1) / per); }
-
 // Device-wide exclusive scans.  Launches and host round trips bound the
 // short ones (a launch costs 2 to 3 us of a dependent chain, a read-back of
 // a device scalar 15 us), so a scan is one kernel up to SC_ONE elements, two
