@@ -127,17 +127,26 @@ __global__ void k_inst_roots(BInst* inst, uint32_t n) {
   }
 }
 
-// Products of entry q of A's second level.
-__device__ __forceinline__ uint64_t entry_products(const BInst& I, uint32_t q) {
+// Products of entry q of A's second level: pairs of a row of A and a row of
+// E (bags may repeat a key pair on either side).  outs: at most this many
+// outputs (E's keys k under the entry).
+__device__ __forceinline__ uint64_t entry_products(const BInst& I, uint32_t q, uint64_t& outs) {
   uint32_t pe;
   if (!find_j(I, I.a_j[q], pe)) return 0;
   uint32_t ab, ae, eb, ee;
   rows_of(I.a_run, q, ab, ae);
   if (I.kind == 0) {
     rows_of(I.e_run, pe, eb, ee);
-    return (uint64_t)(ae - ab) * (ee - eb);
+  } else {
+    eb = I.e_off[pe];
+    ee = I.e_off[pe + 1];
+    outs += ee - eb;
+    if (I.e_run) {
+      eb = I.e_run[eb];
+      ee = I.e_run[ee];
+    }
   }
-  return (uint64_t)(ae - ab) * (I.e_off[pe + 1] - I.e_off[pe]);
+  return (uint64_t)(ae - ab) * (ee - eb);
 }
 
 // Every row's instance, products and output bound.  A thread walks a row of
@@ -163,9 +172,9 @@ __global__ __launch_bounds__(B_NT) void k_row_products(const BInst* inst, const 
       len = inst[ii].a_off[p + 1] - qb;
       row_inst[t] = ii;
     }
-    uint64_t u = 0;
+    uint64_t u = 0, o = 0;
     if (len <= ROW_THREAD) {
-      for (uint32_t q = qb; q < qb + len; q++) u += entry_products(inst[ii], q);
+      for (uint32_t q = qb; q < qb + len; q++) u += entry_products(inst[ii], q, o);
     } else if (len > ROW_WAVE) {
       s_long[atomicAdd(&s_n, 1u)] = threadIdx.x;
     }
@@ -173,10 +182,14 @@ __global__ __launch_bounds__(B_NT) void k_row_products(const BInst* inst, const 
       const int l = __builtin_ctzll(m);
       const BInst& I = inst[__shfl((int)ii, l, WAVE)];
       const uint32_t b = (uint32_t)__shfl((int)qb, l, WAVE), n = (uint32_t)__shfl((int)len, l, WAVE);
-      uint64_t v = 0;
-      for (uint32_t k = lane; k < n; k += WAVE) v += entry_products(I, b + k);
+      uint64_t v = 0, vo = 0;
+      for (uint32_t k = lane; k < n; k += WAVE) v += entry_products(I, b + k, vo);
       v = wave_sum(v);
-      if (lane == l) u = v;
+      vo = wave_sum(vo);
+      if (lane == l) {
+        u = v;
+        o = vo;
+      }
     }
     __syncthreads();
     for (uint32_t i = 0; i < s_n; i++) {  // uniform over the block
@@ -185,18 +198,22 @@ __global__ __launch_bounds__(B_NT) void k_row_products(const BInst* inst, const 
       const BInst& I = inst[il];
       const uint32_t p = (uint32_t)(tl - inst_row0[il]);
       const uint32_t b = I.a_off[p], e = I.a_off[p + 1];
-      uint64_t v = 0;
+      uint64_t v = 0, vo = 0;
       for (uint32_t k = b + threadIdx.x; k < e; k += 4 * B_NT) {
 #pragma unroll
         for (int j = 0; j < 4; j++)
-          if (k + j * B_NT < e) v += entry_products(I, k + j * B_NT);
+          if (k + j * B_NT < e) v += entry_products(I, k + j * B_NT, vo);
       }
       v = block_sum<uint64_t, B_NT>(v, s_red);
-      if (threadIdx.x == s_long[i]) u = v;
+      vo = block_sum<uint64_t, B_NT>(vo, s_red);
+      if (threadIdx.x == s_long[i]) {
+        u = v;
+        o = vo;
+      }
     }
     if (t < R) {
       prod[t] = u;
-      ub[t] = inst[ii].kind == 0 ? 1u : (uint32_t)min<uint64_t>(u, inst[ii].n_k);
+      ub[t] = inst[ii].kind == 0 ? 1u : (uint32_t)min<uint64_t>(o, inst[ii].n_k);
     }
     __syncthreads();  // s_long and s_n are free again
   }
