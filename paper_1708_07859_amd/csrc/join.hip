@@ -517,6 +517,20 @@ __device__ __forceinline__ bool next_combo(const LeafArgs& L, const HitRows<NA>&
   return !carry;
 }
 
+// Sum of the lanes' counts, over the wave (whole) or the unit; flags a sum, or
+// a lane (they saturate), that does not fit 64 bits.
+template <int LPR>
+__device__ __forceinline__ uint64_t sum_counts(uint64_t v, bool whole, uint32_t& bad) {
+  auto sum = [&](uint64_t x) { return whole ? wave_sum(x) : unit_sum<LPR>(x); };
+  // 64 counts below 2^58 cannot leave 64 bits; larger ones are summed by halves
+  if (__any(v >= (1ull << 58))) {
+    const uint64_t lo = sum(v & 0xffffffffull), hi = sum(v >> 32) + (lo >> 32);
+    if (v == UINT64_MAX || hi >> 32) bad |= ERR_COUNT_OVERFLOW;
+    return (hi << 32) | (lo & 0xffffffffull);
+  }
+  return sum(v);
+}
+
 // A unit's carried count and sum into its group's slots: stored when `only`
 // (the group is this unit's row's, which has no other unit; normalized
 // digits are a valid shared-form value), else added; `whole`: by the wave,
@@ -524,9 +538,7 @@ __device__ __forceinline__ bool next_combo(const LeafArgs& L, const HitRows<NA>&
 template <int LPR>
 __device__ __forceinline__ void flush_group(uint64_t& run_cnt, RegAcc& run_acc, uint64_t* count, int64_t* slots,
                                             bool sum, uint32_t D, bool only, bool whole, uint32_t* err, uint32_t& bad) {
-  // lane counts below 2^58 cannot wrap the sum over the lanes
-  if (run_cnt >= (1ull << 58)) bad |= ERR_COUNT_OVERFLOW;
-  const uint64_t cnt = whole ? wave_sum(run_cnt) : unit_sum<LPR>(run_cnt);
+  const uint64_t cnt = sum_counts<LPR>(run_cnt, whole, bad);
   const bool writer = whole ? lane_id() == 0 : lane_id() % LPR == 0;
   if (writer && only) *count = cnt;
   else if (writer && cnt) atomic_add_count(count, cnt, err);
@@ -773,8 +785,7 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
           } while (next_combo(L, h, cur));
         }
       }
-      if (cnt == UINT64_MAX) bad |= ERR_COUNT_OVERFLOW;
-      run_cnt = sat_add_u64(run_cnt, cnt);
+      run_cnt = sat_add_u64(run_cnt, cnt);  // (a saturated count is flagged where it is summed)
       if (!one_group && unit_valid && L.own_group && work <= UNIT_EL) {
         flush_group<LPR>(run_cnt, run_acc, L.gcount + g, L.gacc + g * EXACT_MAXD, L.sum, L.D, true, false, L.err, bad);
         run_g = UINT64_MAX;
@@ -1027,12 +1038,10 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
   if (MODE == M_LEAF_A && !one_group)
     end_groups<LPR>(run_g != UINT64_MAX, run_g, run_cnt, run_acc, L.gcount, L.gacc, L.sum, L.D, L.err, bad);
   if (LEAF_AGG) {
-    if (bad) atomicOr(L.err, bad);
     if (one_group) {
       // reduce the block into LDS, one flush per block
       __syncthreads();
-      if (__any(run_cnt >= (1ull << 58))) atomicOr(L.err, ERR_COUNT_OVERFLOW);
-      const uint64_t c = wave_sum(run_cnt);
+      const uint64_t c = sum_counts<WAVE>(run_cnt, true, bad);
       if (lane == 0 && c) atomic_add_count((uint64_t*)&s_cnt, c, L.err);
       if (MODE == M_LEAF_A && L.sum) run_acc.normalize(L.D);
       if (MODE == M_LEAF_A && L.sum)
@@ -1052,6 +1061,7 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
         }
       }
     }
+    if (bad) atomicOr(L.err, bad);
   }
 }
 
