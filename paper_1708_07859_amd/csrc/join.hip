@@ -235,6 +235,7 @@ struct ElemArgs {
   const uint32_t* urow;   // row of each unit
   uint64_t total_units;
   uint64_t nvblk;         // virtual blocks of J_NW waves of units
+  uint32_t vrun;          // of them next to each other that a block takes at a time
   uint32_t lanes;         // lanes per unit (WAVE or SUB_LANES)
   uint32_t need_pos_mask; // participants whose position is needed
   // fill
@@ -622,14 +623,11 @@ __global__ __launch_bounds__(J_NT) void k_elem(ElemArgs a) {
   run_acc.clear();
   uint64_t run_g = UINT64_MAX;
   uint32_t bad = 0;
-  // carried units are taken from one contiguous range per block
-  const uint64_t vper = MODE == M_LEAF_A ? (a.nvblk + gridDim.x - 1) / gridDim.x : 1;
-  const uint64_t vstep = MODE == M_LEAF_A ? 1 : gridDim.x;
-  const uint64_t vend = MODE == M_LEAF_A ? min<uint64_t>(a.nvblk, (blockIdx.x + 1) * vper) : a.nvblk;
-
   // The grid is capped (a dispatch holds < 2^32 work-items); each block
-  // walks virtual blocks of J_NW waves of units.
-  for (uint64_t vb = blockIdx.x * vper; vb < vend; vb += vstep) {
+  // walks virtual blocks of J_NW waves of units, a.vrun next to each other at
+  // a time (carried units meet their group's).
+  for (uint64_t v0 = (uint64_t)blockIdx.x * a.vrun; v0 < a.nvblk; v0 += (uint64_t)gridDim.x * a.vrun)
+    for (uint64_t vb = v0, v1 = min<uint64_t>(a.nvblk, v0 + a.vrun); vb < v1; vb++) {
     const uint64_t u = (vb * J_NW + w) * UPW + lane / LPR;
     const bool unit_valid = u < a.total_units;
 
@@ -2090,10 +2088,22 @@ __global__ void k_seg_accumulate(SegAccArgs a, uint64_t n) {
 }
 
 // A dispatch counts work-items in 32 bits: cap the grid and let blocks
-// stride over virtual blocks.  Blocks that carry sums take contiguous
-// ranges, long enough that a hub row's units meet in few of them.
-constexpr uint64_t CARRY_BLOCKS = 2048;
+// stride over virtual blocks.
 unsigned elem_grid(uint64_t nvblk) { return (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(nvblk, 32768)); }
+// Blocks that carry grouped sums take up to CARRY_RUN virtual blocks next to
+// each other, so that a hub row's units meet in fewer of them, and stride over
+// the rest: long runs of an expanding atom often lie near each other (the
+// repeated edges of low vertices, popular items), and a block that took
+// a 2048th of all units had them alone.  Microseconds with 1 / 2 / 4 / 8 next
+// to each other, with such ranges, and with a wave per row (before carrying):
+//   SpMV, 250,000 power-law rows (no runs)      465 /  446 /  434 /  475,   447,  2241
+//   SUM over hub rows (no runs)                5555 / 4852 / 4558 / 4363,  4465, 12889
+//   SpMV, R-MAT scale 20 with its repeats      1507 / 1504 / 1855 / 2665,  8024,  3723
+//   24 M rows of runs in 4000 of 2 M rows      1982 / 3701 / 7200 / 13985, 53442, 11872
+// One group needs no neighbours: SUM over R-MAT scale 18 paths of two takes
+// 50 ms, 531 with ranges, 92 with a wave per row.
+constexpr uint64_t CARRY_BLOCKS = 2048, CARRY_MAX_BLOCKS = 8192;
+constexpr uint64_t CARRY_RUN = 4;
 // The merge launch: as many blocks as fit on the device at once; each loops
 // over a contiguous range of tiles, loading the next while counting one.
 unsigned merge_grid() {
@@ -2244,6 +2254,7 @@ void depth_work(const lh_plan_t* p, uint32_t d, const Frontier& F, ElemArgs& a, 
   const uint64_t per_block = (uint64_t)J_NW * (WAVE / a.lanes);
   dw.nblk = (dw.units + per_block - 1) / per_block;
   a.nvblk = dw.nblk;
+  a.vrun = 1;
   a.work = dw.work.p;
   a.drv = dw.drv.p;
   a.nrows = F.n;
@@ -2883,7 +2894,11 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
       } else {
         ProfScope ps("leaf_aggregate", s, F.n, total);
         if (all_set) launch_elem<M_LEAF_COUNT>(a, elem_grid(nblk), s);
-        else launch_elem<M_LEAF_A>(a, (unsigned)std::min<uint64_t>(nblk, CARRY_BLOCKS), s);
+        else {
+          if (L.gid) a.vrun = (uint32_t)std::min<uint64_t>(CARRY_RUN, (nblk + CARRY_BLOCKS - 1) / CARRY_BLOCKS);
+          const uint64_t runs = (nblk + a.vrun - 1) / a.vrun;
+          launch_elem<M_LEAF_A>(a, (unsigned)std::min<uint64_t>(runs, CARRY_MAX_BLOCKS), s);
+        }
       }
       LH_HIP(hipGetLastError());
     }
