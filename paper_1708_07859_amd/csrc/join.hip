@@ -36,8 +36,15 @@ constexpr int U_EL = WAVE * U_IT;  // driver elements per unit of a whole wave
 // SpMV of 250,000 power-law rows (4 M entries): the leaf 1.56 -> 0.23 ms,
 // with sums stored by a row's only unit and carried over a hub row's units;
 // Q5 shape at 24 M rows: its three SUM leaves 1.6 -> 0.33 ms.
+// A frontier need not hold the level's average rows: where the first count
+// finds them longer than a wave's unit on average, a fill counts again in
+// whole waves (hubs of 20,000 keys below an average of 11: 1.91 -> 1.40 ms, a
+// wave per unit at first 1.67), and so does a leaf with more than
+// SUB_MAX_UNITS units (their rows take four bytes each; below, leaves are as
+// fast or faster with eight lanes: 4.48 and 4.58 ms).
 constexpr int SUB_LANES = 8;
 constexpr uint64_t SUB_AVG = 24;
+constexpr uint64_t SUB_MAX_UNITS = 1ull << 28;
 // Two-set leaves: rows whose two sets hold TOP_MIN elements or more
 // together form the top bucket, the largest intersections.  They run as a
 // launch of their own.  Units of TOP_IT elements per lane (twice the loads
@@ -2199,7 +2206,7 @@ void root_work(const lh_plan_t* p, const std::vector<Participant>& parts, ElemAr
 }
 
 void depth_work(const lh_plan_t* p, uint32_t d, const Frontier& F, ElemArgs& a, DepthWork& dw, hipStream_t s,
-                bool leaf2 = false) {
+                bool fill, bool leaf2) {
   const auto& parts = p->parts[d];
   WorkArgs wa{};
   wa.np = (uint32_t)parts.size();
@@ -2214,7 +2221,7 @@ void depth_work(const lh_plan_t* p, uint32_t d, const Frontier& F, ElemArgs& a, 
     const Level& L = p->atoms[pt.atom].trie->lv[pt.level];
     avg = std::min(avg, L.n / std::max<uint64_t>(1, L.n_sets));
   }
-  a.lanes = !leaf2 && wa.np <= 4 && avg <= SUB_AVG ? SUB_LANES : WAVE;
+  a.lanes = !leaf2 && wa.np <= 4 && avg <= SUB_AVG && !arena_tight() ? SUB_LANES : WAVE;
   if (d == 0 && !leaf2) {
     root_work(p, parts, a, dw);
   } else {
@@ -2225,22 +2232,27 @@ void depth_work(const lh_plan_t* p, uint32_t d, const Frontier& F, ElemArgs& a, 
     const unsigned nb = std::min(grid_for(F.n), 4096u);
     DBuf<WorkTotals> part(nb, s);
     HostOut<WorkTotals> out(s);
-    {
-      ProfScope ps("join_work", s, F.n, 0);
-      const uint32_t el = a.lanes * U_IT, l2 = leaf2 ? 1u : 0u;
-      if (wa.np <= 2) k_work<2><<<nb, 256, 0, s>>>(wa, F.n, dw.work.p, dw.drv.p, units.p, el, l2, part.p);
-      else if (wa.np <= 4) k_work<4><<<nb, 256, 0, s>>>(wa, F.n, dw.work.p, dw.drv.p, units.p, el, l2, part.p);
-      else k_work<MAXP><<<nb, 256, 0, s>>>(wa, F.n, dw.work.p, dw.drv.p, units.p, el, l2, part.p);
+    for (;;) {
+      {
+        ProfScope ps("join_work", s, F.n, 0);
+        const uint32_t el = a.lanes * U_IT, l2 = leaf2 ? 1u : 0u;
+        if (wa.np <= 2) k_work<2><<<nb, 256, 0, s>>>(wa, F.n, dw.work.p, dw.drv.p, units.p, el, l2, part.p);
+        else if (wa.np <= 4) k_work<4><<<nb, 256, 0, s>>>(wa, F.n, dw.work.p, dw.drv.p, units.p, el, l2, part.p);
+        else k_work<MAXP><<<nb, 256, 0, s>>>(wa, F.n, dw.work.p, dw.drv.p, units.p, el, l2, part.p);
+      }
+      LH_HIP(hipGetLastError());
+      scan_u32_to_u64_dev(units.p, dw.U.p, F.n, s);
+      k_work_totals<<<1, 256, 0, s>>>(part.p, nb, dw.U.p + F.n, out.p());
+      LH_HIP(hipGetLastError());
+      const WorkTotals h = out.get();
+      dw.units = h.units;
+      dw.total = h.work;
+      dw.top = h.top;
+      dw.merge = h.merge;
+      const bool long_rows = h.work / U_EL > F.n;
+      if (a.lanes == WAVE || !(h.units >= (1ull << 32) || (long_rows && (fill || h.units > SUB_MAX_UNITS)))) break;
+      a.lanes = WAVE;
     }
-    LH_HIP(hipGetLastError());
-    scan_u32_to_u64_dev(units.p, dw.U.p, F.n, s);
-    k_work_totals<<<1, 256, 0, s>>>(part.p, nb, dw.U.p + F.n, out.p());
-    LH_HIP(hipGetLastError());
-    const WorkTotals h = out.get();
-    dw.units = h.units;
-    dw.total = h.work;
-    dw.top = h.top;
-    dw.merge = h.merge;
   }
   if (dw.units >= (1ull << 32)) fail(LH_ERR_OVERFLOW, "join: more than 2^32 work units at one attribute");
   if (dw.units && !a.single) {
@@ -2274,7 +2286,7 @@ bool binds_by(const lh_plan_t* p, uint32_t atom, uint32_t d) {
 void step(const lh_plan_t* p, uint32_t d, Frontier& F, hipStream_t s) {
   ElemArgs a{};
   DepthWork dw;
-  depth_work(p, d, F, a, dw, s);
+  depth_work(p, d, F, a, dw, s, true, false);
   const uint64_t total = dw.total;
   if (total == 0) {
     F.n = 0;
@@ -2760,7 +2772,7 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
   bool all_set = !is_sum;
   for (const auto& A : p->atoms) all_set = all_set && !A.bag;
   const bool leaf2 = p->case_prefix && all_set && p->parts[leaf].size() == 2;
-  if (F.n) depth_work(p, leaf, F, a, dw, s, leaf2);
+  if (F.n) depth_work(p, leaf, F, a, dw, s, false, leaf2);
   const uint64_t total = dw.total;
   const uint64_t nblk = dw.nblk;
   if (nblk >= (1ull << 31)) fail(LH_ERR_OVERFLOW, "join: too much work at the last attribute");
