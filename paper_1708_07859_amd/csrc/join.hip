@@ -2037,10 +2037,30 @@ struct JoinEnd {
   uint64_t rows, err, n_join;
 };
 
-// Up to this many possible groups the result's buffers are sized for all of
-// them, and their number is read with the rest at the end of the join: a wait
-// less (about 10 us), for at most 60 bytes a row.
+// Up to this many possible groups, and bytes of result rows for them, the
+// result's buffers are sized for all of them, and their number is read with
+// the rest at the end of the join: a wait less (about 10 us).  A result that
+// turns out to fill less than a quarter of buffers past KEEP_BYTES moves to
+// smaller ones, since it may be kept for long.
 constexpr uint64_t CAP_ROWS = 1u << 18;
+constexpr uint64_t CAP_BYTES = 16u << 20;
+constexpr uint64_t KEEP_BYTES = 1u << 20;
+
+uint64_t result_row_bytes(const lh_plan_t* p, uint32_t n_cols, bool is_sum) {
+  return 4ull * n_cols + 8 + (is_sum ? 8 + (p->want_parts ? 8ull * EXACT_PARTS : 0) : 0);
+}
+
+bool size_for_all(uint64_t groups, uint64_t row_bytes) {
+  return groups <= CAP_ROWS && groups * row_bytes <= CAP_BYTES && !arena_tight();
+}
+
+template <class T>
+void shrink_to(DBuf<T>& b, uint64_t n, hipStream_t s) {
+  if (!b.p) return;
+  DBuf<T> t(n, s);
+  if (n) LH_HIP(hipMemcpyAsync(t.p, b.p, n * sizeof(T), hipMemcpyDeviceToDevice, s));
+  b = std::move(t);
+}
 
 __global__ void k_join_end(const uint64_t* rows, const uint64_t* ctl, JoinEnd* out) {
   *out = JoinEnd{rows ? *rows : 0ull, ctl[0], ctl[1]};
@@ -2577,7 +2597,7 @@ bool group_in_place(const lh_plan_t* p, const Frontier& F, ElemArgs& a, uint64_t
     off.alloc(tiles + 1, s);
     k_used_counts<<<tiles, GU_NT, 0, s>>>(DenseUsed{L.gacc, L.gstride}, n_ent, used.p);
     LH_HIP(hipGetLastError());
-    if (n_ent <= CAP_ROWS && !arena_tight()) {
+    if (size_for_all(n_ent, result_row_bytes(p, n_cols, is_sum))) {
       scan_u32_to_u64_dev(used.p, off.p, tiles, s);
       n_groups = n_ent;
       rows_at = off.p + tiles;
@@ -2932,7 +2952,7 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
       k_used_counts<<<tiles, GU_NT, 0, s>>>(DenseUsed{reinterpret_cast<const int64_t*>(gcount), 1}, nfin, used.p);
       LH_HIP(hipGetLastError());
       f.off = off.p;
-      if (nfin <= CAP_ROWS && !arena_tight()) {
+      if (size_for_all(nfin, result_row_bytes(p, n_cols, is_sum))) {
         scan_u32_to_u64_dev(used.p, off.p, tiles, s);
         n_out_rows = nfin;
         rows_at = off.p + tiles;
@@ -3083,7 +3103,17 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
   const JoinEnd end = out.get();
   if (end.err & ERR_COUNT_OVERFLOW) fail(LH_ERR_OVERFLOW, "join: a tuple count exceeds 2^64 - 1");
   if (end.err) fail(LH_ERR_UNSUPPORTED, "an annotation product did not fit the exact accumulator");
-  if (rows_at) R.n_rows = end.rows;
+  if (rows_at) {
+    const uint64_t cap = R.n_rows;
+    R.n_rows = end.rows;
+    if (!arena_active() && end.rows < cap / 4 && cap * result_row_bytes(p, n_cols, is_sum) > KEEP_BYTES) {
+      for (DBuf<uint32_t>& c : res->cols) shrink_to(c, end.rows, s);
+      shrink_to(res->counts, end.rows, s);
+      shrink_to(res->sums, end.rows, s);
+      shrink_to(res->parts, end.rows * EXACT_PARTS, s);
+      LH_HIP(hipStreamSynchronize(s));
+    }
+  }
 
   res->colptr.resize(n_cols);
   for (uint32_t c = 0; c < n_cols; c++) res->colptr[c] = res->cols[c].p;
