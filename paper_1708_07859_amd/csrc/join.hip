@@ -2439,18 +2439,20 @@ bool group_in_place(const lh_plan_t* p, const Frontier& F, ElemArgs& a, uint64_t
     bits[c] = bitlen(top[c]);
     space = (space > (1ull << 62) / L.radix[c]) ? (1ull << 62) : space * L.radix[c];
   }
+  constexpr uint64_t dense_limit = 2ull << 30, hash_limit = 16ull << 30;
   const uint64_t dense_bytes = 8 + (is_sum ? 8ull * D : 0);
-  const bool dense_fits = space <= (1ull << 27) && space * dense_bytes <= (2ull << 30);
+  const bool dense_fits = space <= (1ull << 27) && space * dense_bytes <= dense_limit;
   if (impl == 0) impl = (dense_fits && space <= std::max<uint64_t>(4 * total, 1u << 16)) ? 3 : 2;
   if (impl == 3 && !dense_fits) fail(LH_ERR_UNSUPPORTED, "join: the GROUP BY key space is too large for a dense array");
-  const uint64_t hash_bytes = 4 + 4ull * n_cols + 8 + (is_sum ? 8ull * D : 0);  // an upper bound
+  // an upper bound where slots are not padded (below they are only where that fits as well)
+  const uint64_t hash_bytes = 4 + 4ull * n_cols + 8 + (is_sum ? 8ull * D : 0);
   uint64_t cap = 1024;
   if (impl == 2) {
     // (a power of two: two thirds full at most, by the estimate)
     const uint64_t keys = std::min<uint64_t>(space, std::max<uint64_t>(total, 512));
     const uint64_t want = keys + keys / 2;
     while (cap < want) cap <<= 1;
-    if (cap > (1ull << 31) || cap * hash_bytes > (16ull << 30)) return false;
+    if (cap > (1ull << 31) || cap * hash_bytes > hash_limit) return false;
   }
   L.n_cols = n_cols;
   L.gmode = impl == 3 ? 1u : 2u;
@@ -2472,9 +2474,9 @@ bool group_in_place(const lh_plan_t* p, const Frontier& F, ElemArgs& a, uint64_t
   }
   L.gsigned = most < SIGNED_TERMS ? 1u : 0u;
   L.gplain = L.gsigned && once ? 1u : 0u;
-  L.gpack = L.gplain && is_sum && D <= 7 && !L.glds && !arena_tight() ? 1u : 0u;
-  L.gstride = 1 + (is_sum ? D : 0u);
-  if (L.gpack) L.gstride = L.gstride <= 2 ? 2u : L.gstride <= 4 ? 4u : 8u;
+  const bool can_pad = L.gplain && is_sum && D <= 7 && !L.glds && !arena_tight();
+  const uint32_t plain_words = 1 + (is_sum ? D : 0u);
+  const uint32_t padded_words = plain_words <= 2 ? 2u : plain_words <= 4 ? 4u : 8u;
   DBuf<uint32_t> tag;
   std::vector<DBuf<uint32_t>> tkeys;
   DBuf<uint64_t> key64;
@@ -2494,27 +2496,38 @@ bool group_in_place(const lh_plan_t* p, const Frontier& F, ElemArgs& a, uint64_t
   uint64_t n_groups = 0;
   for (;;) {
     const uint64_t n = impl == 3 ? space : cap;
-    // the slots, then the control words (padded slots stay on their lines)
-    ctl.alloc(n * L.gstride + 2, s);
+    const uint64_t key_bytes = impl == 3 ? 0 : packed ? 8 : 4 + 4ull * n_cols;
+    auto make_slots = [&](bool pad) {
+      L.gpack = pad ? 1u : 0u;
+      L.gstride = pad ? padded_words : plain_words;
+      // the slots, then the control words (padded slots stay on their lines)
+      ctl.alloc(n * L.gstride + 2, s);
+      if (impl == 2 && packed) key64.alloc(n, s);
+      if (impl == 2 && !packed) {
+        tag.alloc(n, s);
+        tkeys.clear();
+        for (uint32_t c = 0; c < n_cols; c++) tkeys.emplace_back(n, s);
+      }
+    };
+    const bool pad = can_pad && n * (8ull * padded_words + key_bytes) <= (impl == 3 ? dense_limit : hash_limit);
+    try {
+      make_slots(pad);
+    } catch (const Error& e) {
+      if (e.status != LH_ERR_OOM || !pad) throw;
+      make_slots(false);
+    }
     LH_HIP(hipMemsetAsync(ctl.p, 0, ctl.n * sizeof(uint64_t), s));
     ctl_at = ctl.p + n * L.gstride;
     L.err = reinterpret_cast<uint32_t*>(ctl_at);
     L.gacc = reinterpret_cast<int64_t*>(ctl.p);
+    L.gmask = n - 1;
     if (impl == 2 && packed) {
-      key64.alloc(n, s);
       LH_HIP(hipMemsetAsync(key64.p, 0xff, n * sizeof(uint64_t), s));
       L.gkey64 = key64.p;
-      L.gmask = n - 1;
     } else if (impl == 2) {
-      tag.alloc(n, s);
       LH_HIP(hipMemsetAsync(tag.p, 0, n * sizeof(uint32_t), s));
-      tkeys.clear();
-      for (uint32_t c = 0; c < n_cols; c++) {
-        tkeys.emplace_back(n, s);
-        L.col_out[c] = tkeys.back().p;
-      }
+      for (uint32_t c = 0; c < n_cols; c++) L.col_out[c] = tkeys[c].p;
       L.gtag = tag.p;
-      L.gmask = n - 1;
     }
     if (total) {
       ProfScope ps(impl == 3 ? "leaf_group_dense" : "leaf_group_hash", s, F.n, total);
@@ -2558,7 +2571,7 @@ bool group_in_place(const lh_plan_t* p, const Frontier& F, ElemArgs& a, uint64_t
         want = std::max(want, 2 * std::min<uint64_t>(space, n_emit));
       }
       while (cap < want) cap <<= 1;
-      if (cap > (1ull << 31) || cap * hash_bytes > (16ull << 30)) return false;
+      if (cap > (1ull << 31) || cap * hash_bytes > hash_limit) return false;
       continue;
     }
     break;
