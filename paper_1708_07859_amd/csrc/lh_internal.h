@@ -279,7 +279,8 @@ struct lh_trie {
   uint64_t root_span = 0;
   lh::View<uint64_t> root_bits;
   lh::View<uint32_t> root_rank;
-  // the bitset words of all levels and the root index, and a rank per word
+  // the bitset words of all levels and the root index, and a rank per word (of
+  // a set's last level: none)
   lh::DBuf<uint64_t> words;
   lh::DBuf<uint32_t> ranks;
   // two-level tries whose column statistics were taken: the rows sorted by

@@ -454,14 +454,15 @@ static void build_layouts(lh_trie* t, uint32_t mode, const std::vector<DBuf<uint
   t->words.alloc(all, s);
   ProfScope ps("layout_fill", s, total, all);
   LH_HIP(hipMemsetAsync(t->words.p, 0, all * sizeof(uint64_t), s));
-  t->ranks.alloc(all, s);
+  // positions inside bitset sets are needed when a deeper level hangs below or
+  // the rows of a bag are reached through them: a set's last level has no ranks
+  const uint64_t ranked = base[(t->flags & LH_BAG) ? nl : nl - 1];
+  t->ranks.alloc(ranked + root_words, s);
   for (uint32_t l = 0; l < nl; l++) {
     Level& L = t->lv[l];
     L.pool_words = base[l + 1] - base[l];
     if (!L.pool_words) continue;
     L.pool.p = t->words.p + base[l];
-    // positions inside bitset sets are needed when a deeper level hangs
-    // below or the rows of a bag are reached through them
     if (l + 1 < nl || (t->flags & LH_BAG)) L.bs_rank.p = t->ranks.p + base[l];
     k_layout_fill<<<grid_for(L.n), 256, 0, s>>>(L.keys.p, l ? parent[l].p : nullptr, L.n, L.bs_word.p, L.bs_base.p,
                                                 L.pool.p, L.bs_rank.p);
@@ -470,7 +471,7 @@ static void build_layouts(lh_trie* t, uint32_t mode, const std::vector<DBuf<uint
   if (root_words) {
     t->root_span = span;
     t->root_bits.p = t->words.p + base[nl];
-    t->root_rank.p = t->ranks.p + base[nl];
+    t->root_rank.p = t->ranks.p + ranked;
     k_layout_fill<<<grid_for(n0), 256, 0, s>>>(t->lv[0].keys.p, nullptr, n0, nullptr, nullptr, t->root_bits.p,
                                                t->root_rank.p);
     LH_HIP(hipGetLastError());
