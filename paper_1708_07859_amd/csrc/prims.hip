@@ -422,7 +422,7 @@ struct RsArgs {
 // 64), item i of lane l at offset i * 64 + l, so a wave's items in order are
 // the input order.  A wave ranks its items one after another against digit
 // counters of its own (eight ballots find a lane's equal-digit peers; no
-// barrier between items, the wave's LDS operations run in order), one prefix
+// block barrier between items, the wave's LDS operations run in order), one prefix
 // over the waves per digit places every element in LDS in digit order, and
 // the tile is written out in that order, each digit's run to consecutive
 // slots.  The key, its low word and its value go through the same LDS one
@@ -515,7 +515,10 @@ __global__ __launch_bounds__(RS_NT, WIDE || ONE ? 4 : 8) void k_rs_pass(RsArgs a
       const uint32_t pre = valid ? wcnt[w][d] : 0u;
       lp[i] = pre + below;
       // the lowest peer moves the wave's count on, after every peer has read it
+      // and before any lane reads it for the next item
+      wave_lds_sync();
       if (valid && below == 0) wcnt[w][d] = pre + (uint32_t)__popcll(peers);
+      wave_lds_sync();
     }
     __syncthreads();
     uint32_t c = 0;
