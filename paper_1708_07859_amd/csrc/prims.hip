@@ -441,7 +441,6 @@ struct RsArgs {
 template <int VB, bool FROM_COLS, bool TO_COLS, bool WIDE, bool ONE>
 __global__ __launch_bounds__(RS_NT, WIDE || ONE ? 4 : 8) void k_rs_pass(RsArgs a) {
   __shared__ __align__(16) unsigned char s_raw[RS_TILE * 8];
-  __shared__ uint32_t s_lstart[256];  // first slot of each digit in the tile
   __shared__ uint32_t s_gbase[256];   // global slot of tile slot 0, per digit (modulo 2^32)
   __shared__ uint32_t s_red[RS_NW];
   __shared__ uint32_t s_tile;
@@ -537,7 +536,6 @@ __global__ __launch_bounds__(RS_NT, WIDE || ONE ? 4 : 8) void k_rs_pass(RsArgs a
     uint32_t gstart = 0;  // first slot of digit tid in the output
     if constexpr (!ONE) gstart = block_excl_scan<uint32_t, RS_NT>(tid < 256 ? a.hist[tid] : 0u, s_red, tot);
     if (tid < 256) {
-      s_lstart[tid] = lstart;
       uint32_t slot = lstart;
 #pragma unroll
       for (int j = 0; j < RS_NW; j++) {
@@ -1032,10 +1030,15 @@ struct RadixIO {
   uint32_t phase = 0;
 };
 
+// (keys that are no columns have one word, and a row number or nothing with them)
 template <int VB, bool WIDE>
 void launch_one_tile(const RadixIO& io, const RsArgs& a, hipStream_t s) {
-  if (io.from_cols) k_rs_pass<VB, true, true, WIDE, true><<<1, RS_NT, 0, s>>>(a);
-  else k_rs_pass<VB, false, false, WIDE, true><<<1, RS_NT, 0, s>>>(a);
+  if (io.from_cols) {
+    k_rs_pass<VB, true, true, WIDE, true><<<1, RS_NT, 0, s>>>(a);
+  } else {
+    if constexpr (WIDE || VB == 8) fail(LH_ERR_UNSUPPORTED, "radix sort: wide keys or values without columns");
+    else k_rs_pass<VB, false, false, false, true><<<1, RS_NT, 0, s>>>(a);
+  }
   LH_HIP(hipGetLastError());
 }
 
