@@ -94,23 +94,17 @@ struct DBuf {  // owning device buffer, freed on the stream it was made on
   }
 };
 
-// A small pinned host buffer per host thread, kept until the process ends.
+// A small pinned host buffer per host thread; a thread that ends leaves its
+// own to the next one (runtime.cpp), so there are as many as threads at once.
 // Kernels store the few words that the host waits for straight into it
 // (a store and a wait cost 12 us, a copy of a device scalar into pinned
 // memory 15 us, into pageable memory 22 us).  A thread's next use overwrites
 // it: read the words right after the wait.
 constexpr size_t PINNED_BYTES = 4096;
-inline void*& pinned_slot() {
-  thread_local void* p = nullptr;
-  return p;
-}
-inline void* pinned_scratch() {
-  void*& p = pinned_slot();
-  if (!p) LH_HIP(hipHostMalloc(&p, PINNED_BYTES, hipHostMallocPortable));
-  return p;
-}
+void* pinned_or_null();   // this thread's, if it has one
+void* pinned_scratch();
 // The same, or null when an arena forbids allocating it now.
-inline void* pinned_scratch_or_null() { return arena_active() ? pinned_slot() : pinned_scratch(); }
+inline void* pinned_scratch_or_null() { return arena_active() ? pinned_or_null() : pinned_scratch(); }
 
 template <class T>
 T read_scalar(const T* dptr, hipStream_t s) {

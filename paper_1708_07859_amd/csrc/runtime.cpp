@@ -109,6 +109,44 @@ void register_arena_range(void* base, size_t cap) {
   g_arena_ranges.emplace_back(b, b + cap);
 }
 
+// ---- pinned words -----------------------------------------------------------
+// Every use waits for its stream before the call returns, so a buffer left by
+// an ended thread has no store under way.  (The list is never destroyed: the
+// main thread may end after it would be.)
+namespace {
+std::mutex g_pinned_mu;
+std::vector<void*>& spare_pinned() {
+  static std::vector<void*>* v = new std::vector<void*>();
+  return *v;
+}
+
+struct PinnedSlot {
+  void* p = nullptr;
+  ~PinnedSlot() {
+    if (!p) return;
+    std::lock_guard<std::mutex> lk(g_pinned_mu);
+    spare_pinned().push_back(p);
+  }
+};
+thread_local PinnedSlot t_pinned;
+}  // namespace
+
+void* pinned_or_null() { return t_pinned.p; }
+
+void* pinned_scratch() {
+  if (t_pinned.p) return t_pinned.p;
+  {
+    std::lock_guard<std::mutex> lk(g_pinned_mu);
+    if (!spare_pinned().empty()) {
+      t_pinned.p = spare_pinned().back();
+      spare_pinned().pop_back();
+      return t_pinned.p;
+    }
+  }
+  LH_HIP(hipHostMalloc(&t_pinned.p, PINNED_BYTES, hipHostMallocPortable));
+  return t_pinned.p;
+}
+
 bool arena_active() { return t_arena != nullptr; }
 bool arena_tight() { return t_arena && t_arena->tight; }
 

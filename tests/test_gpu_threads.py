@@ -80,3 +80,20 @@ def test_short_lived_threads(lh):
     want = queries(lh, 300)
     for r in range(20):
         in_threads(lambda k: (queries(lh, 300) == want) or pytest.fail("another result"), 3)
+
+
+def test_ended_threads_leave_nothing(lh):
+    """Host memory mapped for a thread's words is there for the next thread."""
+    import torch
+    key = torch.arange(100, device="cuda", dtype=torch.int32)
+
+    def mapped():
+        with open("/proc/self/maps") as f:
+            return len(f.readlines())
+
+    for r in range(10):
+        in_threads(lambda k: lh.trie_build([key]).free(), 2)
+    before = mapped()
+    for r in range(200):
+        in_threads(lambda k: lh.trie_build([key]).free(), 2)
+    assert mapped() < before + 100
