@@ -19,39 +19,44 @@ def lh():
     return binding
 
 
+@pytest.mark.parametrize("wide", [True, False])
 @pytest.mark.parametrize("agg", ["sum", "count"])
 @pytest.mark.parametrize("where", ["prefix", "dense"])
-@pytest.mark.parametrize("used", [0, 1, 700, 49_999, 50_000, 200_000])
-def test_rows_of_many_possible_groups(lh, where, agg, used):
-    """200,000 possible groups (an attribute of the order's prefix, or outside it), `used` with a tuple."""
+@pytest.mark.parametrize("used", [700, 0, 1, 59_999, 60_000, 240_000])
+def test_rows_of_many_possible_groups(lh, where, agg, used, wide):
+    """240,000 possible groups (attributes of the order's prefix, or outside it), `used` with a tuple;
+    rows of one key column, or of six."""
     import torch
-    print(where, agg, used, file=sys.stderr, flush=True)
+    print(where, agg, used, wide, file=sys.stderr, flush=True)
     rng = synth.rng_for(67)
-    n = 200_000
+    n, w = 240_000, 6 if wide else 1
+    outs = list(range(w))
     i, j = np.arange(n, dtype=np.uint32), rng.permutation(n).astype(np.uint32)
     v = synth.uniform_pm1(rng, n)
     hit = np.sort(rng.choice(n, used, replace=False)) if used < n else np.arange(n)
     on = np.sort(j[hit]) if used else np.array([n + 5], np.uint32)
     tx = lh.trie_build([on], [np.full(len(on), 0.5)], bag=True)
-    if where == "prefix":
-        ta = lh.trie_build([i, j], [v], bag=True)
-        p = lh.plan(2, [(ta, [0, 1], 0), (tx, [1], 0)], out=[0], agg=agg, attr_order=[0, 1], policy="fixed")
-    else:
-        ta = lh.trie_build([j, i], [v], bag=True)
-        p = lh.plan(2, [(ta, [1, 0], 0), (tx, [1], 0)], out=[0], agg=agg, attr_order=[1, 0], policy="fixed",
-                    group_impl="dense")
+    cols = [i] + [np.zeros(n, np.uint32)] * (w - 1)
+    order = outs + [w] if where == "prefix" else [w] + outs
+    ta = lh.trie_build(cols + [j] if where == "prefix" else [j] + cols, [v], bag=True)
+    p = lh.plan(w + 1, [(ta, order, 0), (tx, [w], 0)], out=outs, agg=agg, attr_order=order, policy="fixed",
+                group_impl="dense" if where == "dense" else "auto")
     lh.join_aggregate([p])
     torch.cuda.synchronize()
     free = torch.cuda.mem_get_info()[0]
     kept = [lh.join_aggregate([p])[0] for _ in range(40)]
     held = free - torch.cuda.mem_get_info()[0]
-    row = 4 + 8 + (8 if agg == "sum" else 0)
+    row = 4 * w + 8 + (8 if agg == "sum" else 0)
     print("held", held, file=sys.stderr, flush=True)
-    # (what the rows take four times over, and 1 MiB a result and 32 MiB in all for roundings)
-    assert held <= 40 * (4 * used * row + (1 << 20)) + (32 << 20)
+    # rows for the used groups alone, or for all where those take 6 MiB at most or are filled to a quarter;
+    # a column past 1 MiB is rounded to 2 MiB, and 32 MiB in all are left for other roundings
+    rows = used if n * row > 6 << 20 and used < n // 4 else n
+    sizes = [4 * rows] * w + [8 * rows] * (2 if agg == "sum" else 1)
+    assert held <= 40 * sum(-(-x // (2 << 20)) * (2 << 20) if x > 1 << 20 else x + 512 for x in sizes) + (32 << 20)
     for r in (kept[0], kept[-1]):
         got = r.to_host()
-        assert np.array_equal(got["keys"][:, 0], hit) if used else len(got["keys"]) == 0
+        assert len(got["keys"]) == used
+        assert np.array_equal(got["keys"][:, 0], hit) and not got["keys"][:, 1:].any()
         assert (got["counts"] == 1).all()
         if agg == "sum":
             assert np.array_equal(got["sums"], 0.5 * v[hit])
