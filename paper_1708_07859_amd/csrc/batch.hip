@@ -127,12 +127,16 @@ __global__ void k_inst_roots(BInst* inst, uint32_t n) {
   }
 }
 
-// Products of entry q of A's second level: pairs of a row of A and a row of
-// E (bags may repeat a key pair on either side).  outs: at most this many
-// outputs (E's keys k under the entry).
-__device__ __forceinline__ uint64_t entry_products(const BInst& I, uint32_t q, uint64_t& outs) {
+// What entries of A's second level contribute to their row.
+struct RowTotals {
+  uint64_t prod = 0;  // products: pairs of a row of A and a row of E (bags may repeat a key pair on either side)
+  uint64_t upd = 0;   // a matrix's scattered updates: rows of A times distinct keys of E (the classes go by these:
+                      //   a key's repeated rows are summed where it was found)
+};
+
+__device__ __forceinline__ void add_entry(const BInst& I, uint32_t q, RowTotals& r) {
   uint32_t pe;
-  if (!find_j(I, I.a_j[q], pe)) return 0;
+  if (!find_j(I, I.a_j[q], pe)) return;
   uint32_t ab, ae, eb, ee;
   rows_of(I.a_run, q, ab, ae);
   if (I.kind == 0) {
@@ -140,13 +144,13 @@ __device__ __forceinline__ uint64_t entry_products(const BInst& I, uint32_t q, u
   } else {
     eb = I.e_off[pe];
     ee = I.e_off[pe + 1];
-    outs += ee - eb;
+    r.upd += (uint64_t)(ae - ab) * (ee - eb);
     if (I.e_run) {
       eb = I.e_run[eb];
       ee = I.e_run[ee];
     }
   }
-  return (uint64_t)(ae - ab) * (ee - eb);
+  r.prod += (uint64_t)(ae - ab) * (ee - eb);
 }
 
 // Every row's instance, products and output bound.  A thread walks a row of
@@ -155,7 +159,8 @@ __device__ __forceinline__ uint64_t entry_products(const BInst& I, uint32_t q, u
 // 12.5 ms of a 16-instance setup; now 0.1 ms).
 constexpr uint32_t ROW_THREAD = 16, ROW_WAVE = 2048;
 __global__ __launch_bounds__(B_NT) void k_row_products(const BInst* inst, const uint64_t* inst_row0, uint32_t n_inst,
-                                                       uint64_t R, uint32_t* row_inst, uint64_t* prod, uint32_t* ub) {
+                                                       uint64_t R, uint32_t* row_inst, uint64_t* prod, uint64_t* upd,
+                                                       uint32_t* ub) {
   __shared__ uint32_t s_long[B_NT];
   __shared__ uint32_t s_n;
   __shared__ uint64_t s_red[B_NW];
@@ -172,9 +177,9 @@ __global__ __launch_bounds__(B_NT) void k_row_products(const BInst* inst, const 
       len = inst[ii].a_off[p + 1] - qb;
       row_inst[t] = ii;
     }
-    uint64_t u = 0, o = 0;
+    RowTotals u;
     if (len <= ROW_THREAD) {
-      for (uint32_t q = qb; q < qb + len; q++) u += entry_products(inst[ii], q, o);
+      for (uint32_t q = qb; q < qb + len; q++) add_entry(inst[ii], q, u);
     } else if (len > ROW_WAVE) {
       s_long[atomicAdd(&s_n, 1u)] = threadIdx.x;
     }
@@ -182,14 +187,11 @@ __global__ __launch_bounds__(B_NT) void k_row_products(const BInst* inst, const 
       const int l = __builtin_ctzll(m);
       const BInst& I = inst[__shfl((int)ii, l, WAVE)];
       const uint32_t b = (uint32_t)__shfl((int)qb, l, WAVE), n = (uint32_t)__shfl((int)len, l, WAVE);
-      uint64_t v = 0, vo = 0;
-      for (uint32_t k = lane; k < n; k += WAVE) v += entry_products(I, b + k, vo);
-      v = wave_sum(v);
-      vo = wave_sum(vo);
-      if (lane == l) {
-        u = v;
-        o = vo;
-      }
+      RowTotals v;
+      for (uint32_t k = lane; k < n; k += WAVE) add_entry(I, b + k, v);
+      v.prod = wave_sum(v.prod);
+      v.upd = wave_sum(v.upd);
+      if (lane == l) u = v;
     }
     __syncthreads();
     for (uint32_t i = 0; i < s_n; i++) {  // uniform over the block
@@ -198,35 +200,33 @@ __global__ __launch_bounds__(B_NT) void k_row_products(const BInst* inst, const 
       const BInst& I = inst[il];
       const uint32_t p = (uint32_t)(tl - inst_row0[il]);
       const uint32_t b = I.a_off[p], e = I.a_off[p + 1];
-      uint64_t v = 0, vo = 0;
+      RowTotals v;
       for (uint32_t k = b + threadIdx.x; k < e; k += 4 * B_NT) {
 #pragma unroll
         for (int j = 0; j < 4; j++)
-          if (k + j * B_NT < e) v += entry_products(I, k + j * B_NT, vo);
+          if (k + j * B_NT < e) add_entry(I, k + j * B_NT, v);
       }
-      v = block_sum<uint64_t, B_NT>(v, s_red);
-      vo = block_sum<uint64_t, B_NT>(vo, s_red);
-      if (threadIdx.x == s_long[i]) {
-        u = v;
-        o = vo;
-      }
+      v.prod = block_sum<uint64_t, B_NT>(v.prod, s_red);
+      v.upd = block_sum<uint64_t, B_NT>(v.upd, s_red);
+      if (threadIdx.x == s_long[i]) u = v;
     }
     if (t < R) {
-      prod[t] = u;
-      ub[t] = inst[ii].kind == 0 ? 1u : (uint32_t)min<uint64_t>(o, inst[ii].n_k);
+      prod[t] = u.prod;
+      if (upd) upd[t] = u.upd;
+      ub[t] = inst[ii].kind == 0 ? 1u : (uint32_t)min<uint64_t>(u.upd, inst[ii].n_k);
     }
     __syncthreads();  // s_long and s_n are free again
   }
 }
 
-// The class of every row under a tuning; n_inner[instance] is set where the
-// instance has inner-product rows.
-__global__ void k_row_classes(const BInst* inst, const uint32_t* row_inst, const uint64_t* prod, uint64_t R,
+// The class of every row, by its updates, under a tuning; n_inner[instance] is
+// set where the instance has inner-product rows.
+__global__ void k_row_classes(const BInst* inst, const uint32_t* row_inst, const uint64_t* upd, uint64_t R,
                               uint32_t light_max, uint32_t inner_ratio, uint32_t* is_heavy, uint32_t* is_light,
                               uint32_t* is_inner, uint32_t* n_inner) {
   for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < R; t += (uint64_t)gridDim.x * blockDim.x) {
     const BInst& I = inst[row_inst[t]];
-    const uint64_t u = prod[t];
+    const uint64_t u = upd[t];
     const bool heavy = I.kind == 1 && u > light_max;
     // inner-product form when walking all of E costs less than inner_ratio
     // scattered updates per product
@@ -1059,6 +1059,8 @@ struct BatchState {
   hipStream_t s = nullptr;
   DBuf<BInst> inst;
   DBuf<uint64_t> inst_row0, prod, ub_off;
+  DBuf<uint64_t> upd;          // updates per row, where they are not its products (some E repeats key pairs)
+  const uint64_t* updates() const { return upd.p ? upd.p : prod.p; }
   std::vector<uint64_t> h_nj;   // join tuples per instance (fixed by the plans)
   DBuf<uint32_t> row_inst, ub, heavy_f, light_f, inner_f, heavy, light, inner, qhead, row_nnz, ub_k, err;
   std::shared_ptr<Transposes> tr;
@@ -1221,9 +1223,12 @@ void setup_rows(BatchState& b, hipStream_t s) {
   b.row_inst.alloc(b.R, s);
   b.prod.alloc(b.R, s);
   b.ub.alloc(b.R, s);
+  bool repeats = false;
+  for (const BInst& I : b.h_inst) repeats = repeats || (I.kind == 1 && I.e_run);
+  b.upd.alloc(repeats ? b.R : 0, s);
   if (b.R) {
     k_row_products<<<(unsigned)std::min<uint64_t>((b.R + B_NT - 1) / B_NT, 1u << 16), B_NT, 0, s>>>(
-        b.inst.p, b.inst_row0.p, n, b.R, b.row_inst.p, b.prod.p, b.ub.p);
+        b.inst.p, b.inst_row0.p, n, b.R, b.row_inst.p, b.prod.p, b.upd.p, b.ub.p);
     LH_HIP(hipGetLastError());
   }
   b.ub_off.alloc(b.R + 1, s);
@@ -1265,7 +1270,7 @@ void setup_classes(BatchState& b, hipStream_t s) {
   if (!b.R) return;
   DBuf<uint32_t> has_inner(n, s);
   fill_u32(has_inner.p, 0, n, s);
-  k_row_classes<<<grid_for(b.R), 256, 0, s>>>(b.inst.p, b.row_inst.p, b.prod.p, b.R, b.tune.light_max,
+  k_row_classes<<<grid_for(b.R), 256, 0, s>>>(b.inst.p, b.row_inst.p, b.updates(), b.R, b.tune.light_max,
                                               b.tune.inner_ratio, b.heavy_f.p, b.light_f.p, b.inner_f.p, has_inner.p);
   LH_HIP(hipGetLastError());
   std::vector<uint32_t> h(n);
@@ -1290,7 +1295,7 @@ void setup_classes(BatchState& b, hipStream_t s) {
     // heavy rows longest first (LPT)
     DBuf<uint64_t> k0(b.n_heavy, s), k1(b.n_heavy, s);
     DBuf<uint32_t> other(b.n_heavy, s);
-    k_heavy_keys<<<grid_for(b.n_heavy), 256, 0, s>>>(b.heavy.p, b.n_heavy, b.prod.p, k0.p);
+    k_heavy_keys<<<grid_for(b.n_heavy), 256, 0, s>>>(b.heavy.p, b.n_heavy, b.updates(), k0.p);
     LH_HIP(hipGetLastError());
     uint64_t* const kb[2] = {k0.p, k1.p};
     uint32_t* const vb[2] = {b.heavy.p, other.p};
