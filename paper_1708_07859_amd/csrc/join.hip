@@ -32,7 +32,13 @@ constexpr int U_EL = WAVE * U_IT;  // driver elements per unit of a whole wave
 // left 246 of its 256 element slots idle on rows of ten (SpGEMM, SpMV,
 // small graphs), and every row paid a whole wave's reduction.  Taken when
 // the smallest participating level's sets hold at most SUB_AVG elements on
-// average; longer rows cost only more units.
+// average; longer rows cost only more units.  Whole joins over 4 M elements in
+// rows of one length, microseconds with a wave / with eight lanes:
+//   row length        8           24          32          64         128         256
+//   SUM          1059 / 253   430 / 187   352 / 178   231 / 190   207 / 195   212 / 220
+//   fill          659 / 196   297 / 135   252 / 128   183 / 125   143 / 124   133 / 134
+// Past the line, rows of one length would gain up to about 128 elements; at it
+// all that was measured gains, hub rows among short ones too.
 // SpMV of 250,000 power-law rows (4 M entries): the leaf 1.56 -> 0.23 ms,
 // with sums stored by a row's only unit and carried over a hub row's units;
 // Q5 shape at 24 M rows: its three SUM leaves 1.6 -> 0.33 ms.
@@ -2039,7 +2045,9 @@ struct JoinEnd {
 
 // Up to this many possible groups, and bytes of result rows for them, the
 // result's buffers are sized for all of them, and their number is read with
-// the rest at the end of the join: a wait less (about 10 us).  A result may be
+// the rest at the end of the join: a wait less (SpMV of 1000, 120,000 and
+// 250,000 rows: 223 -> 211, 316 -> 305, 389 -> 378 us; of 400,000, past the
+// line, 458 against 449), for 5 MB of one key, count and sum.  A result may be
 // kept for long, so one that turns out to fill less than a quarter of buffers
 // past KEEP_BYTES moves to smaller ones.  That takes a copy and a wait (20,000
 // of 200,000 groups: 172 -> 192 us), so rows of two keys, count and sum stay.
