@@ -2126,20 +2126,26 @@ __global__ void k_seg_accumulate(SegAccArgs a, uint64_t n) {
 // A dispatch counts work-items in 32 bits: cap the grid and let blocks
 // stride over virtual blocks.
 unsigned elem_grid(uint64_t nvblk) { return (unsigned)std::max<uint64_t>(1, std::min<uint64_t>(nvblk, 32768)); }
-// Blocks that carry grouped sums take up to CARRY_RUN virtual blocks next to
-// each other, so that a hub row's units meet in fewer of them, and stride over
-// the rest: long runs of an expanding atom often lie near each other (the
-// repeated edges of low vertices, popular items), and a block that took
-// a 2048th of all units had them alone.  Microseconds with 1 / 2 / 4 / 8 next
-// to each other, with such ranges, and with a wave per row (before carrying):
-//   SpMV, 250,000 power-law rows (no runs)      465 /  446 /  434 /  475,   447,  2241
-//   SUM over hub rows (no runs)                5555 / 4852 / 4558 / 4363,  4465, 12889
-//   SpMV, R-MAT scale 20 with its repeats      1507 / 1504 / 1855 / 2665,  8024,  3723
-//   24 M rows of runs in 4000 of 2 M rows      1982 / 3701 / 7200 / 13985, 53442, 11872
+// Blocks that carry grouped sums take virtual blocks next to each other, so
+// that a hub row's units, and a large group's rows, meet in few of them: one
+// range each, of at most CARRY_BLOCKS, where every hit has few terms.  Longer runs
+// of an expanding atom often lie near each other (the repeated edges of low
+// vertices, popular items), and a range's block had them alone: the more terms
+// a hit may have, the fewer virtual blocks next to each other (a block's at
+// worst are CARRY_EVEN times a range's at best), down to CARRY_RUN, and a block
+// strides over the rest.  Microseconds with 1 / 2 / 4 / 8 next to each other and
+// striding, with ranges, and with a wave per row (before carrying):
+//   24 M rows of runs in 4000 of 2 M rows      1982 / 3701 / 7150 / 13985, 53442, 11872
+//   SpMV, R-MAT scale 20 with its repeats      1507 / 1504 / 1833 /  2665,  8024,  3723
+//   SpMV, 250,000 power-law rows (no runs)      465 /  446 /  434 /   475,   447,  2241
+//   SUM over hub rows (no runs)                5555 / 4852 / 4558 /  4363,  4465, 12889
+//   SUM of 60 M products in 25 groups             - /    - / 5953 /     -,  4736, 84711
+//     (runs of up to nine: 271 next to each other by the rule, 4605)
 // One group needs no neighbours: SUM over R-MAT scale 18 paths of two takes
 // 50 ms, 531 with ranges, 92 with a wave per row.
 constexpr uint64_t CARRY_BLOCKS = 2048, CARRY_MAX_BLOCKS = 8192;
 constexpr uint64_t CARRY_RUN = 4;
+constexpr uint64_t CARRY_EVEN = 8;
 // The merge launch: as many blocks as fit on the device at once; each loops
 // over a contiguous range of tiles, loading the next while counting one.
 unsigned merge_grid() {
@@ -2949,7 +2955,12 @@ lh_result_impl* run_plan(const lh_plan_t* p, hipStream_t s) {
         ProfScope ps("leaf_aggregate", s, F.n, total);
         if (all_set) launch_elem<M_LEAF_COUNT>(a, elem_grid(nblk), s);
         else {
-          if (L.gid) a.vrun = (uint32_t)std::min<uint64_t>(CARRY_RUN, (nblk + CARRY_BLOCKS - 1) / CARRY_BLOCKS);
+          constexpr uint64_t many = 1u << 20;
+          uint64_t terms = 1;  // of a hit, at most
+          for (uint32_t e = 0; e < na; e++)
+            if (L.at[e].expand && p->atoms[e].bag) terms = std::min(many, terms * std::min(many, p->atoms[e].trie->max_run));
+          const uint64_t range = (nblk + CARRY_BLOCKS - 1) / CARRY_BLOCKS;
+          if (L.gid) a.vrun = (uint32_t)std::min(range, std::max(CARRY_RUN, range * CARRY_EVEN / std::max<uint64_t>(1, terms)));
           const uint64_t runs = (nblk + a.vrun - 1) / a.vrun;
           launch_elem<M_LEAF_A>(a, (unsigned)std::min<uint64_t>(runs, CARRY_MAX_BLOCKS), s);
         }
