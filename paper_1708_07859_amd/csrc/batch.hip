@@ -961,7 +961,7 @@ struct PackArgs2 {
 // rows from the current one are loaded by the lanes and each lane finds its
 // output's row among them by bisecting across the lanes.  Rows without
 // outputs leave the row further on: PACK_WINDOWS windows are looked at, then
-// each lane bisects the offsets itself (150 outputs of two 2 M-row matrices:
+// each lane bisects the offsets itself (3150 outputs of two 2 M-row matrices:
 // 31.5 ms a call walking every window, 0.86 with the bisection, 5.2 with a
 // wave per 64 rows).
 constexpr uint32_t PACK_SPAN = 2048;
