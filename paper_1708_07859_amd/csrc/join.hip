@@ -47,7 +47,8 @@ constexpr int U_EL = WAVE * U_IT;  // driver elements per unit of a whole wave
 // whole waves (hubs of 20,000 keys below an average of 11: 1.91 -> 1.40 ms, a
 // wave per unit at first 1.67), and so does a leaf with more than
 // SUB_MAX_UNITS units (their rows take four bytes each; below, leaves are as
-// fast or faster with eight lanes: 4.48 and 4.58 ms).
+// fast or faster with eight lanes: 4.48 and 4.58 ms).  Where the static scratch
+// was full the join takes what needs less of it.
 constexpr int SUB_LANES = 8;
 constexpr uint64_t SUB_AVG = 24;
 constexpr uint64_t SUB_MAX_UNITS = 1ull << 28;
@@ -2256,7 +2257,7 @@ void depth_work(const lh_plan_t* p, uint32_t d, const Frontier& F, ElemArgs& a, 
     const Level& L = p->atoms[pt.atom].trie->lv[pt.level];
     avg = std::min(avg, L.n / std::max<uint64_t>(1, L.n_sets));
   }
-  a.lanes = !leaf2 && wa.np <= 4 && avg <= SUB_AVG && !arena_tight() ? SUB_LANES : WAVE;
+  a.lanes = !leaf2 && wa.np <= 4 && avg <= SUB_AVG ? SUB_LANES : WAVE;
   if (d == 0 && !leaf2) {
     root_work(p, parts, a, dw);
   } else {
@@ -2284,8 +2285,12 @@ void depth_work(const lh_plan_t* p, uint32_t d, const Frontier& F, ElemArgs& a, 
       dw.total = h.work;
       dw.top = h.top;
       dw.merge = h.merge;
+      if (a.lanes == WAVE) break;
+      const uint64_t wave_units = h.work / U_EL + F.n;  // at most
       const bool long_rows = h.work / U_EL > F.n;
-      if (a.lanes == WAVE || !(h.units >= (1ull << 32) || (long_rows && (fill || h.units > SUB_MAX_UNITS)))) break;
+      // (bytes: a unit's row, and its share of a block's count and offset)
+      const bool smaller = arena_tight() && 7 * wave_units < 5 * h.units;
+      if (!smaller && h.units < (1ull << 32) && !(long_rows && (fill || h.units > SUB_MAX_UNITS))) break;
       a.lanes = WAVE;
     }
   }
